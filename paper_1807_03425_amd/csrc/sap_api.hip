@@ -264,22 +264,29 @@ static sap_status load_P(sap_ctx *h, const double *P_dev) {
 
 // ---------------------------------------------------------------- init pieces
 
+template <typename TX>
+static sap_status launch_moments(sap_ctx *h, double *part, int64_t nblk, int64_t rows) {
+    const TX *X = static_cast<const TX *>(h->X);
+    hipLaunchKernelGGL(k_col_partial<TX>, dim3((unsigned)nblk), dim3(256), 0, h->stream, X, h->ldx, h->N, h->n, rows,
+                       part, &h->d_st->nonfinite);
+    SAP_LAUNCHED(h, "k_col_partial");
+    hipLaunchKernelGGL(k_col_mean, dim3((unsigned)ceil_div(h->n, 256)), dim3(256), 0, h->stream,
+                       part, nblk, h->n, h->N, h->d_mu);
+    SAP_LAUNCHED(h, "k_col_mean");
+    hipLaunchKernelGGL(k_radius<TX>, dim3((unsigned)std::min<int64_t>(ceil_div(h->N, 4), 2048)), dim3(256), 0, h->stream,
+                       X, h->ldx, h->N, h->n, h->d_mu, reinterpret_cast<unsigned long long *>(&h->d_st->radius_bits));
+    SAP_LAUNCHED(h, "k_radius");
+    return SAP_OK;
+}
+
 static sap_status init_moments(sap_ctx *h) {
     const int64_t rows = 256;
     const int64_t nblk = ceil_div(h->N, rows);
     double *part = nullptr;
     SAP_TRY(dalloc(h, &part, sizeof(double) * nblk * h->n));
     SAP_HIP(h, hipMemsetAsync(h->d_st, 0, sizeof(DevState), h->stream));
-    hipLaunchKernelGGL(k_col_partial, dim3((unsigned)nblk), dim3(256), 0, h->stream, h->X,
-                       h->cfg.dtype, h->ldx, h->N, h->n, rows, part, &h->d_st->nonfinite);
-    SAP_LAUNCHED(h, "k_col_partial");
-    hipLaunchKernelGGL(k_col_mean, dim3((unsigned)ceil_div(h->n, 256)), dim3(256), 0, h->stream,
-                       part, nblk, h->n, h->N, h->d_mu);
-    SAP_LAUNCHED(h, "k_col_mean");
-    hipLaunchKernelGGL(k_radius, dim3((unsigned)ceil_div(h->N, 4)), dim3(256), 0, h->stream, h->X,
-                       h->cfg.dtype, h->ldx, h->N, h->n, h->d_mu,
-                       reinterpret_cast<unsigned long long *>(&h->d_st->radius_bits));
-    SAP_LAUNCHED(h, "k_radius");
+    if (h->cfg.dtype == SAP_F64) SAP_TRY(launch_moments<double>(h, part, nblk, rows));
+    else SAP_TRY(launch_moments<float>(h, part, nblk, rows));
     DevState st;
     SAP_HIP(h, hipMemcpyAsync(&st, h->d_st, sizeof st, hipMemcpyDeviceToHost, h->stream));
     SAP_HIP(h, hipStreamSynchronize(h->stream));
@@ -367,11 +374,19 @@ static sap_status init_fused(sap_ctx *h) {
     SAP_TRY(dalloc(h, &d_ladder, sizeof(float) * 64));
     SAP_HIP(h, hipMemcpyAsync(d_ladder, ladder.data(), sizeof(float) * 64, hipMemcpyHostToDevice, h->stream));
     const unsigned grid = (unsigned)std::min<int64_t>(h->ntiles, 8192);
-    hipLaunchKernelGGL(k_build_invd2, dim3(grid), dim3(256), 0, h->stream, h->X, h->cfg.dtype,
-                       h->ldx, h->N, h->n, h->d_tiles, h->ntiles, h->cfg.min_len, h->d_invd2,
-                       d_ladder, reinterpret_cast<unsigned long long *>(h->d_st->hist),
-                       reinterpret_cast<unsigned long long *>(&h->d_st->kept),
-                       reinterpret_cast<unsigned long long *>(&h->d_st->dropped));
+    {
+        auto *hist = reinterpret_cast<unsigned long long *>(h->d_st->hist);
+        auto *kept = reinterpret_cast<unsigned long long *>(&h->d_st->kept);
+        auto *drop = reinterpret_cast<unsigned long long *>(&h->d_st->dropped);
+        if (h->cfg.dtype == SAP_F64)
+            hipLaunchKernelGGL(k_build_invd2<double>, dim3(grid), dim3(256), 0, h->stream,
+                               static_cast<const double *>(h->X), h->ldx, h->N, h->n, h->d_tiles, h->ntiles,
+                               h->cfg.min_len, h->d_invd2, d_ladder, hist, kept, drop);
+        else
+            hipLaunchKernelGGL(k_build_invd2<float>, dim3(grid), dim3(256), 0, h->stream,
+                               static_cast<const float *>(h->X), h->ldx, h->N, h->n, h->d_tiles, h->ntiles,
+                               h->cfg.min_len, h->d_invd2, d_ladder, hist, kept, drop);
+    }
     SAP_LAUNCHED(h, "k_build_invd2");
     DevState st;
     SAP_HIP(h, hipMemcpyAsync(&st, h->d_st, sizeof st, hipMemcpyDeviceToHost, h->stream));

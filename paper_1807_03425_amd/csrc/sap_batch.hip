@@ -39,6 +39,7 @@
 
 #include <hip/hip_ext.h>
 
+#include "sap_dist.h"
 #include "sap_iter.hip"
 
 namespace sap {
@@ -107,8 +108,18 @@ __global__ __launch_bounds__(256) void k_batch_mean(BatchArgs a) {
     const BatchSet st = a.sets[s];
     const TX *X = static_cast<const TX *>(a.X);
     double acc = 0.0;
-    int bad = 0;
-    for (int p = 0; p < st.M; ++p) {
+    int bad = 0, p = 0;
+    for (; p + 16 <= st.M; p += 16) {   // 16 rows' loads in flight, the sum in point order
+        TX v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = X[(int64_t)a.pts[st.pt_off + p + u] * a.ldx + l];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            if (!isfinite(v[u])) bad = 1;
+            acc += (double)v[u];
+        }
+    }
+    for (; p < st.M; ++p) {
         const double v = (double)X[(int64_t)a.pts[st.pt_off + p] * a.ldx + l];
         if (!isfinite(v)) bad = 1;
         acc += v;
@@ -138,70 +149,58 @@ __global__ __launch_bounds__(256) void k_batch_radius(BatchArgs a) {
 }
 
 // 1/d^2 tiles of every set, by direct FP64 differences of the gathered rows
-// (the single-problem layout: element (r, c) of a tile at float index
-// (r/4)*256 + c*4 + r%4).  Dropped pairs (duplicates, d < the set's l) and
-// padding / i >= j hold -1.  Counts kept and dropped pairs per set and folds
-// the largest kept FP32 value into the set's statistics.
+// (tile_dist2; the single-problem layout: element (r, c) of a tile at float
+// index (r/4)*256 + c*4 + r%4).  Dropped pairs (duplicates, d < the set's l)
+// and padding / i >= j hold -1.  Counts kept and dropped pairs per set and
+// folds the largest kept FP32 value into the set's statistics.
 template <typename TX>
-__global__ __launch_bounds__(256) void k_batch_invd2(BatchArgs a, int64_t ntiles_all) {
-    __shared__ unsigned long long s_kept, s_drop;
-    __shared__ unsigned s_wmax;
-    const int c = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+__global__ __launch_bounds__(256, 4) void k_batch_invd2(BatchArgs a, int64_t ntiles_all) {
+    __shared__ __align__(16) DistLds L;
+    __shared__ unsigned s_kept, s_drop, s_wmax;
+    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
     const TX *X = static_cast<const TX *>(a.X);
     for (int64_t t = blockIdx.x; t < ntiles_all; t += gridDim.x) {
-        if (threadIdx.x == 0) { s_kept = 0; s_drop = 0; s_wmax = 0u; }
-        __syncthreads();
         const int4 tb = a.tiles[t];
         const BatchSet st = a.sets[tb.z];
         const double ml = a.set_min_len ? a.set_min_len[tb.z] : 0.0;
-        const int32_t *idx = a.pts + st.pt_off;
-        const int64_t j = (int64_t)tb.y * kTile + c;
-        const bool jin = j < st.M;
-        const TX *xj = X + (int64_t)idx[jin ? j : st.M - 1] * a.ldx;
-        unsigned mx = 0u;
-        for (int m = 0; m < 4; ++m) {
-            const int g = w + 4 * m;
-            const int64_t i0 = (int64_t)tb.x * kTile + 4 * g;
-            const TX *xi[4];
+        if (threadIdx.x == 0) { s_kept = 0u; s_drop = 0u; s_wmax = 0u; }
+        if (threadIdx.x < 2 * kTile) {
+            const int p = (threadIdx.x < kTile ? tb.x : tb.y) * kTile + (threadIdx.x & (kTile - 1));
+            L.row[threadIdx.x] = a.pts[st.pt_off + (p < st.M ? p : st.M - 1)];
+        }
+        __syncthreads();
+        double d2[4][4];
+        tile_dist2(X, a.ldx, a.n, L, d2);
+        const int i0 = tb.x * kTile + 4 * ty, j0 = tb.y * kTile + 4 * tx;
+        unsigned mx = 0u, nkept = 0u, ndrop = 0u;
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr) xi[rr] = X + (int64_t)idx[i0 + rr < st.M ? i0 + rr : st.M - 1] * a.ldx;
-            double d2[4] = {0.0, 0.0, 0.0, 0.0};
-            if (jin) {
-                for (int l = 0; l < a.n; ++l) {
-                    const double xv = (double)xj[l];
-#pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) {
-                        const double t2 = (double)xi[rr][l] - xv;
-                        d2[rr] += t2 * t2;
-                    }
-                }
-            }
+        for (int q = 0; q < 4; ++q) {
+            const int j = j0 + q;
             float out[4];
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const int64_t i = i0 + rr;
+            for (int r = 0; r < 4; ++r) {
                 float v = kMaskDropped;
-                if (jin && i < j) {
-                    const double d = sqrt(d2[rr]);
-                    if (d == 0.0 || d < ml) {
-                        atomicAdd(&s_drop, 1ull);
+                if (j < st.M && i0 + r < j) {
+                    if (d2[r][q] == 0.0 || (ml > 0.0 && sqrt(d2[r][q]) < ml)) {
+                        ++ndrop;
                     } else {
-                        v = (float)(1.0 / d2[rr]);
-                        atomicAdd(&s_kept, 1ull);
+                        v = (float)(1.0 / d2[r][q]);
+                        ++nkept;
                         mx = max(mx, __float_as_uint(v));
                     }
                 }
-                out[rr] = v;
+                out[r] = v;
             }
-            a.w[t * (kTileElems / 4) + g * 64 + c] = make_float4(out[0], out[1], out[2], out[3]);
+            a.w[t * (kTileElems / 4) + ty * 64 + 4 * tx + q] = make_float4(out[0], out[1], out[2], out[3]);
         }
+        atomicAdd(&s_kept, nkept);
+        atomicAdd(&s_drop, ndrop);
         atomicMax(&s_wmax, mx);
         __syncthreads();
         if (threadIdx.x == 0) {
             BatchStat *so = a.stat + tb.z;
-            if (s_kept) atomicAdd(reinterpret_cast<unsigned long long *>(&so->kept), s_kept);
-            if (s_drop) atomicAdd(reinterpret_cast<unsigned long long *>(&so->dropped), s_drop);
+            if (s_kept) atomicAdd(reinterpret_cast<unsigned long long *>(&so->kept), (unsigned long long)s_kept);
+            if (s_drop) atomicAdd(reinterpret_cast<unsigned long long *>(&so->dropped), (unsigned long long)s_drop);
             if (s_wmax) atomicMax(&so->wmax_bits, s_wmax);
         }
         __syncthreads();

@@ -11,22 +11,36 @@
 // Pairs that the method drops (duplicates; secants shorter than the length
 // threshold of Sec. 7) are masked in both forms.
 #include "sap_common.h"
+#include "sap_dist.h"
 
 namespace sap {
 
 // ---------------------------------------------------------------- moments
 
-// Block b sums rows [b*rows, (b+1)*rows) of every column, in row order.
-__global__ __launch_bounds__(256) void k_col_partial(const void *X, int dtype, int64_t ldx,
+// Block b sums rows [b*rows, (b+1)*rows) of every column, in row order, 16
+// rows' loads in flight (one load at a time was a round trip per row).
+template <typename TX>
+__global__ __launch_bounds__(256) void k_col_partial(const TX *__restrict__ X, int64_t ldx,
                                                      int64_t N, int n, int64_t rows,
-                                                     double *part, int32_t *nonfinite) {
+                                                     double *__restrict__ part, int32_t *nonfinite) {
     const int64_t r0 = (int64_t)blockIdx.x * rows;
     const int64_t r1 = r0 + rows < N ? r0 + rows : N;
     int bad = 0;
     for (int l = threadIdx.x; l < n; l += blockDim.x) {
         double acc = 0.0;
-        for (int64_t i = r0; i < r1; ++i) {
-            double v = load_x(X, dtype, i * ldx + l);
+        int64_t i = r0;
+        for (; i + 16 <= r1; i += 16) {
+            TX v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = X[(i + u) * ldx + l];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                if (!isfinite(v[u])) bad = 1;
+                acc += (double)v[u];
+            }
+        }
+        for (; i < r1; ++i) {
+            const double v = (double)X[i * ldx + l];
             if (!isfinite(v)) bad = 1;
             acc += v;
         }
@@ -40,25 +54,42 @@ __global__ __launch_bounds__(256) void k_col_mean(const double *part, int64_t nb
     int l = blockIdx.x * blockDim.x + threadIdx.x;
     if (l >= n) return;
     double acc = 0.0;
-    for (int64_t b = 0; b < nblk; ++b) acc += part[b * n + l];
+    int64_t b = 0;
+    for (; b + 8 <= nblk; b += 8) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = part[(b + u) * n + l];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += v[u];
+    }
+    for (; b < nblk; ++b) acc += part[b * n + l];
     mu[l] = acc / (double)N;
 }
 
-// One wavefront per row: ||x_i - mu||, folded into a max on the FP64 bits
-// (non-negative doubles order like their bit patterns).
-__global__ __launch_bounds__(256) void k_radius(const void *X, int dtype, int64_t ldx,
-                                                int64_t N, int n, const double *mu,
+// One wavefront per row (grid-stride): ||x_i - mu||, folded into a max on the
+// FP64 bits (non-negative doubles order like their bit patterns) -- per block
+// first, so that the one address sees an atomic per block and not per row.
+template <typename TX>
+__global__ __launch_bounds__(256) void k_radius(const TX *__restrict__ X, int64_t ldx,
+                                                int64_t N, int n, const double *__restrict__ mu,
                                                 unsigned long long *rbits) {
+    __shared__ unsigned long long s_max;
+    if (threadIdx.x == 0) s_max = 0ull;
+    __syncthreads();
     const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= N) return;
-    double acc = 0.0;
-    for (int l = lane; l < n; l += kWave) {
-        double t = load_x(X, dtype, row * ldx + l) - mu[l];
-        acc += t * t;
+    double rmax = 0.0;
+    for (int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); row < N; row += (int64_t)gridDim.x * 4) {
+        double acc = 0.0;
+        for (int l = lane; l < n; l += kWave) {
+            const double t = (double)X[row * ldx + l] - mu[l];
+            acc += t * t;
+        }
+        // (a NaN row stays out of the maximum; X is checked for it beforehand)
+        rmax = fmax(rmax, sqrt(wave_sum(acc)));
     }
-    acc = wave_sum(acc);
-    if (lane == 0) atomicMax(rbits, (unsigned long long)__double_as_longlong(sqrt(acc)));
+    if (lane == 0) atomicMax(&s_max, (unsigned long long)__double_as_longlong(rmax));
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMax(rbits, s_max);
 }
 
 // ---------------------------------------------------------------- plain form
@@ -125,52 +156,49 @@ template __global__ void k_build_secants<double>(const void *, int, int64_t, int
 // A kept pair is counted in bin m when ladder[m] < invd2 <= ladder[m+1]
 // (bin 63 takes everything above ladder[63]); the same FP32 comparison later
 // decides membership of the close list, so the counts are exact.
-__global__ __launch_bounds__(256) void k_build_invd2(const void *X, int dtype, int64_t ldx,
-                                                     int64_t N, int n, const int2 *tiles,
-                                                     int64_t ntiles, double min_len,
-                                                     float4 *invd2, const float *ladder,
-                                                     unsigned long long *hist,
-                                                     unsigned long long *kept,
-                                                     unsigned long long *dropped) {
+//
+// One block per tile (grid-stride), distances from tile_dist2; a thread's
+// 4 x 4 pairs are four consecutive float4 of the tile.  Kept and dropped
+// pairs are counted per thread and reduced once per block.
+template <typename TX>
+__global__ __launch_bounds__(256, 4) void k_build_invd2(const TX *__restrict__ X, int64_t ldx, int64_t N, int n,
+                                                        const int2 *__restrict__ tiles, int64_t ntiles,
+                                                        double min_len, float4 *__restrict__ invd2,
+                                                        const float *__restrict__ ladder, unsigned long long *hist,
+                                                        unsigned long long *kept, unsigned long long *dropped) {
+    __shared__ __align__(16) DistLds L;
     __shared__ unsigned long long s_hist[64];
     __shared__ unsigned long long s_kept, s_drop;
     __shared__ float s_ladder[64];
     if (threadIdx.x < 64) { s_hist[threadIdx.x] = 0; s_ladder[threadIdx.x] = ladder[threadIdx.x]; }
     if (threadIdx.x == 0) { s_kept = 0; s_drop = 0; }
-    __syncthreads();
-    const int c = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
+    unsigned long long nkept = 0, ndrop = 0;
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int2 b = tiles[t];
-        const int64_t j = (int64_t)b.y * kTile + c;
-        const bool jin = j < N;
-        for (int m = 0; m < 4; ++m) {
-            const int g = w + 4 * m;   // uniform within the wavefront
-            const int64_t i0 = (int64_t)b.x * kTile + 4 * g;
-            double d2[4] = {0.0, 0.0, 0.0, 0.0};
-            if (jin) {
-                for (int l = 0; l < n; ++l) {
-                    const double xj = load_x(X, dtype, j * ldx + l);
+        __syncthreads();   // the previous tile's rows and chunks have been read
+        if (threadIdx.x < 2 * kTile) {
+            const int64_t p = (int64_t)(threadIdx.x < kTile ? b.x : b.y) * kTile + (threadIdx.x & (kTile - 1));
+            L.row[threadIdx.x] = (int32_t)(p < N ? p : N - 1);
+        }
+        __syncthreads();
+        double d2[4][4];
+        tile_dist2(X, ldx, n, L, d2);
+        const int64_t i0 = (int64_t)b.x * kTile + 4 * ty, j0 = (int64_t)b.y * kTile + 4 * tx;
 #pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) {
-                        const int64_t i = i0 + rr < N ? i0 + rr : N - 1;
-                        const double t2 = load_x(X, dtype, i * ldx + l) - xj;
-                        d2[rr] += t2 * t2;
-                    }
-                }
-            }
+        for (int q = 0; q < 4; ++q) {
+            const int64_t j = j0 + q;
             float out[4];
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const int64_t i = i0 + rr;
+            for (int r = 0; r < 4; ++r) {
                 float v = kMaskDropped;
-                if (jin && i < j) {
-                    const double d = sqrt(d2[rr]);
-                    if (d == 0.0 || d < min_len) {
-                        atomicAdd(&s_drop, 1ull);
+                if (j < N && i0 + r < j) {
+                    // (the root only where a length is asked for: d = 0 is d^2 = 0)
+                    if (d2[r][q] == 0.0 || (min_len > 0.0 && sqrt(d2[r][q]) < min_len)) {
+                        ++ndrop;
                     } else {
-                        v = (float)(1.0 / d2[rr]);
-                        atomicAdd(&s_kept, 1ull);
+                        v = (float)(1.0 / d2[r][q]);
+                        ++nkept;
                         if (v > s_ladder[0]) {
                             int lo = 0;  // largest m with ladder[m] < v
                             for (int hi = 63; lo < hi;) {
@@ -181,11 +209,13 @@ __global__ __launch_bounds__(256) void k_build_invd2(const void *X, int dtype, i
                         }
                     }
                 }
-                out[rr] = v;
+                out[r] = v;
             }
-            invd2[t * (kTileElems / 4) + g * 64 + c] = make_float4(out[0], out[1], out[2], out[3]);
+            invd2[t * (kTileElems / 4) + ty * 64 + 4 * tx + q] = make_float4(out[0], out[1], out[2], out[3]);
         }
     }
+    atomicAdd(&s_kept, nkept);
+    atomicAdd(&s_drop, ndrop);
     __syncthreads();
     if (threadIdx.x < 64 && s_hist[threadIdx.x]) atomicAdd(&hist[threadIdx.x], s_hist[threadIdx.x]);
     if (threadIdx.x == 0) {
@@ -211,11 +241,14 @@ __global__ __launch_bounds__(256) void k_mark_close(float4 *invd2, const int2 *t
     unsigned mx = 0u;
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int2 b = tiles[t];
+        float4 v4[4];   // the tile's loads together, ahead of the rare stores
+#pragma unroll
+        for (int m = 0; m < 4; ++m) v4[m] = invd2[t * (kTileElems / 4) + (w + 4 * m) * 64 + c];
+#pragma unroll
         for (int m = 0; m < 4; ++m) {
             const int g = w + 4 * m;
             float4 *ptr = invd2 + t * (kTileElems / 4) + g * 64 + c;
-            float4 v = *ptr;
-            float vv[4] = {v.x, v.y, v.z, v.w};
+            float vv[4] = {v4[m].x, v4[m].y, v4[m].z, v4[m].w};
             bool hit = false;
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr) {

@@ -2162,9 +2162,21 @@ __global__ void k_short_len(const TX *__restrict__ X, int64_t ldx, int n,
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= nclose) return;
     const int2 pr = close[e];
+    const TX *xi = X + (int64_t)pr.x * ldx, *xj = X + (int64_t)pr.y * ldx;
     double d2 = 0.0;
-    for (int l = 0; l < n; ++l) {
-        const double dl = (double)X[(int64_t)pr.x * ldx + l] - (double)X[(int64_t)pr.y * ldx + l];
+    int l = 0;
+    for (; l + 16 <= n; l += 16) {   // 32 loads in flight, the sum in component order
+        TX a[16], b[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) { a[u] = xi[l + u]; b[u] = xj[l + u]; }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const double dl = (double)a[u] - (double)b[u];
+            d2 = __builtin_fma(dl, dl, d2);
+        }
+    }
+    for (; l < n; ++l) {
+        const double dl = (double)xi[l] - (double)xj[l];
         d2 = __builtin_fma(dl, dl, d2);
     }
     cd[e] = sqrt(d2);

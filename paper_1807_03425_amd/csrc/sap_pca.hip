@@ -17,6 +17,7 @@
 //   Jacobi) that reports the Ritz values and the residuals of the first k
 //   Ritz vectors.
 #include "sap_common.h"
+#include "sap_dist.h"
 
 namespace sap {
 
@@ -37,44 +38,38 @@ __device__ __forceinline__ void pca_block_sums(double *v, int nv, double *sb) {
     __syncthreads();
 }
 
-// 1/d^2 of every kept pair of tile t = (bi, bj), row-major 64 x 64 FP64;
-// zero for dropped pairs (duplicates, d < min_len), i >= j and padding.
+// 1/d^2 of every kept pair of tile t = (bi, bj), row-major 64 x 64 FP64
+// (distances from tile_dist2); zero for dropped pairs (duplicates, d <
+// min_len), i >= j and padding.
 template <typename TX>
-__global__ __launch_bounds__(256) void k_pca_w(const TX *__restrict__ X, int64_t ldx, int64_t N, int n,
-                                               const int2 *__restrict__ tiles, int64_t ntiles, double min_len,
-                                               double *__restrict__ W) {
-    const int c = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+__global__ __launch_bounds__(256, 4) void k_pca_w(const TX *__restrict__ X, int64_t ldx, int64_t N, int n,
+                                                  const int2 *__restrict__ tiles, int64_t ntiles, double min_len,
+                                                  double *__restrict__ W) {
+    __shared__ __align__(16) DistLds L;
+    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int2 b = tiles[t];
-        const int64_t j = (int64_t)b.y * kTile + c;
-        const bool jin = j < N;
-        const TX *xj = X + (jin ? j : N - 1) * ldx;
-        for (int m = 0; m < 4; ++m) {
-            const int g = w + 4 * m;
-            const int64_t i0 = (int64_t)b.x * kTile + 4 * g;
-            double d2[4] = {0.0, 0.0, 0.0, 0.0};
-            if (jin) {
-                for (int l = 0; l < n; ++l) {
-                    const double xv = (double)xj[l];
+        __syncthreads();   // the previous tile's rows and chunks have been read
+        if (threadIdx.x < 2 * kTile) {
+            const int64_t p = (int64_t)(threadIdx.x < kTile ? b.x : b.y) * kTile + (threadIdx.x & (kTile - 1));
+            L.row[threadIdx.x] = (int32_t)(p < N ? p : N - 1);
+        }
+        __syncthreads();
+        double d2[4][4];
+        tile_dist2(X, ldx, n, L, d2);
+        const int64_t i0 = (int64_t)b.x * kTile + 4 * ty, j0 = (int64_t)b.y * kTile + 4 * tx;
 #pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) {
-                        const int64_t i = i0 + rr < N ? i0 + rr : N - 1;
-                        const double t2 = (double)X[i * ldx + l] - xv;
-                        d2[rr] += t2 * t2;
-                    }
-                }
-            }
+        for (int r = 0; r < 4; ++r) {
+            double v[4];
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const int64_t i = i0 + rr;
-                double v = 0.0;
-                if (jin && i < j) {
-                    const double d = sqrt(d2[rr]);
-                    if (!(d == 0.0 || d < min_len)) v = 1.0 / d2[rr];
-                }
-                W[t * kTileElems + (4 * g + rr) * kTile + c] = v;
+            for (int q = 0; q < 4; ++q) {
+                const double s = d2[r][q];
+                const bool kept = j0 + q < N && i0 + r < j0 + q && s != 0.0 && !(min_len > 0.0 && sqrt(s) < min_len);
+                v[q] = kept ? 1.0 / s : 0.0;
             }
+            double2 *o = reinterpret_cast<double2 *>(W + t * kTileElems + (4 * ty + r) * kTile + 4 * tx);
+            o[0] = make_double2(v[0], v[1]);
+            o[1] = make_double2(v[2], v[3]);
         }
     }
 }
