@@ -85,3 +85,31 @@ def test_pca_sets_the_start_of_algorithm_1():
     assert res["certified"] == 1 and (res["i"], res["j"]) == (ref["i"], ref["j"])
     assert abs(res["min_norm"] - ref["r_min"]) <= 1e-12 * ref["r_min"] + 2 * np.sqrt(6) * 64 * 2.0 ** -53
     ctx.close()
+
+
+# ------------------------------------------------------------------ block shapes of the iteration
+
+def _graded(N, n, ratio, seed):
+    """Gaussian points whose components' scales fall geometrically: every
+    eigenvalue of S S^T apart from its neighbours."""
+    rng = np.random.default_rng(seed)
+    return rng.standard_normal((N, n)) * ratio ** np.arange(n)
+
+
+@pytest.mark.parametrize("N,n,k,form", [(150, 70, 10, "fused"), (130, 33, 16, "plain"), (64, 64, 8, "fused"),
+                                        (65, 65, 9, "plain"), (90, 17, 16, "fused"), (3, 1, 1, "plain")])
+def test_pca_two_column_tiles_and_ragged_rows(N, n, k, form):
+    """Blocks of 16 and of more than 16 vectors (b = max(k + 8, 2k)), row
+    lengths around the 64-component padding, b = n."""
+    _compare(_graded(N, n, 0.85, N + n), k, f"graded/N{N}/n{n}/k{k}", form=form)
+
+
+@pytest.mark.parametrize("rank,k", [(5, 3), (2, 2), (12, 10)])
+def test_pca_rank_below_the_block(rank, k):
+    """Points in a subspace of fewer dimensions than the block has vectors:
+    the smallest Ritz values are zero and the block's last columns carry
+    nothing (no filter interval; the orthonormalisation replaces them)."""
+    rng = np.random.default_rng(rank)
+    Q = sap_inputs.random_orthonormal(rng, 40, rank)
+    X = _graded(120, rank, 0.8, rank) @ Q.T
+    _compare(X, k, f"rank{rank}/k{k}")
