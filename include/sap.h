@@ -275,15 +275,17 @@ sap_status sap_profile_enable(sap_handle h, int32_t on);
 sap_status sap_profile_read(sap_handle h, sap_profile_t *out);
 
 /* ------------------------------------------------------------------------
- * Batched SAP: many independent small problems in one launch.
+ * Batched SAP: many independent small problems side by side.
  *
  * The paper runs Algorithm 1 on many small secant sets: once per target
  * dimension to read off the dimension of the data (Sec. 6.1, the sweep over
  * the projection dimension), on random subsamples of a set too large for its
  * secant matrix (Sec. 6.3, ten samples of 512 points), and with the length
  * threshold l of Sec. 7 to see through noise.  sap_batch_run runs B such
- * problems at once, each on its own workgroup, the whole run of iters
- * updates and iters+1 evaluations inside one kernel launch.
+ * problems at once, iters updates and iters+1 evaluations each: two launches
+ * per iteration for the whole batch, every problem with its own workgroups in
+ * both, or, where no set has more than 64 points, one launch with one
+ * workgroup per problem.
  *
  * A problem is Algorithm 1 on a point set S_s (rows of X listed by
  * set_points[set_offsets[s] .. set_offsets[s+1]), in that order; pairs and
@@ -306,9 +308,12 @@ typedef struct {
 
 typedef struct {
     double init_ms;     /* device time of the per-set precomputation          */
-    double run_ms;      /* device time of the run kernel (all problems)      */
+    double run_ms;      /* device time of the run (all problems, all iterations) */
     int64_t n_pairs;    /* kept pairs summed over the problems' sets          */
-    int64_t scratch_bytes; /* device scratch the call used                    */
+    int64_t scratch_bytes; /* device scratch of the batch's data (what
+                              sap_batch_run_noalloc limits); the run's block
+                              tables, block results and second copy of P come
+                              on top                                         */
 } sap_batch_stats;
 
 /* Run the batch.  Host arrays: set_offsets (n_sets + 1, increasing, sets of
@@ -338,12 +343,12 @@ sap_status sap_batch_run(const void *X, int32_t dtype, int64_t N, int32_t n, int
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * call as sap_batch_run -- same arguments, same kernels, same results --
- * except that its device scratch is a fixed array inside the library, 32 MiB
- * per GPU (each GPU the library runs on holds it until the process ends),
- * and that it creates no events (stats, if given, reports init_ms = run_ms =
- * -1).  It calls no hipMalloc or hipFree.  A batch that needs more scratch
- * than the array holds (stats->scratch_bytes of sap_batch_run tells) fails
- * with SAP_ERR_CAPACITY.  Every call on a GPU uses that GPU's one array and
+ * except that its device scratch is a fixed array inside the library (each GPU
+ * the library runs on holds its 65 MiB until the process ends), and that it
+ * creates no events (stats, if given, reports init_ms = run_ms = -1).  It
+ * calls no hipMalloc or hipFree.  A batch whose data need more than 32 MiB
+ * of scratch (stats->scratch_bytes of sap_batch_run tells) fails with
+ * SAP_ERR_CAPACITY.  Every call on a GPU uses that GPU's one array and
  * leaves its contents behind (each call rewrites what it reads, and clears
  * its counters with a kernel): calls that overlap on one GPU (concurrent
  * streams or threads) race, and must be serialised by the caller. */

@@ -304,7 +304,7 @@ class SapContext:
 
 def batch_run(X, sets, problems, P0s, iters: int, set_min_len=None, cand_cap: int = 0,
               stream=None, noalloc: bool = False) -> dict:
-    """Run independent SAP problems on point subsets of X in one launch
+    """Run independent SAP problems on point subsets of X in one call
     (sap_batch_run).
 
     X: N x n cuda tensor (float32/float64, unit stride along n).

@@ -1,30 +1,36 @@
-// Batched SAP (gfx950): many independent small problems, one workgroup each,
-// the whole run of Algorithm 1 (Sec. 4) inside one kernel launch.
+// Batched SAP (gfx950): many independent small problems, Algorithm 1 (Sec. 4)
+// on all of them side by side.
 //
 // The paper applies Algorithm 1 to many small secant sets: for every target
 // dimension of a sweep (Sec. 6.1), to random subsamples of a data set whose
 // full secant matrix does not fit (Sec. 6.3), and with the length threshold
-// of Sec. 7.  Each such problem here is one workgroup of 256 threads that
-// loops over the iterations with block barriers only:
-//   Y = (X_S - mean_S) P     FP64 on the matrix cores (v_mfma_f64_16x16x4f64),
-//                            the set's rows gathered through its index list;
-//   pass                     for every 16 x 64 quarter of the set's 64 x 64
-//                            tiles: ||y_i - y_j||^2 (FP64 differences) times
-//                            the stored FP32 1/d^2, rounded to an FP32 key;
-//                            the candidate window of the block's running
-//                            minimum, as in the single-problem pass;
-//   rescoring                every window pair in FP64 from X (the same
-//                            routine as the single-problem pass), lexicographic
-//                            (r, i, j) minimum, certificate, trace entry;
-//   update                   the FP64 argmax / modified Gram-Schmidt / shift
-//                            of the single-problem handle, in LDS.
+// of Sec. 7.  An iteration is two launches for the whole batch, each problem
+// with its own blocks in both (the kernel boundary is the barrier between
+// them, as in the single-problem run):
+//   pass       every 16 x 64 quarter of the set's 64 x 64 tiles: ||y_i - y_j||^2
+//              (FP64 differences) times the stored FP32 1/d^2, rounded to an
+//              FP32 key; the candidate window of the block's running minimum,
+//              as in the single-problem pass; then the block's window pairs in
+//              FP64 from X (the same routine), one result per block;
+//   selection  every block of a problem takes the lexicographic (r, i, j)
+//              minimum of the problem's results and applies the FP64 argmax /
+//              modified Gram-Schmidt / shift of the single-problem handle in
+//              LDS, then computes its rows of Y = (X_S - mean_S) P' in FP64 on
+//              the matrix cores (v_mfma_f64_16x16x4f64), the set's rows gathered
+//              through its index list; the problem's first block writes the
+//              trace entry and P'.
+// One workgroup per problem for the whole run -- no launches between the
+// phases, but 4 wavefronts on one compute unit -- took 52 us per iteration at
+// 30 problems of 256 points (n = 15) and 184 us at 60 of 512 points (n =
+// 200), against 21 and 43 us.
+//
 // Y stays FP64, so the coarse error is that of the FP64 product (no pair is
 // too short for it and there is no short-pair list); keys round to FP32.
 //
 // Scratch (device): per-set index lists, tile tables and 1/d^2 tiles (FP32,
 // the single-problem layout), per-set mean / radius / largest kept 1/d^2 /
-// pair counts, per-problem P (kp x n FP64, rows >= k zero) and Y
-// (Mpad x kp FP64).
+// pair counts, per-problem P twice (kp x n FP64, rows >= k zero; the selection
+// reads one and writes the other) and Y (Mpad x kp FP64), block results.
 #define SAP_KINST 1
 
 #include <algorithm>
@@ -35,6 +41,7 @@
 #include <limits>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include <hip/hip_ext.h>
@@ -70,6 +77,23 @@ struct BatchStat {
     uint64_t kept, dropped;
 };
 
+// What the blocks of the run need of a problem and its set, in one record:
+// npass blocks of the pass (their results at part_off), and selection blocks
+// of 64 gt rows of Y each.
+struct BatchDesc {
+    int64_t pt_off, tile_off, P_off, Y_off, part_off;
+    double alpha;
+    int32_t set, k, kp, rule;
+    int32_t M, nb, ntiles;
+    int32_t npass, gt, pad;
+};
+
+// a start's check: max |P^T P - I| and whether an entry is NaN or Inf
+struct BatchCheck {
+    double err;
+    int32_t nonfinite, pad;
+};
+
 struct BatchArgs {
     const void *X;
     int64_t ldx;
@@ -82,7 +106,12 @@ struct BatchArgs {
     double *mu;              // n_sets x n
     BatchStat *stat;         // n_sets
     const double *set_min_len;
-    double *Pbuf, *Ybuf;
+    const BatchDesc *desc;
+    BatchCheck *chk;
+    const int2 *pass_blk, *sel_blk;   // (problem, block of it) per block of the two launches
+    Partial *part;
+    double *Pbuf, *Pnext;    // the current P of every problem and the next
+    double *Ybuf;
     const double *P0;
     double *P_out;
     int iters, cap;
@@ -207,14 +236,48 @@ __global__ __launch_bounds__(256, 4) void k_batch_invd2(BatchArgs a, int64_t nti
     }
 }
 
-// P0 blocks (n x k row-major) -> per-problem P (kp x n, rows >= k zero)
+// P0 blocks (n x k row-major) -> per-problem P (kp x n, rows >= k zero), both buffers
 __global__ void k_batch_loadP(BatchArgs a) {
     const BatchProb pr = a.probs[blockIdx.y];
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     const int n = a.n;
     if (e >= pr.kp * n) return;
     const int q = e / n, l = e % n;
-    a.Pbuf[pr.P_off + e] = q < pr.k ? a.P0[pr.P0_off + (int64_t)l * pr.k + q] : 0.0;
+    const double v = q < pr.k ? a.P0[pr.P0_off + (int64_t)l * pr.k + q] : 0.0;
+    a.Pbuf[pr.P_off + e] = v;
+    a.Pnext[pr.P_off + e] = v;   // (its rows >= k stay zero)
+}
+
+// The starts: one block per problem, entry (x, y) of P0^T P0 per thread, the
+// rows in order and 16 at a time in flight (on the host, after a copy of every
+// start, this took as long as ten iterations of 60 problems at n = 200).
+__global__ __launch_bounds__(256) void k_batch_checkP(BatchArgs a) {
+    __shared__ unsigned long long s_err;
+    __shared__ int s_bad;
+    const BatchDesc d = a.desc[blockIdx.x];
+    const double *P = a.P0 + a.probs[blockIdx.x].P0_off;
+    const int n = a.n, k = d.k;
+    if (threadIdx.x == 0) { s_err = 0ull; s_bad = 0; }
+    __syncthreads();
+    int bad = 0;
+    for (int e = threadIdx.x; e < n * k; e += 256) bad |= isfinite(P[e]) ? 0 : 1;
+    if (bad) atomicOr(&s_bad, 1);
+    if ((int)threadIdx.x < k * k) {
+        const int x = threadIdx.x / k, y = threadIdx.x % k;
+        double acc = 0.0;
+        int l = 0;
+        for (; l + 16 <= n; l += 16) {
+            double u[16], v[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) { u[q] = P[(l + q) * k + x]; v[q] = P[(l + q) * k + y]; }
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc += u[q] * v[q];
+        }
+        for (; l < n; ++l) acc += P[l * k + x] * P[l * k + y];
+        atomicMax(&s_err, (unsigned long long)__double_as_longlong(fabs(acc - (x == y ? 1.0 : 0.0))));
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) a.chk[blockIdx.x] = BatchCheck{__longlong_as_double((long long)s_err), s_bad, 0};
 }
 
 // per-problem P (kp x n) -> P_out blocks (n x k row-major)
@@ -229,20 +292,19 @@ __global__ void k_batch_storeP(BatchArgs a) {
 // ---------------------------------------------------------------- the run
 
 // 16 rows of Y = (X_S - mean) P in FP64 (rows row0 .. row0 + 15 of the set;
-// rows >= M are zero), KP columns (P rows >= k are zero).  The MFMA tiling of
-// gemm_block, the rows gathered through the set's index list.
-template <typename TX, int KP>
+// rows >= M are zero), kp columns (zero past the k rows of P, k x n).  The
+// MFMA tiling of gemm_block, the rows gathered through the set's index list.
+template <typename TX>
 __device__ __forceinline__ void batch_gemm16(const TX *__restrict__ X, int64_t ldx, const int32_t *__restrict__ idx,
-                                             int M, int n, const double *__restrict__ mu,
-                                             const double *__restrict__ P, double *__restrict__ Y, int row0,
-                                             bool vx, bool vp) {
+                                             int M, int n, int k, int kp, const double *__restrict__ mu,
+                                             const double *P, double *__restrict__ Y, int row0, bool vx, bool vp) {
     const int lane = threadIdx.x & 63;
     const int m = lane & 15, kk = lane >> 4;
     const int row = row0 + m;
     const bool rin = row < M;
-    const double rmask = rin ? 1.0 : 0.0, pmask = m < KP ? 1.0 : 0.0;
+    const double rmask = rin ? 1.0 : 0.0, pmask = m < k ? 1.0 : 0.0;
     const TX *xr = X + (int64_t)idx[rin ? row : M - 1] * ldx;
-    const double *pc = P + (int64_t)(m < KP ? m : KP - 1) * n;
+    const double *pc = P + (m < k ? m : k - 1) * n;
     double4_t acc = {0.0, 0.0, 0.0, 0.0};
     int l0 = 0;
     for (; l0 + 64 <= n; l0 += 64) {
@@ -260,57 +322,50 @@ __device__ __forceinline__ void batch_gemm16(const TX *__restrict__ X, int64_t l
         double x = 0.0, p = 0.0;
         if (l < n) {
             if (rin) x = (double)xr[l] - mu[l];
-            if (m < KP) p = pc[l];
+            if (m < k) p = pc[l];
         }
         acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x, p, acc, 0, 0, 0);
     }
-    if (m < KP) {
+    if (m < kp) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int r = row0 + kk + 4 * v;
-            Y[(int64_t)r * KP + m] = r < M ? acc[v] : 0.0;
+            Y[(int64_t)r * kp + m] = r < M ? acc[v] : 0.0;
         }
     }
 }
 
 // The FP64 update of Algorithm 1 for the exact k (K_LO <= k <= K_HI), with
-// P (k x n) staged in LDS and written back to P (global, rows 0..k-1): the
-// single-problem handle's routines -- one wavefront with the vectors in
-// registers when n <= 64 and k <= 8, the whole block over LDS otherwise.
-// Every thread of the block calls it.
+// P (k x n) staged in LDS, updated there and written to Pn (k x n, may be
+// null): the single-problem handle's routines -- one wavefront with the
+// vectors in registers when n <= 64 and k <= 8, the whole block over LDS
+// otherwise.  Every thread of the block calls it.
 template <typename TX, int K_LO, int K_HI>
-__device__ __forceinline__ void batch_update(const TX *X, int64_t ldx, int n, int k, double *P, double alpha, int rule,
+__device__ __forceinline__ void batch_update(const TX *X, int64_t ldx, int n, int k, double *Pn, double alpha, int rule,
                                              int64_t gi, int64_t gj, double *sm) {
     if constexpr (K_LO <= K_HI) {
         if (k == K_LO) {
             if (K_LO <= 8 && n <= kWave) {
                 if (threadIdx.x < kWave)
-                    apply_update_reg<K_LO, 1, TX>(X, ldx, n, sm, P, nullptr, 0, alpha, rule, nullptr, gi, gj, false);
+                    apply_update_reg<K_LO, 1, TX>(X, ldx, n, sm, Pn, nullptr, 0, alpha, rule, nullptr, gi, gj, true);
             } else {
-                apply_update<K_LO, TX>(X, ldx, n, P, nullptr, 0, alpha, rule, nullptr, gi, gj, sm);
+                apply_update<K_LO, TX>(X, ldx, n, Pn, nullptr, 0, alpha, rule, nullptr, gi, gj, sm);
             }
         } else {
-            batch_update<TX, K_LO + 1, K_HI>(X, ldx, n, k, P, alpha, rule, gi, gj, sm);
+            batch_update<TX, K_LO + 1, K_HI>(X, ldx, n, k, Pn, alpha, rule, gi, gj, sm);
         }
     }
 }
 
-template <int KP> struct KRange;
-template <> struct KRange<2> { static constexpr int lo = 1, hi = 2; };
-template <> struct KRange<4> { static constexpr int lo = 3, hi = 4; };
-template <> struct KRange<8> { static constexpr int lo = 5, hi = 8; };
-template <> struct KRange<12> { static constexpr int lo = 9, hi = 12; };
-template <> struct KRange<16> { static constexpr int lo = 13, hi = 16; };
-
-// LDS of a problem's pass, declared once in the kernel (the five KP variants
-// share it): every wavefront's staged y_i rows and candidate list, the
-// block's running minimum and its result.
+// LDS of a pass block, declared once in the kernel (the five KP variants
+// share it): every wavefront's staged y_i rows and candidate list, the list
+// lengths and the block's running minimum.
 struct BatchLds {
     double y[kPairBlock / kWave][16 * kMaxK];
     int2 cij[kPairBlock / kWave][kCandCap];
     uint32_t ckey[kPairBlock / kWave][kCandCap];
+    int cn[kPairBlock / kWave];
     uint32_t run;
-    Partial fin;
 };
 
 // Tile (bi, bj), bi <= bj, of index t in the row-major order of a set's
@@ -326,195 +381,254 @@ __device__ __forceinline__ int2 tile_of_index(int64_t t, int nb) {
     return make_int2((int)bi, (int)(bi + (t - start(bi))));
 }
 
-// One problem, the whole run.  Every thread of the block calls it.
-template <int KP, typename TX>
-__device__ void batch_problem(const BatchArgs &a, int b, double *sm, BatchLds &L) {
-    constexpr int NY = (16 * KP + kWave - 1) / kWave;   // doubles of an item's y_i rows per lane
-    auto &s_y = L.y;
-    auto &s_cij = L.cij;
-    auto &s_ckey = L.ckey;
-    uint32_t &s_run = L.run;
-    Partial &s_fin = L.fin;
-    const int lane = threadIdx.x & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const BatchProb pr = a.probs[b];
-    const BatchSet st = a.sets[pr.set];
-    const BatchStat bs = a.stat[pr.set];
-    const int n = a.n, k = pr.k, M = st.M;
-    const TX *X = static_cast<const TX *>(a.X);
-    const int32_t *idx = a.pts + st.pt_off;
-    double *P = a.Pbuf + pr.P_off;
-    double *Y = a.Ybuf + pr.Y_off;
-    const double *mu = a.mu + (int64_t)pr.set * n;
-    const float4 *wt = a.w + st.tile_off * (kTileElems / 4);
-    const bool vp = (n & 1) == 0;
-    // coarse error bound |r~ - r| <= e_abs + e_rel r: the FP64 product's
-    // error on y (norm over the k columns) and the FP32 rounding of 1/d^2
-    // and of the key
+// Coarse error bound of a problem's keys, |r~ - r| <= e_abs + e_rel r -- the
+// FP64 product's error on y (norm over the k columns) and the FP32 rounding
+// of 1/d^2 and of the key -- and item_window's coefficients.
+struct BatchBound {
+    double e_abs, e_rel;
+    float wa, wb;
+};
+__device__ __forceinline__ BatchBound batch_bound(const BatchStat &bs, int n, int k, int kp) {
+    BatchBound o;
     const double R = __longlong_as_double((long long)bs.radius_bits);
     const double delta = R * (double)(n + 2) * sqrt((double)k) * 1.1102230246251565e-16 * 4.0;
     const double wmax = (double)__uint_as_float(bs.wmax_bits);
-    const double e_abs = bs.wmax_bits ? 2.0 * delta * sqrt(wmax * (1.0 + 2.384185791015625e-07)) : 0.0;
-    const double e_rel = 2.0 * 5.9604644775390625e-08 + (KP + 4) * 1.1102230246251565e-16;
-    float wa = (float)((1.0 + e_rel) / (1.0 - e_rel));
-    wa = __uint_as_float(__float_as_uint(wa) + 1u);
-    float wbb = (float)(2.0 * e_abs / (1.0 - e_rel));
-    wbb = __uint_as_float(__float_as_uint(wbb) + 1u);
-    const int64_t nitem = (int64_t)st.ntiles * 4;        // quarter tiles
-    const int iters = a.iters;
-    const int64_t tr0 = (int64_t)b * (iters + 1);
-    for (int it = 0; it <= iters; ++it) {
-        // Y = (X_S - mean) P
-        for (int slab = wv; slab < st.nb * 4; slab += kPairBlock / kWave)
-            batch_gemm16<TX, KP>(X, a.ldx, idx, M, n, mu, P, Y, slab * 16, a.vx, vp);
-        if (threadIdx.x == 0) s_run = kKeyNone;
-        __syncthreads();
-        // pass: wavefront wv takes quarter tiles wv, wv + 4, ...; the loads of
-        // the next item are issued before the current item's arithmetic, and
-        // every load of an item is independent (tile coordinates computed,
-        // not loaded)
-        WaveBest wb{__builtin_huge_val(), __builtin_huge_val(), 0x7fffffff, 0x7fffffff, 0, 0, 0};
-        CandList cl{s_cij[wv], s_ckey[wv], 0, a.cap, 0, kKeyNone};
-        uint32_t kmin = kKeyNone;
-        double *yl = s_y[wv];
-        struct ItemLoads {
-            float4 w4[4];
-            double yr[NY];
-            double yj[KP];
-            int32_t row0, col;
-        };
-        auto fetch = [&](int64_t hh, ItemLoads &L) __attribute__((always_inline)) {
-            const int64_t t = hh >> 2;
-            const int q = (int)(hh & 3);
-            const int2 tc = tile_of_index(t, st.nb);
-            const float4 *tp = wt + t * (kTileElems / 4) + q * 256 + lane;
+    o.e_abs = bs.wmax_bits ? 2.0 * delta * sqrt(wmax * (1.0 + 2.384185791015625e-07)) : 0.0;
+    o.e_rel = 2.0 * 5.9604644775390625e-08 + (kp + 4) * 1.1102230246251565e-16;
+    o.wa = __uint_as_float(__float_as_uint((float)((1.0 + o.e_rel) / (1.0 - o.e_rel))) + 1u);
+    o.wb = __uint_as_float(__float_as_uint((float)(2.0 * o.e_abs / (1.0 - o.e_rel))) + 1u);
+    return o;
+}
+
+// Pass block lb of a problem: wavefront w takes the quarter tiles 4 lb + w, +
+// 4 npass, ... (every load of an item is independent: tile coordinates are
+// computed, not loaded), then the block's wavefronts share the rescoring of
+// its window pairs.  Every thread of the block calls it and gets the result.
+template <int KP, typename TX>
+__device__ __forceinline__ Partial batch_pass_block(const BatchArgs &a, const BatchDesc &d, int lb, BatchLds &L,
+                                                    Partial *out) {
+    constexpr int NY = (16 * KP + kWave - 1) / kWave;   // doubles of an item's y_i rows per lane
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const BatchBound bd = batch_bound(a.stat[d.set], a.n, d.k, KP);
+    const TX *X = static_cast<const TX *>(a.X);
+    const int32_t *idx = a.pts + d.pt_off;
+    const double *P = a.Pbuf + d.P_off;
+    const double *Y = a.Ybuf + d.Y_off;
+    const float4 *wt = a.w + d.tile_off * (kTileElems / 4);
+    const int64_t nitem = (int64_t)d.ntiles * 4;         // quarter tiles
+    if (threadIdx.x == 0) L.run = kKeyNone;
+    __syncthreads();
+    WaveBest wb{__builtin_huge_val(), __builtin_huge_val(), 0x7fffffff, 0x7fffffff, 0, 0, 0};
+    CandList cl{L.cij[wv], L.ckey[wv], 0, a.cap, 0, kKeyNone};
+    uint32_t kmin = kKeyNone;
+    double *yl = L.y[wv];
+    for (int64_t h = (int64_t)lb * (kPairBlock / kWave) + wv; h < nitem; h += (int64_t)d.npass * (kPairBlock / kWave)) {
+        const int64_t t = h >> 2;
+        const int q = (int)(h & 3);
+        const int2 tc = tile_of_index(t, d.nb);
+        const float4 *tp = wt + t * (kTileElems / 4) + q * 256 + lane;
+        float4 w4[4];
 #pragma unroll
-            for (int g = 0; g < 4; ++g) L.w4[g] = tp[g * 64];
-            L.row0 = tc.x * kTile + 16 * q;
-            L.col = tc.y * kTile + lane;
-            const double *ysrc = Y + (int64_t)L.row0 * KP;
+        for (int g = 0; g < 4; ++g) w4[g] = tp[g * 64];
+        const int32_t row0 = tc.x * kTile + 16 * q, col = tc.y * kTile + lane;
+        const double *ysrc = Y + (int64_t)row0 * KP;
+        double yr[NY], yj[KP];
 #pragma unroll
-            for (int u = 0; u < NY; ++u) {
-                const int f = lane + u * kWave;
-                L.yr[u] = ysrc[f < 16 * KP ? f : 0];
-            }
-#pragma unroll
-            for (int c = 0; c < KP; ++c) L.yj[c] = Y[(int64_t)L.col * KP + c];
-        };
-        ItemLoads cur, nxt;
-        int64_t h = wv;
-        if (h < nitem) fetch(h, cur);
-        nxt = cur;
-        for (; h < nitem; h += kPairBlock / kWave) {
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int u = 0; u < NY; ++u) {
-                const int f = lane + u * kWave;
-                if (f < 16 * KP) yl[f] = cur.yr[u];
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (h + kPairBlock / kWave < nitem) fetch(h + kPairBlock / kWave, nxt);
-            uint32_t key[16];
-            uint32_t lmin = kKeyNone;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const double *yi = yl + e * KP;
-                double acc = 0.0;
-#pragma unroll
-                for (int c = 0; c < KP; ++c) {
-                    const double d = yi[c] - cur.yj[c];
-                    acc = __builtin_fma(d, d, acc);
-                }
-                const float4 &wg = cur.w4[e >> 2];
-                const float wv4 = (e & 3) == 0 ? wg.x : (e & 3) == 1 ? wg.y : (e & 3) == 2 ? wg.z : wg.w;
-                key[e] = __float_as_uint((float)(acc * (double)wv4));
-                lmin = min(lmin, key[e]);
-            }
-            const uint32_t m = wave_min_u32_fast(lmin);
-            kmin = min(kmin, m);
-            const uint32_t T2 = item_window(block_run_min(&s_run, m), wa, wbb);
-            const int32_t row0 = cur.row0, col = cur.col;
-            if (m <= T2)
-                emit_cands(cl, key, lmin, T2,
-                           [=](int e, int32_t &i, int32_t &j) __attribute__((always_inline)) {
-                               i = row0 + e;
-                               j = col;
-                           },
-                           wb);
-            __builtin_amdgcn_wave_barrier();
-            cur = nxt;
+        for (int u = 0; u < NY; ++u) {
+            const int f = lane + u * kWave;
+            yr[u] = ysrc[f < 16 * KP ? f : 0];
         }
-        // rescore the window pairs in FP64 from X
-        {
-            const uint32_t run = __builtin_amdgcn_readfirstlane(*(const volatile uint32_t *)&s_run);
-            if (run < 0x7f800000u) {
-                const uint32_t T2b = item_window(run, wa, wbb);
-                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int c = 0; c < KP; ++c) yj[c] = Y[(int64_t)col * KP + c];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < NY; ++u) {
+            const int f = lane + u * kWave;
+            if (f < 16 * KP) yl[f] = yr[u];
+        }
+        __builtin_amdgcn_wave_barrier();
+        uint32_t key[16];
+        uint32_t lmin = kKeyNone;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const double *yi = yl + e * KP;
+            double acc = 0.0;
+#pragma unroll
+            for (int c = 0; c < KP; ++c) {
+                const double t2 = yi[c] - yj[c];
+                acc = __builtin_fma(t2, t2, acc);
+            }
+            const float4 &wg = w4[e >> 2];
+            const float wv4 = (e & 3) == 0 ? wg.x : (e & 3) == 1 ? wg.y : (e & 3) == 2 ? wg.z : wg.w;
+            key[e] = __float_as_uint((float)(acc * (double)wv4));
+            lmin = min(lmin, key[e]);
+        }
+        const uint32_t m = wave_min_u32_fast(lmin);
+        kmin = min(kmin, m);
+        const uint32_t T2 = item_window(block_run_min(&L.run, m), bd.wa, bd.wb);
+        if (m <= T2)
+            emit_cands(cl, key, lmin, T2,
+                       [=](int e, int32_t &i, int32_t &j) __attribute__((always_inline)) {
+                           i = row0 + e;
+                           j = col;
+                       },
+                       wb);
+        __builtin_amdgcn_wave_barrier();
+    }
+    // the window pairs of the block's minimum in FP64 from X, every fourth of
+    // the four lists per wavefront (as finish_pass_block)
+    if (lane == 0) L.cn[wv] = cl.n;
+    __syncthreads();
+    const uint32_t run = __builtin_amdgcn_readfirstlane(*(const volatile uint32_t *)&L.run);
+    if (run < 0x7f800000u) {
+        const uint32_t T2b = item_window(run, bd.wa, bd.wb);
+        const int n0 = L.cn[0], n1 = L.cn[1], n2 = L.cn[2], tot = n0 + n1 + n2 + L.cn[3];
+        int g = wv;
+        uint32_t kv;
+        int2 ij;
 #pragma unroll 1
-                for (int c = 0; c < cl.n; ++c) {
-                    const uint32_t kv = cl.key[c];
-                    if (kv > T2b) continue;
-                    const int2 ij = cl.ij[c];
-                    const double r = exact_r_wave<KP, TX>(X, a.ldx, n, P, idx[ij.x], idx[ij.y]);
-                    ++wb.nwin;
-                    wb.nviol += bound_broken(r, (double)__uint_as_float(kv), e_abs, e_rel);
-                    if (lex_less(r, ij.x, ij.y, wb.r, wb.i, wb.j)) {
-                        wb.r2 = wb.r;
-                        wb.r = r; wb.i = ij.x; wb.j = ij.y;
-                    } else {
-                        wb.r2 = fmin(wb.r2, r);
-                    }
-                }
-            }
-            wb.nviol += cl.lost;
-            block_reduce_partial(wb.r, wb.i, wb.j, wb.r2, lane == 0 ? wb.nwin : 0, lane == 0 ? wb.nunits : 0,
-                                 lane == 0 ? wb.nviol : 0, kmin, cl.limit, &s_fin, true);
+        while (next_window_entry(g, tot, n0, n1, n2, L.cij, L.ckey, T2b, kv, ij)) {
+            g += kPairBlock / kWave;
+            const double r = exact_r_wave<KP, TX>(X, a.ldx, a.n, P, idx[ij.x], idx[ij.y]);
+            ++wb.nwin;
+            wb.nviol += bound_broken(r, (double)__uint_as_float(kv), bd.e_abs, bd.e_rel);
+            lex_pick2(wb.r, wb.i, wb.j, wb.r2, r, ij.x, ij.y, __builtin_huge_val());
         }
-        const Partial f = s_fin;
-        const bool found = f.r < __builtin_huge_val();
-        if (threadIdx.x == 0) {
-            const uint32_t wkey = f.kmin < 0x7f800000u ? item_window(f.kmin, wa, wbb) : 0u;
-            const int cert = (found && f.n_viol == 0 && f.limit >= wkey) ? 1 : 0;
-            a.tr_min[tr0 + it] = f.r;
-            if (a.tr_ij) {
-                a.tr_ij[2 * (tr0 + it)] = found ? f.i : -1;
-                a.tr_ij[2 * (tr0 + it) + 1] = found ? f.j : -1;
-            }
-            if (a.tr_cert) a.tr_cert[tr0 + it] = cert;
-        }
-        if (it == iters || !found) {
-            if (it < iters) {
-                // no kept pair: the remaining entries repeat this one
-                if (threadIdx.x == 0)
-                    for (int r = it + 1; r <= iters; ++r) {
-                        a.tr_min[tr0 + r] = f.r;
-                        if (a.tr_ij) { a.tr_ij[2 * (tr0 + r)] = -1; a.tr_ij[2 * (tr0 + r) + 1] = -1; }
-                        if (a.tr_cert) a.tr_cert[tr0 + r] = 0;
-                    }
-            }
-            break;
-        }
-        // the update, in LDS
-        stage_P(P, k * n, sm);
-        __syncthreads();
-        batch_update<TX, KRange<KP>::lo, KRange<KP>::hi>(X, a.ldx, n, k, P, pr.alpha, pr.rule, idx[f.i], idx[f.j],
-                                                         sm);
-        __syncthreads();
+    }
+    wb.nviol += cl.lost;
+    return block_reduce_partial(wb.r, wb.i, wb.j, wb.r2, wb.nwin, wb.nunits, wb.nviol, kmin, cl.limit, out, false,
+                                true);
+}
+
+template <typename TX>
+__global__ __launch_bounds__(kPairBlock, 3) void k_batch_pass(BatchArgs a) {
+    __shared__ BatchLds L;
+    const int2 bl = a.pass_blk[blockIdx.x];
+    const BatchDesc d = a.desc[bl.x];
+    Partial *out = a.part + d.part_off + bl.y;
+    switch (d.kp) {
+        case 2: batch_pass_block<2, TX>(a, d, bl.y, L, out); break;
+        case 4: batch_pass_block<4, TX>(a, d, bl.y, L, out); break;
+        case 8: batch_pass_block<8, TX>(a, d, bl.y, L, out); break;
+        case 12: batch_pass_block<12, TX>(a, d, bl.y, L, out); break;
+        default: batch_pass_block<16, TX>(a, d, bl.y, L, out); break;
     }
 }
 
-// One workgroup per problem.  Dynamic LDS: the update's (k + 2) n doubles.
+// Trace entry `it` of problem b from its evaluation f.
+__device__ __forceinline__ void batch_record(const BatchArgs &a, const BatchDesc &d, int b, int it, const Partial &f) {
+    const BatchBound bd = batch_bound(a.stat[d.set], a.n, d.k, d.kp);
+    const bool found = f.r < __builtin_huge_val();
+    const uint32_t wkey = f.kmin < 0x7f800000u ? item_window(f.kmin, bd.wa, bd.wb) : 0u;
+    const int cert = (found && f.n_viol == 0 && f.limit >= wkey) ? 1 : 0;
+    const int64_t tr = (int64_t)b * (a.iters + 1) + it;
+    a.tr_min[tr] = f.r;
+    if (a.tr_ij) {
+        a.tr_ij[2 * tr] = found ? f.i : -1;
+        a.tr_ij[2 * tr + 1] = found ? f.j : -1;
+    }
+    if (a.tr_cert) a.tr_cert[tr] = cert;
+}
+
+// Rows [16 s0, 16 s1) of a problem's Y from P in LDS, a slab of 16 per wavefront step.
+template <typename TX>
+__device__ __forceinline__ void batch_Y(const BatchArgs &a, const BatchDesc &d, const double *sm, int s0, int s1) {
+    const double *mu = a.mu + (int64_t)d.set * a.n;
+    for (int s = s0 + (int)(threadIdx.x >> 6); s < s1; s += kPairBlock / kWave)
+        batch_gemm16<TX>(static_cast<const TX *>(a.X), a.ldx, a.pts + d.pt_off, d.M, a.n, d.k, d.kp, mu, sm,
+                         a.Ybuf + d.Y_off, s * 16, a.vx, (a.n & 1) == 0);
+}
+
+// Selection, trace entry `it` and (step) update of every problem, then its
+// next Y; with sel = 0 only Y, of the starting P.  Block (b, lb) computes the
+// rows 64 gt lb .. of problem b's Y; every block of a problem takes the same
+// selection and update (identical inputs and arithmetic), block lb = 0 writes
+// the trace and P' to the other buffer.  Dynamic LDS: P and the update's two
+// vectors, (k + 2) n doubles.
+template <typename TX>
+__global__ __launch_bounds__(kPairBlock) void k_batch_select(BatchArgs a, int it, int sel, int step) {
+    extern __shared__ __align__(16) double sm_batch[];
+    const int2 bl = a.sel_blk[blockIdx.x];
+    const bool lead = bl.y == 0;
+    if (sel && !step && !lead) return;   // the last evaluation: the record alone
+    const BatchDesc d = a.desc[bl.x];
+    const int n = a.n, k = d.k;
+    double *Pn = a.Pnext + d.P_off;
+    if (!sel || step) stage_P(a.Pbuf + d.P_off, k * n, sm_batch);
+    if (sel) {
+        const Partial *part = a.part + d.part_off;
+        double best = __builtin_huge_val(), second = __builtin_huge_val();
+        int32_t bi = 0x7fffffff, bj = 0x7fffffff, nviol = 0;
+        uint32_t kmin = kKeyNone, limit = kKeyNone;
+        for (int e = threadIdx.x; e < d.npass; e += kPairBlock) {
+            const Partial p = part[e];
+            lex_pick2(best, bi, bj, second, p.r, p.i, p.j, p.r2);
+            nviol += p.n_viol;
+            kmin = min(kmin, p.kmin);
+            limit = min(limit, p.limit);
+        }
+        const Partial f = block_reduce_partial(best, bi, bj, second, 0, 0, nviol, kmin, limit, nullptr, false);
+        if (lead && threadIdx.x == 0) batch_record(a, d, bl.x, it, f);
+        if (!step) return;
+        // (the barrier inside block_reduce_partial has ordered P's staging)
+        if (f.r < __builtin_huge_val()) {
+            const int32_t *idx = a.pts + d.pt_off;
+            batch_update<TX, 1, kMaxK>(static_cast<const TX *>(a.X), a.ldx, n, k, lead ? Pn : nullptr, d.alpha, d.rule,
+                                       idx[f.i], idx[f.j], sm_batch);
+        } else if (lead) {
+            for (int e = threadIdx.x; e < k * n; e += kPairBlock) Pn[e] = sm_batch[e];   // no kept pair: P unchanged
+        }
+    }
+    __syncthreads();
+    batch_Y<TX>(a, d, sm_batch, 4 * d.gt * bl.y, min(4 * d.gt * (bl.y + 1), 4 * d.nb));
+}
+
+template <int KP> struct KRange;
+template <> struct KRange<2> { static constexpr int lo = 1, hi = 2; };
+template <> struct KRange<4> { static constexpr int lo = 3, hi = 4; };
+template <> struct KRange<8> { static constexpr int lo = 5, hi = 8; };
+template <> struct KRange<12> { static constexpr int lo = 9, hi = 12; };
+template <> struct KRange<16> { static constexpr int lo = 13, hi = 16; };
+
+// A whole run of problem b in one block (P stays in LDS and, for the
+// rescoring, in its first buffer).
+template <int KP, typename TX>
+__device__ __forceinline__ void batch_run_block(BatchArgs &a, const BatchDesc &d, int b, double *sm, BatchLds &L) {
+    const int32_t *idx = a.pts + d.pt_off;
+    double *P = a.Pbuf + d.P_off;
+    stage_P(P, d.k * a.n, sm);
+    for (int it = 0; it <= a.iters; ++it) {
+        __syncthreads();   // P' (and, before that, the reads of Y) are done
+        batch_Y<TX>(a, d, sm, 0, 4 * d.nb);
+        __syncthreads();
+        const Partial f = batch_pass_block<KP, TX>(a, d, 0, L, nullptr);
+        if (threadIdx.x == 0) batch_record(a, d, b, it, f);
+        // (a set without a kept pair keeps P: the same evaluation each time)
+        if (it < a.iters && f.r < __builtin_huge_val())
+            batch_update<TX, KRange<KP>::lo, KRange<KP>::hi>(static_cast<const TX *>(a.X), a.ldx, a.n, d.k, P, d.alpha,
+                                                             d.rule, idx[f.i], idx[f.j], sm);
+    }
+}
+
+// Batches of sets of at most 64 points (one tile, an item per wavefront): one
+// block per problem runs all its iterations.  There the two launches of an
+// iteration cost more than the block barriers between its phases: a call on 30
+// problems of 40 points, n = 15, 40 iterations, takes 0.84 ms here and 1.18 ms
+// in two launches; from 65 points (three tiles) on the launches are as fast
+// (three problems of 65 points, one block each 0.84 ms, launches 0.82) and
+// with more points much faster.
 template <typename TX>
 __global__ __launch_bounds__(kPairBlock) void k_batch_run(BatchArgs a) {
     extern __shared__ __align__(16) double sm_batch[];
     __shared__ BatchLds L;
-    const int b = blockIdx.x;
-    switch (a.probs[b].kp) {
-        case 2: batch_problem<2, TX>(a, b, sm_batch, L); break;
-        case 4: batch_problem<4, TX>(a, b, sm_batch, L); break;
-        case 8: batch_problem<8, TX>(a, b, sm_batch, L); break;
-        case 12: batch_problem<12, TX>(a, b, sm_batch, L); break;
-        default: batch_problem<16, TX>(a, b, sm_batch, L); break;
+    const BatchDesc d = a.desc[blockIdx.x];
+    switch (d.kp) {
+        case 2: batch_run_block<2, TX>(a, d, blockIdx.x, sm_batch, L); break;
+        case 4: batch_run_block<4, TX>(a, d, blockIdx.x, sm_batch, L); break;
+        case 8: batch_run_block<8, TX>(a, d, blockIdx.x, sm_batch, L); break;
+        case 12: batch_run_block<12, TX>(a, d, blockIdx.x, sm_batch, L); break;
+        default: batch_run_block<16, TX>(a, d, blockIdx.x, sm_batch, L); break;
     }
 }
 
@@ -559,11 +673,51 @@ struct BatchPlan {
     std::vector<int4> tiles;
     std::vector<int32_t> pts;
     std::vector<double> minlen;
+    std::vector<BatchDesc> desc;
+    bool one_block = false;  // every set has at most 64 points: k_batch_run
+    std::vector<int2> pass_blk, sel_blk;
     int64_t ntiles_all = 0, P_total = 0, Y_total = 0, P0_total = 0;
     size_t lds = 0;
-    // scratch offsets (bytes)
-    size_t o_pts, o_sets, o_probs, o_tiles, o_w, o_mu, o_stat, o_minlen, o_P, o_Y, total;
+    // scratch offsets (bytes); the tables the host fills come first, one copy
+    size_t o_pts, o_sets, o_probs, o_tiles, o_minlen, o_desc, o_pblk, o_sblk, o_w, o_mu, o_stat, o_chk, o_P, o_Y,
+        o_part, o_P2;
+    std::vector<char> tables;   // the tables' host copy
+    size_t total = 0;        // bytes of the scratch
+    size_t counted = 0;      // without the block tables, the block results and the second P: what
+                             // scratch_bytes reports and the fixed scratch's limit counts
 };
+
+// Blocks of the two launches.  Pass: one round of resident blocks (three per
+// compute unit) dealt to the problems by their quarter tiles, at most one per
+// four of them; where every problem gets one block there are as many as
+// problems.  Selection: every block repeats its problem's selection and
+// update, so there are about as many as compute units (its registers allow one
+// block on each), each with whole 64-row groups of Y.
+void plan_blocks(BatchPlan &pl, int cus) {
+    const int64_t slots = 3 * (int64_t)cus;
+    int64_t items = 0, groups = 0, parts = 0;
+    for (const BatchProb &p : pl.probs) {
+        items += 4ll * pl.sets[p.set].ntiles;
+        groups += pl.sets[p.set].nb;
+    }
+    const int32_t gt = (int32_t)std::max<int64_t>(1, (groups + cus - 1) / cus);
+    pl.one_block = true;
+    pl.desc.resize(pl.probs.size());
+    for (size_t b = 0; b < pl.probs.size(); ++b) {
+        const BatchProb &p = pl.probs[b];
+        const BatchSet &st = pl.sets[p.set];
+        BatchDesc &g = pl.desc[b];
+        g = BatchDesc{st.pt_off, st.tile_off, p.P_off, p.Y_off, 0, p.alpha, p.set, p.k, p.kp, p.rule,
+                      st.M, st.nb, st.ntiles, 0, 0, 0};
+        pl.one_block = pl.one_block && st.nb == 1;
+        g.npass = (int32_t)std::max<int64_t>(1, std::min<int64_t>(st.ntiles, slots * 4 * st.ntiles / items));
+        g.gt = gt;
+        g.part_off = parts;
+        parts += g.npass;
+        for (int q = 0; q < g.npass; ++q) pl.pass_blk.push_back(make_int2((int)b, q));
+        for (int q = 0; q * gt < st.nb; ++q) pl.sel_blk.push_back(make_int2((int)b, q));
+    }
+}
 
 sap_status plan_batch(const void *X, int32_t dtype, int64_t N, int32_t n, int64_t ldx, int32_t n_sets,
                       const int64_t *set_offsets, const int32_t *set_points, const double *set_min_len,
@@ -632,40 +786,55 @@ sap_status plan_batch(const void *X, int32_t dtype, int64_t N, int32_t n, int64_
         lds = std::max(lds, sizeof(double) * (size_t)n * (q.k + 2));
     }
     pl.lds = lds;
-    size_t off = 0;
+    int cus = 0, dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) {
+        (void)hipGetLastError();
+        cus = 256;
+    }
+    plan_blocks(pl, cus);
+    size_t off = 0, extra = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off = (size_t)align_up((int64_t)(off + bytes), 256); return o; };
+    auto more = [&](size_t bytes) { const size_t o = take(bytes); extra += off - o; return o; };
     pl.o_pts = take(sizeof(int32_t) * npts);
     pl.o_sets = take(sizeof(BatchSet) * n_sets);
     pl.o_probs = take(sizeof(BatchProb) * n_problems);
     pl.o_tiles = take(sizeof(int4) * pl.ntiles_all);
+    pl.o_minlen = take(sizeof(double) * n_sets);
+    pl.o_desc = more(sizeof(BatchDesc) * n_problems);
+    pl.o_pblk = more(sizeof(int2) * pl.pass_blk.size());
+    pl.o_sblk = more(sizeof(int2) * pl.sel_blk.size());
+    pl.tables.resize(off);
     pl.o_w = take(sizeof(float) * (size_t)pl.ntiles_all * kTileElems);
     pl.o_mu = take(sizeof(double) * (size_t)n_sets * n);
     pl.o_stat = take(sizeof(BatchStat) * n_sets);
-    pl.o_minlen = take(sizeof(double) * n_sets);
+    pl.o_chk = more(sizeof(BatchCheck) * n_problems);
     pl.o_P = take(sizeof(double) * (size_t)pl.P_total);
     pl.o_Y = take(sizeof(double) * (size_t)pl.Y_total);
+    pl.o_part = more(sizeof(Partial) * pl.pass_blk.size());
+    pl.o_P2 = more(sizeof(double) * (size_t)pl.P_total);
     pl.total = off;
+    pl.counted = off - extra;
+    // (the copy's source: it lives as long as the plan, past the call's last wait)
+    auto put = [&](size_t at, const void *p, size_t bytes) { if (bytes) std::memcpy(pl.tables.data() + at, p, bytes); };
+    put(pl.o_pts, pl.pts.data(), sizeof(int32_t) * pl.pts.size());
+    put(pl.o_sets, pl.sets.data(), sizeof(BatchSet) * pl.sets.size());
+    put(pl.o_probs, pl.probs.data(), sizeof(BatchProb) * pl.probs.size());
+    put(pl.o_tiles, pl.tiles.data(), sizeof(int4) * pl.tiles.size());
+    put(pl.o_minlen, pl.minlen.data(), sizeof(double) * pl.minlen.size());
+    put(pl.o_desc, pl.desc.data(), sizeof(BatchDesc) * pl.desc.size());
+    put(pl.o_pblk, pl.pass_blk.data(), sizeof(int2) * pl.pass_blk.size());
+    put(pl.o_sblk, pl.sel_blk.data(), sizeof(int2) * pl.sel_blk.size());
     (void)iters;
     return SAP_OK;
 }
 
-sap_status check_P0(const BatchPlan &pl, int n, const double *P0, hipStream_t stream) {
-    std::vector<double> h((size_t)pl.P0_total);
-    B_HIP(hipMemcpyAsync(h.data(), P0, sizeof(double) * h.size(), hipMemcpyDeviceToHost, stream));
-    B_HIP(hipStreamSynchronize(stream));
-    for (size_t b = 0; b < pl.probs.size(); ++b) {
-        const BatchProb &p = pl.probs[b];
-        const double *P = h.data() + p.P0_off;
-        double e = 0.0;
-        for (int l = 0; l < n * p.k; ++l)
-            if (!std::isfinite(P[l])) return bfail(SAP_ERR_NONFINITE, "problem %zu: P0 holds NaN or Inf", b);
-        for (int x = 0; x < p.k; ++x)
-            for (int y = 0; y < p.k; ++y) {
-                double acc = 0.0;
-                for (int l = 0; l < n; ++l) acc += P[(size_t)l * p.k + x] * P[(size_t)l * p.k + y];
-                e = std::max(e, std::fabs(acc - (x == y ? 1.0 : 0.0)));
-            }
-        if (e > 1e-6) return bfail(SAP_ERR_NOT_ORTHONORMAL, "problem %zu: max |P0^T P0 - I| = %.3g > 1e-6", b, e);
+// The starts' checks: finite and orthonormal.
+sap_status check_P0(const BatchCheck *chk, int n_problems) {
+    for (int b = 0; b < n_problems; ++b) {
+        if (chk[b].nonfinite) return bfail(SAP_ERR_NONFINITE, "problem %d: P0 holds NaN or Inf", b);
+        if (chk[b].err > 1e-6)
+            return bfail(SAP_ERR_NOT_ORTHONORMAL, "problem %d: max |P0^T P0 - I| = %.3g > 1e-6", b, chk[b].err);
     }
     return SAP_OK;
 }
@@ -690,7 +859,13 @@ sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dty
     a.mu = reinterpret_cast<double *>(base + pl.o_mu);
     a.stat = reinterpret_cast<BatchStat *>(base + pl.o_stat);
     a.set_min_len = reinterpret_cast<const double *>(base + pl.o_minlen);
+    a.desc = reinterpret_cast<const BatchDesc *>(base + pl.o_desc);
+    a.chk = reinterpret_cast<BatchCheck *>(base + pl.o_chk);
+    a.pass_blk = reinterpret_cast<const int2 *>(base + pl.o_pblk);
+    a.sel_blk = reinterpret_cast<const int2 *>(base + pl.o_sblk);
+    a.part = reinterpret_cast<Partial *>(base + pl.o_part);
     a.Pbuf = reinterpret_cast<double *>(base + pl.o_P);
+    a.Pnext = reinterpret_cast<double *>(base + pl.o_P2);
     a.Ybuf = reinterpret_cast<double *>(base + pl.o_Y);
     a.P0 = P0;
     a.P_out = P_out;
@@ -699,13 +874,7 @@ sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dty
     a.tr_min = min_trace;
     a.tr_ij = ij_trace;
     a.tr_cert = cert_trace;
-    B_HIP(hipMemcpyAsync(base + pl.o_pts, pl.pts.data(), sizeof(int32_t) * pl.pts.size(), hipMemcpyHostToDevice, stream));
-    B_HIP(hipMemcpyAsync(base + pl.o_sets, pl.sets.data(), sizeof(BatchSet) * pl.sets.size(), hipMemcpyHostToDevice, stream));
-    B_HIP(hipMemcpyAsync(base + pl.o_probs, pl.probs.data(), sizeof(BatchProb) * pl.probs.size(), hipMemcpyHostToDevice,
-                         stream));
-    B_HIP(hipMemcpyAsync(base + pl.o_tiles, pl.tiles.data(), sizeof(int4) * pl.tiles.size(), hipMemcpyHostToDevice, stream));
-    B_HIP(hipMemcpyAsync(base + pl.o_minlen, pl.minlen.data(), sizeof(double) * pl.minlen.size(), hipMemcpyHostToDevice,
-                         stream));
+    B_HIP(hipMemcpyAsync(base, pl.tables.data(), pl.tables.size(), hipMemcpyHostToDevice, stream));
     hipEvent_t e0 = nullptr, e1 = nullptr, e2 = nullptr;
     if (timed) {
         B_HIP(hipEventCreate(&e0));
@@ -740,11 +909,19 @@ sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dty
     hipLaunchKernelGGL(k_batch_loadP, dim3((unsigned)((kpmax * n + 255) / 256), (unsigned)n_problems), dim3(256), 0,
                        stream, a);
     if ((st = launched("k_batch_loadP")) != SAP_OK) return st;
-    // inputs checked before the run: finite rows, kept pairs
+    hipLaunchKernelGGL(k_batch_checkP, dim3((unsigned)n_problems), dim3(256), 0, stream, a);
+    if ((st = launched("k_batch_checkP")) != SAP_OK) return st;
+    // inputs checked before the run: orthonormal starts, finite rows, kept pairs
     {
-        std::vector<BatchStat> hs(n_sets);
-        B_HIP(hipMemcpyAsync(hs.data(), a.stat, sizeof(BatchStat) * n_sets, hipMemcpyDeviceToHost, stream));
+        // (the sets' statistics and the starts' checks lie one behind the other)
+        std::vector<char> back(pl.o_chk + sizeof(BatchCheck) * n_problems - pl.o_stat);
+        B_HIP(hipMemcpyAsync(back.data(), base + pl.o_stat, back.size(), hipMemcpyDeviceToHost, stream));
         B_HIP(hipStreamSynchronize(stream));
+        std::vector<BatchStat> hs(n_sets);
+        std::vector<BatchCheck> hc(n_problems);
+        std::memcpy(hs.data(), back.data(), sizeof(BatchStat) * n_sets);
+        std::memcpy(hc.data(), back.data() + (pl.o_chk - pl.o_stat), sizeof(BatchCheck) * n_problems);
+        if ((st = check_P0(hc.data(), n_problems)) != SAP_OK) return st;
         int64_t kept = 0;
         for (int s = 0; s < n_sets; ++s) {
             if (hs[s].nonfinite) return bfail(SAP_ERR_NONFINITE, "set %d: X holds NaN or Inf", s);
@@ -753,14 +930,38 @@ sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dty
         if (stats) stats->n_pairs = kept;
     }
     if (timed) B_HIP(hipEventRecord(e1, stream));
-    const void *fn = dtype == SAP_F64 ? reinterpret_cast<const void *>(&k_batch_run<double>)
-                                      : reinterpret_cast<const void *>(&k_batch_run<float>);
+    const bool f64 = dtype == SAP_F64, one = pl.one_block;
+    const void *fn = one ? (f64 ? reinterpret_cast<const void *>(&k_batch_run<double>)
+                                : reinterpret_cast<const void *>(&k_batch_run<float>))
+                         : (f64 ? reinterpret_cast<const void *>(&k_batch_select<double>)
+                                : reinterpret_cast<const void *>(&k_batch_select<float>));
     B_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds));
-    if (dtype == SAP_F64)
-        hipLaunchKernelGGL(k_batch_run<double>, dim3((unsigned)n_problems), dim3(kPairBlock), (uint32_t)pl.lds, stream, a);
-    else
-        hipLaunchKernelGGL(k_batch_run<float>, dim3((unsigned)n_problems), dim3(kPairBlock), (uint32_t)pl.lds, stream, a);
-    if ((st = launched("k_batch_run")) != SAP_OK) return st;
+    // Y of the starts, then per iteration the pass and the selection (with the
+    // update and the next Y); the last evaluation is only recorded
+    const dim3 gp((unsigned)pl.pass_blk.size()), gs((unsigned)pl.sel_blk.size());
+    auto select = [&](int it, int sel, int step) {
+        if (f64)
+            hipLaunchKernelGGL(k_batch_select<double>, gs, dim3(kPairBlock), (uint32_t)pl.lds, stream, a, it, sel, step);
+        else
+            hipLaunchKernelGGL(k_batch_select<float>, gs, dim3(kPairBlock), (uint32_t)pl.lds, stream, a, it, sel, step);
+        return launched("k_batch_select");
+    };
+    if (one) {
+        if (f64)
+            hipLaunchKernelGGL(k_batch_run<double>, dim3((unsigned)n_problems), dim3(kPairBlock), (uint32_t)pl.lds, stream, a);
+        else
+            hipLaunchKernelGGL(k_batch_run<float>, dim3((unsigned)n_problems), dim3(kPairBlock), (uint32_t)pl.lds, stream, a);
+        if ((st = launched("k_batch_run")) != SAP_OK) return st;
+    } else {
+        if ((st = select(0, 0, 0)) != SAP_OK) return st;
+        for (int it = 0; it <= iters; ++it) {
+            if (f64) hipLaunchKernelGGL(k_batch_pass<double>, gp, dim3(kPairBlock), 0, stream, a);
+            else hipLaunchKernelGGL(k_batch_pass<float>, gp, dim3(kPairBlock), 0, stream, a);
+            if ((st = launched("k_batch_pass")) != SAP_OK) return st;
+            if ((st = select(it, 1, it < iters ? 1 : 0)) != SAP_OK) return st;
+            if (it < iters) std::swap(a.Pbuf, a.Pnext);
+        }
+    }
     if (timed) B_HIP(hipEventRecord(e2, stream));
     hipLaunchKernelGGL(k_batch_storeP, dim3((unsigned)((kpmax * n + 255) / 256), (unsigned)n_problems), dim3(256), 0,
                        stream, a);
@@ -769,7 +970,7 @@ sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dty
     if (stats) {
         stats->init_ms = -1.0;
         stats->run_ms = -1.0;
-        stats->scratch_bytes = (int64_t)pl.total;
+        stats->scratch_bytes = (int64_t)pl.counted;
     }
     if (timed) {
         float t1 = 0.0f, t2 = 0.0f;
@@ -797,7 +998,6 @@ extern "C" sap_status sap_batch_run(const void *X, int32_t dtype, int64_t N, int
                                P0, iters, cand_cap, P_out, min_trace, pl);
     if (st != SAP_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if ((st = check_P0(pl, n, P0, s)) != SAP_OK) return st;
     void *base = nullptr;
     hipError_t e = hipMalloc(&base, pl.total);
     if (e != hipSuccess) {
@@ -819,8 +1019,13 @@ extern "C" sap_status sap_batch_run(const void *X, int32_t dtype, int64_t N, int
 // looked up once per device (hipGetSymbolAddress, with that device current)
 // and that address is what the kernels are given.  Each device holds its own
 // copy until the process ends; every call on one device shares it.
+// The limit counts a batch's data (BatchPlan::counted); the array has room
+// beside it for the second P (no larger than the first, which is counted) and
+// the block tables and results (under 200 bytes per problem, whose counted Y
+// is 1 KB at least, and under 100 per block of one round).
 constexpr size_t kStaticScratchBytes = size_t(32) << 20;
-static __device__ __align__(256) char scratch[kStaticScratchBytes];
+constexpr size_t kStaticArrayBytes = (size_t(65) << 20);
+static __device__ __align__(256) char scratch[kStaticArrayBytes];
 
 namespace {
 std::mutex g_scratch_mu;
@@ -855,13 +1060,12 @@ extern "C" sap_status sap_batch_run_noalloc(const void *X, int32_t dtype, int64_
     sap_status st = plan_batch(X, dtype, N, n, ldx, n_sets, set_offsets, set_points, set_min_len, n_problems, problems,
                                P0, iters, cand_cap, P_out, min_trace, pl);
     if (st != SAP_OK) return st;
-    if (pl.total > kStaticScratchBytes)
+    if (pl.counted > kStaticScratchBytes || pl.total > kStaticArrayBytes)
         return bfail(SAP_ERR_CAPACITY, "sap_batch_run_noalloc: the batch needs %zu bytes of scratch, above the fixed %zu",
-                     pl.total, kStaticScratchBytes);
+                     pl.counted, kStaticScratchBytes);
     hipStream_t s = static_cast<hipStream_t>(stream);
     char *base = nullptr;
     if ((st = static_scratch(&base)) != SAP_OK) return st;
-    if ((st = check_P0(pl, n, P0, s)) != SAP_OK) return st;
     st = run_batch(pl, base, X, dtype, ldx, n, n_sets, n_problems, P0, iters, cand_cap, P_out, min_trace, ij_trace,
                    cert_trace, s, stats, false);
     (void)hipStreamSynchronize(s);

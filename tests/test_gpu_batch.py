@@ -220,3 +220,50 @@ def test_errors_reported():
     # still usable afterwards
     out = batch_run(Xt, sets, [dict(set=0, k=2)], P0s[:1], 1)
     assert out["certified"][0, 0].item() == 1
+
+
+# ------------------------------------------------------------------ how a batch is spread
+
+def _equal(a, b, m):
+    """The first m problems of two batches: traces and projections, bit for bit."""
+    for key in ("min", "ij", "certified"):
+        assert torch.equal(a[key][:m], b[key][:m]), key
+    for b_i in range(m):
+        assert torch.equal(a["P"][b_i], b["P"][b_i]), b_i
+
+
+def test_sets_of_one_tile_in_one_launch_equal_the_two_launch_run():
+    """Sets of at most 64 points run in one launch, unless another set of the
+    batch is larger: the same bits either way (all five padded widths, the
+    register and the block-wide update, a set without a kept pair)."""
+    rng = np.random.default_rng(12)
+    X = rng.standard_normal((300, 70))
+    sets = [np.arange(0, 64, dtype=np.int32), np.arange(64, 101, dtype=np.int32), np.array([200, 7], dtype=np.int32),
+            np.arange(110, 120, dtype=np.int32), np.arange(130, 195, dtype=np.int32)]
+    problems = [dict(set=s, k=k) for s in range(4) for k in (1, 2, 4, 7, 11, 14)]
+    P0s = sap_inputs.sweep_starts(70, [q["k"] for q in problems] + [3], seed=13)
+    ml = [0.0, 0.0, 0.0, 100.0, 0.0]
+    Xt = torch.from_numpy(X).to(DEV)
+    one = batch_run(Xt, sets[:4], problems, P0s[:-1], 9, set_min_len=ml[:4])
+    two = batch_run(Xt, sets, problems + [dict(set=4, k=3)], P0s, 9, set_min_len=ml)
+    _equal(one, two, len(problems))
+    _lockstep(X, sets[:3], [q for q in problems if q["set"] < 3],
+              [P for P, q in zip(P0s, problems) if q["set"] < 3], 2, tag="one tile")
+
+
+def test_one_large_problem_and_many_small_ones():
+    """Many blocks for one problem (1000 points), and more problems than
+    blocks of a round (several row groups per selection block, one pass block
+    each): the same bits as run by themselves, and the oracle's in lockstep."""
+    w = sap_inputs.make("hyper", N=3000)
+    Xt = torch.from_numpy(w.X).to(DEV)
+    sets = sap_inputs.subsample_sets(w.N, 1, 1000, seed=3)
+    P0s = sap_inputs.sweep_starts(w.n, [6], seed=4)
+    _lockstep(w.X, sets, [dict(set=0, k=6)], P0s, 3, tag="large")
+    many = sap_inputs.subsample_sets(w.N, 300, 130, seed=5)
+    problems = [dict(set=s, k=3 + s % 3) for s in range(300)]
+    starts = sap_inputs.sweep_starts(w.n, [q["k"] for q in problems], seed=6)
+    out = batch_run(Xt, many, problems, starts, 4)
+    alone = batch_run(Xt, many[:7], problems[:7], starts[:7], 4)
+    _equal(out, alone, 7)
+    assert np.all(out["certified"].cpu().numpy() == 1)
