@@ -292,8 +292,8 @@ __global__ void k_batch_storeP(BatchArgs a) {
 // ---------------------------------------------------------------- the run
 
 // 16 rows of Y = (X_S - mean) P in FP64 (rows row0 .. row0 + 15 of the set;
-// rows >= M are zero), kp columns (zero past the k rows of P, k x n).  The
-// MFMA tiling of gemm_block, the rows gathered through the set's index list.
+// rows >= M are zero), kp columns (zero past the k rows of P, k x n): gemm16
+// on rows gathered through the set's index list.
 template <typename TX>
 __device__ __forceinline__ void batch_gemm16(const TX *__restrict__ X, int64_t ldx, const int32_t *__restrict__ idx,
                                              int M, int n, int k, int kp, const double *__restrict__ mu,
@@ -302,30 +302,10 @@ __device__ __forceinline__ void batch_gemm16(const TX *__restrict__ X, int64_t l
     const int m = lane & 15, kk = lane >> 4;
     const int row = row0 + m;
     const bool rin = row < M;
-    const double rmask = rin ? 1.0 : 0.0, pmask = m < k ? 1.0 : 0.0;
-    const TX *xr = X + (int64_t)idx[rin ? row : M - 1] * ldx;
-    const double *pc = P + (m < k ? m : k - 1) * n;
-    double4_t acc = {0.0, 0.0, 0.0, 0.0};
-    int l0 = 0;
-    for (; l0 + 64 <= n; l0 += 64) {
-        double xa[16], ma[16], pb[16];
-        const int lb = l0 + 16 * kk;
-        load16(xr + lb, vx, xa);
-        load16(mu + lb, true, ma);
-        load16(pc + lb, vp, pb);
-#pragma unroll
-        for (int s = 0; s < 16; ++s)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64((xa[s] - ma[s]) * rmask, pb[s] * pmask, acc, 0, 0, 0);
-    }
-    for (; l0 < n; l0 += 4) {
-        const int l = l0 + kk;
-        double x = 0.0, p = 0.0;
-        if (l < n) {
-            if (rin) x = (double)xr[l] - mu[l];
-            if (m < k) p = pc[l];
-        }
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x, p, acc, 0, 0, 0);
-    }
+    const TX nx[16] = {};
+    const double none[16] = {};
+    const double4_t acc = gemm16<TX>(X + (int64_t)idx[rin ? row : M - 1] * ldx, rin, mu, P + (m < k ? m : k - 1) * n,
+                                     m < k, n, vx, vp, nx, none, false);
     if (m < kp) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {

@@ -330,39 +330,55 @@ __device__ __forceinline__ void gemm_block_lowp(const TX *__restrict__ X, int64_
     }
 }
 
-// x0, m0 (used when use_x0): the first chunk's X values and means, loaded
-// earlier by k_selprep.  gemm: SAP_GEMM_F64 (below), or SAP_GEMM_F32 /
-// SAP_GEMM_BF16 (gemm_block_lowp).  With the FP64 GEMM, Y64 (if not null)
-// receives the same products unrounded (the short-pair bounds use them).
-// A block covers 64 tpw rows; this call computes the wavefront's 16 rows of
-// its tile-th group of 64.
-template <typename TX>
-__device__ __forceinline__ void gemm_block(const TX *__restrict__ X, int64_t ldx, int64_t N, int n, int k,
-                           const double *__restrict__ mu, const double *__restrict__ P64t,
-                           float *__restrict__ Y, double *__restrict__ Y64, int kp, int64_t Npad, bool vx,
-                           bool vp, const TX (&x0)[16], const double (&m0)[16], bool use_x0, int gemm,
-                           int tpw = 1, int tile = 0) {
-    const int lane = threadIdx.x & 63;
-    const int64_t row0 = (((int64_t)blockIdx.x * tpw + tile) * 4 + (threadIdx.x >> 6)) * 16;
-    if (row0 >= Npad) return;
-    if (gemm != SAP_GEMM_F64) {
-        gemm_block_lowp<TX>(X, ldx, N, n, k, mu, P64t, Y, kp, row0, vx, vp, x0, m0, use_x0, gemm);
-        return;
+// One step of a GEMM's tail (n not a multiple of 64): S MFMAs whose k-slot kk
+// carries component l0 + 4 s + kk.  The loads are unconditional (clamped) and
+// all issued before any is used: guarded one by one they were a round trip
+// per MFMA, up to 16 in a row.
+template <typename TX, int S>
+struct GemmTail {
+    TX x[S];
+    double mu[S], p[S];
+    __device__ __forceinline__ void load(const TX *__restrict__ xr, const double *__restrict__ mup, const double *pc,
+                                         int n, int l0) {
+        const int kk = (threadIdx.x & 63) >> 4;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int lc = min(l0 + 4 * s + kk, n - 1);
+            x[s] = xr[lc];
+            mu[s] = mup[lc];
+            p[s] = pc[lc];
+        }
     }
-    const int m = lane & 15, kk = lane >> 4;
-    const int64_t row = row0 + m;
-    const bool rin = row < N;
-    // out-of-range rows and columns read a valid element and are zeroed by a
-    // mask afterwards, so that every load of a chunk is unconditional and the
-    // 48 of them are in flight together (X is finite: checked at init)
-    const double rmask = rin ? 1.0 : 0.0, pmask = m < k ? 1.0 : 0.0;
-    const TX *xr = X + (rin ? row : N - 1) * ldx;
-    const double *pc = P64t + (int64_t)(m < k ? m : k - 1) * n;
+    __device__ __forceinline__ double4_t apply(double4_t acc, int n, int l0, bool rin, bool cin) const {
+        const int kk = (threadIdx.x & 63) >> 4;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            if (l0 + 4 * s < n) {   // wavefront-uniform
+                const bool in = l0 + 4 * s + kk < n;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in && rin ? (double)x[s] - mu[s] : 0.0,
+                                                           in && cin ? p[s] : 0.0, acc, 0, 0, 0);
+            }
+        }
+        return acc;
+    }
+};
+
+// The 16 x 16 tile (x_r - mu) P in FP64 for the lane's row xr (rin: it
+// exists; any valid row otherwise) and column pc (cin: likewise), n
+// components; x0, m0 (used when use_x0): the first chunk, loaded earlier.
+// Software-pipelined over 64-component chunks: the next chunk's operands are
+// in flight during this chunk's 16 MFMAs.  Out-of-range rows and columns read
+// a valid element and are zeroed by a mask afterwards, so that every load of
+// a chunk is unconditional (X is finite: checked at init).
+template <typename TX>
+__device__ __forceinline__ double4_t gemm16(const TX *__restrict__ xr, bool rin, const double *__restrict__ mu,
+                                            const double *pc, bool cin, int n, bool vx, bool vp, const TX (&x0)[16],
+                                            const double (&m0)[16], bool use_x0) {
+    const int kk = (threadIdx.x & 63) >> 4;
+    const double rmask = rin ? 1.0 : 0.0, pmask = cin ? 1.0 : 0.0;
     double4_t acc = {0.0, 0.0, 0.0, 0.0};
     int l0 = 0;
     if (n >= 64) {
-        // software-pipelined over 64-component chunks: the next chunk's
-        // operands are in flight during this chunk's 16 MFMAs
         double xa[16], ma[16], pb[16];
         if (use_x0) {
 #pragma unroll
@@ -399,15 +415,43 @@ __device__ __forceinline__ void gemm_block(const TX *__restrict__ X, int64_t ldx
             }
         }
     }
-    for (; l0 < n; l0 += 4) {
-        const int l = l0 + kk;
-        double a = 0.0, b = 0.0;
-        if (l < n) {
-            if (rin) a = (double)xr[l] - mu[l];
-            if (m < k) b = pc[l];
-        }
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+    for (; n - l0 > 16; l0 += 32) {
+        GemmTail<TX, 8> t;
+        t.load(xr, mu, pc, n, l0);
+        acc = t.apply(acc, n, l0, rin, cin);
     }
+    if (l0 < n) {
+        GemmTail<TX, 4> t;
+        t.load(xr, mu, pc, n, l0);
+        acc = t.apply(acc, n, l0, rin, cin);
+    }
+    return acc;
+}
+
+// x0, m0 (used when use_x0): the first chunk's X values and means, loaded
+// earlier by k_selprep.  gemm: SAP_GEMM_F64 (below), or SAP_GEMM_F32 /
+// SAP_GEMM_BF16 (gemm_block_lowp).  With the FP64 GEMM, Y64 (if not null)
+// receives the same products unrounded (the short-pair bounds use them).
+// A block covers 64 tpw rows; this call computes the wavefront's 16 rows of
+// its tile-th group of 64.
+template <typename TX>
+__device__ __forceinline__ void gemm_block(const TX *__restrict__ X, int64_t ldx, int64_t N, int n, int k,
+                           const double *__restrict__ mu, const double *__restrict__ P64t,
+                           float *__restrict__ Y, double *__restrict__ Y64, int kp, int64_t Npad, bool vx,
+                           bool vp, const TX (&x0)[16], const double (&m0)[16], bool use_x0, int gemm,
+                           int tpw = 1, int tile = 0) {
+    const int lane = threadIdx.x & 63;
+    const int64_t row0 = (((int64_t)blockIdx.x * tpw + tile) * 4 + (threadIdx.x >> 6)) * 16;
+    if (row0 >= Npad) return;
+    if (gemm != SAP_GEMM_F64) {
+        gemm_block_lowp<TX>(X, ldx, N, n, k, mu, P64t, Y, kp, row0, vx, vp, x0, m0, use_x0, gemm);
+        return;
+    }
+    const int m = lane & 15, kk = lane >> 4;
+    const int64_t row = row0 + m;
+    const bool rin = row < N;
+    const double4_t acc = gemm16<TX>(X + (rin ? row : N - 1) * ldx, rin, mu, P64t + (int64_t)(m < k ? m : k - 1) * n,
+                                     m < k, n, vx, vp, x0, m0, use_x0);
     if (m < kp) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -1374,11 +1418,24 @@ __device__ __forceinline__ double4_t short_c16(const TX *__restrict__ X, int64_t
         for (int q = 0; q < 16; ++q)
             acc = __builtin_amdgcn_mfma_f64_16x16x4f64((xa[q] - xb[q]) * rmask, pb[q] * pmask, acc, 0, 0, 0);
     }
-    for (; l0 < n; l0 += 4) {
-        const int l = l0 + kk;
-        const double x = (l < n && rin) ? (double)xi[l] - (double)xj[l] : 0.0;
-        const double p = (l < n && m < K) ? pc[l] : 0.0;
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x, p, acc, 0, 0, 0);
+    for (; l0 < n; l0 += 32) {   // eight steps' loads together (clamped), as in GemmTail
+        TX xa[8], xb[8];
+        double pb[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const int lc = min(l0 + 4 * s + kk, n - 1);
+            xa[s] = xi[lc];
+            xb[s] = xj[lc];
+            pb[s] = pc[lc];
+        }
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            if (l0 + 4 * s < n) {   // wavefront-uniform
+                const bool in = l0 + 4 * s + kk < n;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in && rin ? (double)xa[s] - (double)xb[s] : 0.0,
+                                                           in && m < K ? pb[s] : 0.0, acc, 0, 0, 0);
+            }
+        }
     }
     return acc;
 }
