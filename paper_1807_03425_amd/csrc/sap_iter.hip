@@ -566,10 +566,35 @@ __device__ __forceinline__ void gemm_block_deep(const TX *__restrict__ X, int64_
 
 // ------------------------------------------------------------------ coarse scores
 
+// Wavefront-uniform read-only data: scalar loads into scalar registers.
+typedef const __attribute__((address_space(4))) float *UniformF;
+typedef int int2_bits __attribute__((ext_vector_type(2)));
+typedef const __attribute__((address_space(4))) int2_bits *UniformI2;
+
+// R consecutive rows of Y (KP floats each) from a wavefront-uniform address,
+// whole rows (one or two scalar loads each).
+template <int KP, int R>
+__device__ __forceinline__ void load_rows(UniformF p, float (&y)[R][KP]) {
+    constexpr int W = KP == 12 ? 4 : KP;
+    typedef float vec __attribute__((ext_vector_type(W)));
+    typedef float vec8 __attribute__((ext_vector_type(8)));
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if constexpr (KP == 12) {
+            const vec8 v = *reinterpret_cast<const __attribute__((address_space(4))) vec8 *>(p + r * KP);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) y[r][c] = v[c];
+        }
+        const vec v = *reinterpret_cast<const __attribute__((address_space(4))) vec *>(p + r * KP + KP - W);
+#pragma unroll
+        for (int c = 0; c < W; ++c) y[r][KP - W + c] = v[c];
+    }
+}
+
 // Coarse squared ratio of one pair: ||y_i - y_j||^2 * (1/d^2).  y_i is
 // wavefront-uniform, y_j lives in the lane's registers.
 template <int K>
-__device__ __forceinline__ float pair_r2(const float *__restrict__ yi, const float (&yj)[K],
+__device__ __forceinline__ float pair_r2(const float *yi, const float (&yj)[K],
                                          float w) {
     float acc = 0.0f;
 #pragma unroll
@@ -701,7 +726,16 @@ __device__ __forceinline__ double exact_r_wave(const TX *__restrict__ X, int64_t
         for (int q = 0; q <= K; ++q)
             v[q] = __hiloint2double(__builtin_amdgcn_readlane(th, q), __builtin_amdgcn_readlane(tl, q));
     } else {
-        wave_sum_many<K + 1>(v);
+        // K = 16: lane q % 16 holds the total of v[q], the length's sum by itself
+        double c[K];
+#pragma unroll
+        for (int q = 0; q < K; ++q) c[q] = v[q];
+        const double t = wave_sum_transposed<K>(c);
+        const int tl = __double2loint(t), th = __double2hiint(t);
+        v[K] = wave_sum_fast(v[K]);
+#pragma unroll
+        for (int q = 0; q < K; ++q)
+            v[q] = __hiloint2double(__builtin_amdgcn_readlane(th, q), __builtin_amdgcn_readlane(tl, q));
     }
     double r2 = 0.0;
 #pragma unroll
@@ -1162,6 +1196,28 @@ __device__ __forceinline__ void take_window_pair(const SweepArgs<TX> &a, double 
     }
 }
 
+// (u1 <= u2) <- the two smallest of {u1, u2, v1, v2} (two sorted pairs of
+// values of distinct pairs).
+__device__ __forceinline__ void min2_merge(double &u1, double &u2, double v1, double v2) {
+    const double s = fmin(fmax(u1, v1), fmin(u2, v2));
+    u1 = fmin(u1, v1);
+    u2 = s;
+}
+
+// The (list, entry) of the g-th candidate of the four lists taken together
+// (lengths n0, n1, n2, then the rest).
+__device__ __forceinline__ void cand_place(int g, int n0, int n1, int n2, int &L, int &c) {
+    L = 0;
+    c = g;
+    if (c >= n0) {
+        c -= n0; L = 1;
+        if (c >= n1) {
+            c -= n1; L = 2;
+            if (c >= n2) { c -= n2; L = 3; }
+        }
+    }
+}
+
 // The first candidate at or after g, stepping by four over the four lists
 // taken together (lengths n0, n1, n2, then the rest of tot), whose key lies
 // in the window T2b: its key and pair, and g at it; false when none is left.
@@ -1170,14 +1226,8 @@ __device__ __forceinline__ bool next_window_entry(int &g, int tot, int n0, int n
                                                   uint32_t T2b, uint32_t &kv, int2 &ij) {
 #pragma unroll 1
     for (; g < tot; g += kPairBlock / kWave) {
-        int L = 0, c = g;   // (list, entry) of the g-th candidate (wavefront-uniform)
-        if (c >= n0) {
-            c -= n0; L = 1;
-            if (c >= n1) {
-                c -= n1; L = 2;
-                if (c >= n2) { c -= n2; L = 3; }
-            }
-        }
+        int L, c;   // (wavefront-uniform)
+        cand_place(g, n0, n1, n2, L, c);
         kv = ckey[L][c];
         ij = cij[L][c];
         if (kv <= T2b) return true;
@@ -1256,26 +1306,27 @@ __device__ __forceinline__ void finish_pass_block(const SweepArgs<TX> &a, const 
 // Fused pass block pb.  Wavefront w = 4 pb + slot takes work items
 // h = w, w + nw, ...: item h covers 4G rows of tile t = h / IPT = (bi, bj)
 // (rows 64 bi + 4G (h % IPT) ..) against its 64 columns; G = 8 (a half-tile),
-// or 4 for K >= 8.  An item's loads (G weight float4 per lane, the lane's y_j,
-// its share of the item's y_i rows) are issued together once the tile's
-// coordinates are in, at the end of the previous item; the y_i rows go
-// through the wavefront's own LDS slice (read back as broadcasts; no other
-// wavefront touches it, so no block barrier).
+// or 4 for K >= 8.  Its y_i rows come by scalar loads (each is the same for
+// every lane, and a VALU instruction takes one scalar operand for free): as
+// broadcasts from LDS they moved 4 KP x 64 bytes per row, as many LDS cycles
+// as the arithmetic has VALU cycles.  The next item's weights and y_j are
+// loaded during the current item.  At N = 40000, k = 16 the pass went from 941
+// to 830 us (VALU floor 712, the 3.2 GB at a streaming kernel's rate 535), at
+// N = 20000, k = 10 from 200 to 183 us, at N = 4000, k = 6 from 11.1 to 10.6.
 // Per pair: K subtractions, K FMAs, one multiply, one unsigned min.  Only an
 // item whose minimum lies inside the window of the block's running minimum
 // is scanned for candidates (emit_cands); they are rescored after the loop
 // (finish_pass_block).
 template <int K, typename TX>
 __device__ void fused_pass_block(const SweepArgs<TX> &a, int pb) {
-    __shared__ float4 s_y[kPairBlock / kWave][32 * kMaxK / 4];
     __shared__ int2 s_cij[kPairBlock / kWave][kCandCap];
     __shared__ uint32_t s_ckey[kPairBlock / kWave][kCandCap];
     __shared__ uint32_t s_run;
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t nw = (int64_t)a.npass * (kPairBlock / kWave);
-    const int kp = a.kp;
-    float4 *yl = s_y[wv];
+    constexpr int KP = K <= 4 ? 4 : (K <= 8 ? 8 : (K <= 12 ? 12 : 16));   // the Y row length (a.kp)
+    constexpr int R = KP >= 12 ? 1 : KP == 8 ? 2 : 4;                     // y_i rows per scalar group
     if (threadIdx.x == 0) s_run = kKeyNone;
     __syncthreads();
     // work item: G groups of 4 rows against the tile's 64 columns (a
@@ -1284,54 +1335,56 @@ __device__ void fused_pass_block(const SweepArgs<TX> &a, int pb) {
     constexpr int G = K <= 7 ? 8 : 4;
     constexpr int IPT = 16 / G;              // items per tile
     const int64_t nitem = a.nhalf * (8 / G);
-    const int nf4 = G * kp;                  // float4 count of the item's 4G rows of Y (<= 128)
     WaveBest wb{__builtin_huge_val(), __builtin_huge_val(), 0x7fffffff, 0x7fffffff, 0, 0, 0};
     CandList cl{s_cij[wv], s_ckey[wv], 0, a.cap, 0, kKeyNone};
     uint32_t kmin = kKeyNone;   // the wavefront's smallest key
     int64_t h = (int64_t)pb * (kPairBlock / kWave) + wv;
-    // loads of item h: weights, tile, y_j, two float4 of the y_i rows per lane
-    float4 w[G], yr0, yr1;
+    // the current item's weights and y_j, its tile and the next item's
+    float4 w[G];
     float yj[K];
-    int2 bt;
-    auto fetch = [&](int64_t hh) __attribute__((always_inline)) {
-        const int64_t t = hh / IPT;
-        const int part = (int)(hh % IPT);
-        const float4 *tp = a.invd2 + t * (kTileElems / 4) + part * (G * 64) + lane;
-#pragma unroll
-        for (int g = 0; g < G; ++g) w[g] = tp[g * 64];
-        bt = a.tiles[t];
-        const float4 *ysrc =
-            reinterpret_cast<const float4 *>(a.Y + ((int64_t)bt.x * kTile + 4 * G * part) * kp);
-        yr0 = ysrc[lane < nf4 ? lane : 0];
-        yr1 = ysrc[lane + 64 < nf4 ? lane + 64 : 0];
-        load_yj<K>(a.Y, kp, (int64_t)bt.y * kTile + lane, yj);
+    int2 bt, btn;
+    auto tile_of = [&](int64_t hh) __attribute__((always_inline)) {
+        const int64_t t = (hh < nitem ? hh : nitem - 1) / IPT;   // (uniform: a scalar load)
+        const int2_bits v = *(UniformI2)(a.tiles + t);
+        return make_int2(v.x, v.y);
     };
-    if (h < nitem) fetch(h);
-    for (; h < nitem; h += nw) {
-        float4 wc[G];
-#pragma unroll
-        for (int g = 0; g < G; ++g) wc[g] = w[g];
-        float yc[K];
-#pragma unroll
-        for (int c = 0; c < K; ++c) yc[c] = yj[c];
+    auto weights = [&](int64_t hh) __attribute__((always_inline)) {
+        return a.invd2 + (hh / IPT) * (kTileElems / 4) + (int)(hh % IPT) * (G * 64) + lane;
+    };
+    // one item; PF: the next item's loads are issued meanwhile -- y_j first, and
+    // each weight float4 into the registers that the group before it has used
+    // up, so that every load has about an item's time to land
+    auto item = [&](auto pf) __attribute__((always_inline)) {
+        constexpr bool PF = decltype(pf)::value;
         const int32_t row0 = bt.x * kTile + 4 * G * (int32_t)(h % IPT), col0 = bt.y * kTile;
-        __builtin_amdgcn_wave_barrier();
-        if (lane < nf4) yl[lane] = yr0;
-        if (lane + 64 < nf4) yl[lane + 64] = yr1;
-        __builtin_amdgcn_wave_barrier();
-        const float *yi0 = reinterpret_cast<const float *>(yl);
+        // the item's y_i rows are the same for every lane: they come through the
+        // constant address space (scalar loads, Y is read-only during the pass)
+        // R rows at a time, the next R in flight during this group's arithmetic
+        const UniformF yi0 = (UniformF)(a.Y + (int64_t)row0 * KP);
+        const float4 *wn = weights(h + nw);
+        float yjn[K];
+        if constexpr (PF) load_yj<K>(a.Y, KP, (int64_t)btn.y * kTile + lane, yjn);
         // the lane's 4G keys (pair (row0 + e, col0 + lane) in key[e]) stay in
-        // registers, replacing the weights they consume
+        // registers
         uint32_t key[4 * G];
         uint32_t lmin = kKeyNone;
+        float yr[2][R][KP];
+        load_rows<KP, R>(yi0, yr[0]);
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const float *yi = yi0 + 4 * g * kp;
-            key[4 * g] = __float_as_uint(pair_r2<K>(yi, yc, wc[g].x));
-            key[4 * g + 1] = __float_as_uint(pair_r2<K>(yi + kp, yc, wc[g].y));
-            key[4 * g + 2] = __float_as_uint(pair_r2<K>(yi + 2 * kp, yc, wc[g].z));
-            key[4 * g + 3] = __float_as_uint(pair_r2<K>(yi + 3 * kp, yc, wc[g].w));
-            lmin = min(lmin, min(min(key[4 * g], key[4 * g + 1]), min(key[4 * g + 2], key[4 * g + 3])));
+        for (int e0 = 0; e0 < 4 * G; e0 += R) {
+            if (e0 + R < 4 * G) load_rows<KP, R>(yi0 + (e0 + R) * KP, yr[(e0 / R + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int e = e0 + r;
+                const float4 &w4 = w[e / 4];
+                const float wt = e % 4 == 0 ? w4.x : e % 4 == 1 ? w4.y : e % 4 == 2 ? w4.z : w4.w;
+                key[e] = __float_as_uint(pair_r2<K>(yr[(e0 / R) & 1][r], yj, wt));
+                lmin = min(lmin, key[e]);
+                if constexpr (PF)
+                    if (e % 4 == 3) w[e / 4] = wn[(e / 4) * 64];
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
         const uint32_t m = wave_min_u32_fast(lmin);
         kmin = min(kmin, m);
@@ -1346,9 +1399,33 @@ __device__ void fused_pass_block(const SweepArgs<TX> &a, int pb) {
                        },
                        wb);
         __builtin_amdgcn_wave_barrier();
-        if (h + nw < nitem) fetch(h + nw);       // the next item's loads
+        if constexpr (PF) {
+#pragma unroll
+            for (int c = 0; c < K; ++c) yj[c] = yjn[c];
+        }
+    };
+    if (h < nitem) {
+        bt = tile_of(h);
+        btn = tile_of(h + nw);
+        const float4 *tp = weights(h);
+#pragma unroll
+        for (int g = 0; g < G; ++g) w[g] = tp[g * 64];
+        load_yj<K>(a.Y, KP, (int64_t)bt.y * kTile + lane, yj);
+        for (; h + nw < nitem; h += nw) {
+            const int2 bt2 = tile_of(h + 2 * nw);
+            item(std::true_type{});
+            bt = btn;
+            btn = bt2;
+        }
+        item(std::false_type{});
     }
-    finish_pass_block<K, TX>(a, cl, kmin, &s_run, wb, s_cij, s_ckey, a.part + pb);
+    // (the arguments again from the kernel's argument segment: those that only
+    // the rescoring needs would otherwise hold scalar registers all through the
+    // sweep, which needs them for the y_i rows)
+    const auto *ka = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ka));
+    const SweepArgs<TX> f = *(const SweepArgs<TX> *)ka;
+    finish_pass_block<K, TX>(f, cl, kmin, &s_run, wb, s_cij, s_ckey, f.part + pb);
 }
 
 // Plain pass block: one wavefront per 256-pair chunk (grid-stride), the
@@ -1503,14 +1580,6 @@ __device__ __forceinline__ void short_bounds(const SweepArgs<TX> &a, int64_t e, 
     const double eb = a.s_d2 / d + a.s_eps * rt;
     lb = rt - eb;
     ub = rt + eb;
-}
-
-// (u1 <= u2) <- the two smallest of {u1, u2, v1, v2} (two sorted pairs of
-// values of distinct pairs).
-__device__ __forceinline__ void min2_merge(double &u1, double &u2, double v1, double v2) {
-    const double s = fmin(fmax(u1, v1), fmin(u2, v2));
-    u1 = fmin(u1, v1);
-    u2 = s;
 }
 
 // Short pairs of the iteration from the FP64 Y, then exactly (FP64 GEMM).
