@@ -1218,6 +1218,74 @@ __device__ __forceinline__ void cand_place(int g, int n0, int n1, int n2, int &L
     }
 }
 
+// Between the coarse window and the exact evaluations (fused pass, FP64 GEMM,
+// a block with more than four candidates): every candidate of the block's
+// window T2b gets bounds from the unrounded Y64 and the stored 1/d^2,
+//   r~ = ||y64_i - y64_j|| sqrt(w),  |r~ - r| <= s_d2 sqrt(w) + (s_eps + 2^-24) r~
+// (w is 1/d^2 rounded to FP32: half of 2^-24 in r), a candidate per thread,
+// and those whose lower bound exceeds U2, the second-smallest upper bound, are
+// struck from the lists (key kKeyNone).  A candidate struck is worth more than
+// two others of the block, so the block's two smallest values stay exact FP64
+// evaluations.  The coarse value is checked against its bound here too.
+//
+// Where the window is wide against the spacing of the values (rows of FP32 Y
+// at R u32 against short pairs) it holds several pairs per block, each an
+// FP64 product over n: at N = 8000, n = 1024, k = 8 4000 of them kept blocks
+// busy for 12 to 27 us after their sweep (pass 61 us, 37 now).  Returns the
+// thread's bound violations.
+template <int K, typename TX>
+__device__ __forceinline__ int strike_candidates(const SweepArgs<TX> &a, uint32_t T2b, int tot, int n0, int n1,
+                                                 int n2, const int2 (*cij)[kCandCap], uint32_t (*ckey)[kCandCap]) {
+    __shared__ double s_u[kPairBlock / kWave][2];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const double inf = __builtin_huge_val();
+    const int g = (int)threadIdx.x;
+    double lb = 0.0, u1 = inf, u2 = inf;
+    int viol = 0, L = 0, c = 0;
+    if (g < tot) {
+        cand_place(g, n0, n1, n2, L, c);
+        const uint32_t kv = ckey[L][c];
+        if (kv <= T2b) {
+            const int2 ij = cij[L][c];
+            // (opaque: nothing of this is worth registers during the sweep)
+            int64_t N = a.N;
+            asm volatile("" : "+s"(N));
+            const int64_t nb = (N + kTile - 1) / kTile;
+            const int64_t bi = ij.x / kTile, bj = ij.y / kTile;
+            const int r = ij.x % kTile, q = ij.y % kTile;
+            const int64_t t = bi * nb - bi * (bi - 1) / 2 + (bj - bi);
+            const double w = (double)reinterpret_cast<const float *>(
+                a.invd2)[t * kTileElems + (r / 4) * 256 + q * 4 + r % 4];
+            const double *yi = a.Y64 + (int64_t)ij.x * a.kp, *yj = a.Y64 + (int64_t)ij.y * a.kp;
+            double s = 0.0;
+#pragma unroll
+            for (int e = 0; e < K; ++e) {
+                const double d = yi[e] - yj[e];
+                s = __builtin_fma(d, d, s);
+            }
+            const double sw = sqrt(w), rt = sqrt(s) * sw;
+            const double eb = (a.s_d2 * sw + (a.s_eps + 5.9604644775390625e-08) * rt) * (1.0 + 1e-6);
+            const double rc = sqrt((double)__uint_as_float(kv));
+            viol = fabs(rt - rc) > (a.e_abs + a.e_rel * fmax(rt, rc) + eb) * 1.0001 ? 1 : 0;
+            lb = rt - eb;
+            u1 = rt + eb;
+        }
+    }
+#pragma unroll 1
+    for (int o = 32; o > 0; o >>= 1) {
+        const double v1 = __shfl_xor(u1, o, kWave), v2 = __shfl_xor(u2, o, kWave);
+        min2_merge(u1, u2, v1, v2);
+    }
+    if (lane == 0) { s_u[wv][0] = u1; s_u[wv][1] = u2; }
+    __syncthreads();
+    double U1 = s_u[0][0], U2 = s_u[0][1];
+#pragma unroll
+    for (int w = 1; w < kPairBlock / kWave; ++w) min2_merge(U1, U2, s_u[w][0], s_u[w][1]);
+    if (lb > U2) ckey[L][c] = kKeyNone;
+    __syncthreads();
+    return viol;
+}
+
 // The first candidate at or after g, stepping by four over the four lists
 // taken together (lengths n0, n1, n2, then the rest of tot), whose key lies
 // in the window T2b: its key and pair, and g at it; false when none is left.
@@ -1242,10 +1310,10 @@ __device__ __forceinline__ bool next_window_entry(int &g, int tot, int n0, int n
 // Partial slot.  The block window contains the window of the pass's global
 // minimum, so every pair of the latter is rescored.  Every thread of the
 // block must call it.
-template <int K, typename TX>
+template <int K, typename TX, bool FUSED>
 __device__ __forceinline__ void finish_pass_block(const SweepArgs<TX> &a, const CandList &cl,
                                                   uint32_t kmin, const uint32_t *s_run, WaveBest &wb,
-                                                  const int2 (*cij)[kCandCap], const uint32_t (*ckey)[kCandCap],
+                                                  const int2 (*cij)[kCandCap], uint32_t (*ckey)[kCandCap],
                                                   Partial *out) {
     __shared__ int s_cn[kPairBlock / kWave];
     const int lane = threadIdx.x & 63;
@@ -1257,6 +1325,12 @@ __device__ __forceinline__ void finish_pass_block(const SweepArgs<TX> &a, const 
         const uint32_t T2b = item_window(run, a.wa, a.wb);
         const int n0 = s_cn[0], n1 = s_cn[1], n2 = s_cn[2], n3 = s_cn[3];
         const int tot = n0 + n1 + n2 + n3;
+        // up to four candidates are one evaluation per wavefront, the
+        // wavefronts side by side: no fewer would be any faster
+        if constexpr (FUSED) {
+            if (tot > kPairBlock / kWave && a.Y64)
+                wb.nviol += wave_sum_i32_fast(strike_candidates<K, TX>(a, T2b, tot, n0, n1, n2, cij, ckey));
+        }
         int g = wv;
         uint32_t k1, k2;
         int2 p1, p2;
@@ -1425,7 +1499,7 @@ __device__ void fused_pass_block(const SweepArgs<TX> &a, int pb) {
     const auto *ka = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(ka));
     const SweepArgs<TX> f = *(const SweepArgs<TX> *)ka;
-    finish_pass_block<K, TX>(f, cl, kmin, &s_run, wb, s_cij, s_ckey, f.part + pb);
+    finish_pass_block<K, TX, true>(f, cl, kmin, &s_run, wb, s_cij, s_ckey, f.part + pb);
 }
 
 // Plain pass block: one wavefront per 256-pair chunk (grid-stride), the
@@ -1464,7 +1538,7 @@ __device__ void plain_pass_block(const SweepArgs<TX> &a, int pb) {
                        },
                        wb);
     }
-    finish_pass_block<K, TX>(a, cl, kmin, &s_run, wb, s_cij, s_ckey, a.part + pb);
+    finish_pass_block<K, TX, false>(a, cl, kmin, &s_run, wb, s_cij, s_ckey, a.part + pb);
 }
 
 // c = P^T (x_i - x_j) for 16 short pairs in FP64 on the matrix cores, tiled
