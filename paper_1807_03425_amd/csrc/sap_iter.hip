@@ -570,6 +570,8 @@ __device__ __forceinline__ void gemm_block_deep(const TX *__restrict__ X, int64_
 typedef const __attribute__((address_space(4))) float *UniformF;
 typedef int int2_bits __attribute__((ext_vector_type(2)));
 typedef const __attribute__((address_space(4))) int2_bits *UniformI2;
+typedef int int4_bits __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(4))) int4_bits *UniformI4;
 
 // R consecutive rows of Y (KP floats each) from a wavefront-uniform address,
 // whole rows (one or two scalar loads each).
@@ -589,6 +591,16 @@ __device__ __forceinline__ void load_rows(UniformF p, float (&y)[R][KP]) {
 #pragma unroll
         for (int c = 0; c < W; ++c) y[r][KP - W + c] = v[c];
     }
+}
+
+// Waits for rows loaded by load_rows (the empty asm reads the end of each
+// row's loads).  Scalar loads return in any order, so a wait is for all of
+// them: it has to stand before the next rows' loads, not behind.
+template <int KP, int R>
+__device__ __forceinline__ void wait_rows(const float (&y)[R][KP]) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) asm volatile("" ::"s"(y[r][0]), "s"(y[r][KP - 1]));
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // Coarse squared ratio of one pair: ||y_i - y_j||^2 * (1/d^2).  y_i is
@@ -1384,9 +1396,10 @@ __device__ __forceinline__ void finish_pass_block(const SweepArgs<TX> &a, const 
 // every lane, and a VALU instruction takes one scalar operand for free): as
 // broadcasts from LDS they moved 4 KP x 64 bytes per row, as many LDS cycles
 // as the arithmetic has VALU cycles.  The next item's weights and y_j are
-// loaded during the current item.  At N = 40000, k = 16 the pass went from 941
-// to 830 us (VALU floor 712, the 3.2 GB at a streaming kernel's rate 535), at
-// N = 20000, k = 10 from 200 to 183 us, at N = 4000, k = 6 from 11.1 to 10.6.
+// loaded during the current item.  The pass at N = 40000, k = 16: 780 us, 950
+// before (VALU floor 712, the 3.2 GB at a streaming kernel's rate 535); N =
+// 20000, k = 10: 159 and 182; N = 8000, k = 4: 29.8 and 35; N = 4000, k = 6:
+// 9.5 and 9.7.
 // Per pair: K subtractions, K FMAs, one multiply, one unsigned min.  Only an
 // item whose minimum lies inside the window of the block's running minimum
 // is scanned for candidates (emit_cands); they are rescored after the loop
@@ -1400,7 +1413,10 @@ __device__ void fused_pass_block(const SweepArgs<TX> &a, int pb) {
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t nw = (int64_t)a.npass * (kPairBlock / kWave);
     constexpr int KP = K <= 4 ? 4 : (K <= 8 ? 8 : (K <= 12 ? 12 : 16));   // the Y row length (a.kp)
-    constexpr int R = KP >= 12 ? 1 : KP == 8 ? 2 : 4;                     // y_i rows per scalar group
+    // y_i rows per scalar group: two groups in flight fill the scalar registers
+    // (half as many rows left a wait per 140 cycles of arithmetic, 10% of the
+    // pass at k = 16; twice as many spill)
+    constexpr int R = KP >= 12 ? 2 : KP == 8 ? 4 : 8;
     if (threadIdx.x == 0) s_run = kKeyNone;
     __syncthreads();
     // work item: G groups of 4 rows against the tile's 64 columns (a
@@ -1446,6 +1462,7 @@ __device__ void fused_pass_block(const SweepArgs<TX> &a, int pb) {
         load_rows<KP, R>(yi0, yr[0]);
 #pragma unroll
         for (int e0 = 0; e0 < 4 * G; e0 += R) {
+            wait_rows<KP, R>(yr[(e0 / R) & 1]);
             if (e0 + R < 4 * G) load_rows<KP, R>(yi0 + (e0 + R) * KP, yr[(e0 / R + 1) & 1]);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -1454,6 +1471,7 @@ __device__ void fused_pass_block(const SweepArgs<TX> &a, int pb) {
                 const float4 &w4 = w[e / 4];
                 const float wt = e % 4 == 0 ? w4.x : e % 4 == 1 ? w4.y : e % 4 == 2 ? w4.z : w4.w;
                 key[e] = __float_as_uint(pair_r2<K>(yr[(e0 / R) & 1][r], yj, wt));
+                asm volatile("" : "+v"(key[e]));   // computed here: deferred, the rows would outlive the scalar registers
                 lmin = min(lmin, key[e]);
                 if constexpr (PF)
                     if (e % 4 == 3) w[e / 4] = wn[(e / 4) * 64];
