@@ -91,6 +91,7 @@ struct sap_ctx {
     // than compute units, so that one round of blocks covers the rows)
     int gtiles = 1;
     int short_grid_it = 0;   // short-pair blocks of the iteration's pass (<= short_grid)
+    int cus = 256;     // compute units
     int sm_grid = 0;   // fused: blocks of the soft-min tile passes
     size_t tail_lds = 0;
 
@@ -99,6 +100,7 @@ struct sap_ctx {
     float *d_smP32 = nullptr;         // the forward's P as passed (n x k FP32)
     float *d_smY = nullptr;
     SmPart *d_smpart = nullptr;
+    int sm_nshares = 0, sm_layer = 1;   // backward: shares (four per block), blocks per round
     float *d_smZr = nullptr, *d_smZc = nullptr;
     double *d_smZ = nullptr, *d_zpair = nullptr, *d_smG = nullptr;
     int sm_chunks = 0;
@@ -495,6 +497,7 @@ static sap_status init_fused(sap_ctx *h) {
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || cus <= 0)
         cus = 256;
+    h->cus = cus;
     const int64_t slots = 4 * (int64_t)cus;
     // the split GEMM: 512 or 1024 components, 16-byte X rows, FP64, and fewer
     // 64-row blocks than compute units (the split doubles them)
@@ -503,9 +506,8 @@ static sap_status init_fused(sap_ctx *h) {
     h->gtiles = (h->n < 512 && h->Npad / 64 > cus) ? 2 : 1;
     h->pass_grid = (int)std::max<int64_t>(
         1, std::min<int64_t>(ceil_div(2 * h->ntiles, 4), std::max<int64_t>(slots / 4, slots - h->short_grid_it)));
-    // soft-min tile passes (three or four blocks per compute unit): eight
-    // half-tiles per block, many rounds
-    h->sm_grid = (int)std::min<int64_t>(ceil_div(2 * h->ntiles, 8), 8192);
+    // soft-min forward: one round of resident blocks over the half-tiles
+    h->sm_grid = (int)std::min<int64_t>(ceil_div(2 * h->ntiles, 4), slots);
     return SAP_OK;
 }
 
@@ -751,15 +753,23 @@ static sap_status sm_check(sap_ctx *h, const float *P, double tau) {
 static sap_status sm_alloc(sap_ctx *h) {
     if (h->d_smY) return SAP_OK;
     const int K = h->k;
-    const int64_t nhalf = 2 * h->ntiles;
+    // Backward shares: the half-tiles in equal runs (to one half-tile), one for
+    // each resident wavefront (k_sm_bwd's blocks per compute unit); fewer rounds
+    // of blocks, or a part of one, where that covers the half-tiles (a few
+    // shares can then be empty)
+    const int64_t nhalf = 2 * h->ntiles, wpb = kPairBlock / kWave;
+    const int64_t layer = std::min<int64_t>(h->cus, ceil_div(nhalf, wpb));
+    const int64_t nw = wpb * layer * std::min<int64_t>(K <= 12 ? 3 : 2, ceil_div(nhalf, wpb * layer));
+    h->sm_nshares = (int)nw;
+    h->sm_layer = (int)layer;
     h->sm_rows = std::max<int64_t>(64, ceil_div(h->N, 256));
     h->sm_chunks = (int)ceil_div(h->N, h->sm_rows);
     SAP_TRY(dalloc(h, &h->d_smP64t, sizeof(double) * h->n * K));
     SAP_TRY(dalloc(h, &h->d_smP32, sizeof(float) * h->n * K));
     SAP_TRY(dalloc(h, &h->d_smY, sizeof(float) * (size_t)h->Npad * h->kp));
     SAP_TRY(dalloc(h, &h->d_smpart, sizeof(SmPart) * (size_t)(h->sm_grid + h->short_grid)));
-    SAP_TRY(dalloc(h, &h->d_smZr, sizeof(float) * (size_t)nhalf * K * 32));
-    SAP_TRY(dalloc(h, &h->d_smZc, sizeof(float) * (size_t)nhalf * K * 64));
+    SAP_TRY(dalloc(h, &h->d_smZr, sizeof(float) * (size_t)(h->sm_nshares + h->nb) * K * 64));
+    SAP_TRY(dalloc(h, &h->d_smZc, sizeof(float) * (size_t)(h->ntiles + h->sm_nshares) * K * 64));
     SAP_TRY(dalloc(h, &h->d_smZ, sizeof(double) * (size_t)h->N * K));
     SAP_TRY(dalloc(h, &h->d_zpair, sizeof(double) * (size_t)std::max<int64_t>(h->nclose, 1) * K));
     SAP_TRY(dalloc(h, &h->d_smG, sizeof(double) * (size_t)h->sm_chunks * h->n * K));
@@ -786,6 +796,12 @@ static SmArgs sm_args(sap_ctx *h, double tau) {
     a.c2 = (float)(1.4426950408889634 / tau);   // log2(e) / tau
     a.part = h->d_smpart;
     a.Lp = &h->d_st->sm_L;
+    a.nshares = h->sm_nshares;
+    a.layer = h->sm_layer;
+    a.share = a.nhalf / a.nshares;
+    a.share_rem = (int)(a.nhalf % a.nshares);
+    a.ntiles = h->ntiles;
+    a.nb = h->nb;
     a.Zr = h->d_smZr;
     a.Zc = h->d_smZc;
     a.zpair = h->d_zpair;
@@ -825,9 +841,9 @@ static sap_status sm_backward(sap_ctx *h, double tau, const float *grad_loss, fl
                                               [&](const LaunchCfg &c) {
             return KLaunch<K, TX>::sm_prep(c, a, X, h->ldx, h->N, h->d_mu, h->d_smY, h->Npad, 0, 1);
         })));
-    SAP_DISPATCH_K(K, SAP_TRY(launch_with(h, 4, "k_sm_bwd", dim3((unsigned)h->sm_grid), blk, 0,
+    SAP_DISPATCH_K(K, SAP_TRY(launch_with(h, 4, "k_sm_bwd", dim3((unsigned)h->sm_nshares / (kPairBlock / kWave)), blk, 0,
                                           [&](const LaunchCfg &c) { return KLaunch<K, TX>::sm_bwd(c, a); })));
-    SAP_DISPATCH_K(K, SAP_TRY(launch_with(h, 5, "k_sm_zred", dim3((unsigned)h->nb), blk, 0,
+    SAP_DISPATCH_K(K, SAP_TRY(launch_with(h, 5, "k_sm_zred", dim3((unsigned)h->nb), dim3(kZredWaves * kWave), 0,
                                           [&](const LaunchCfg &c) {
         return KLaunch<K, TX>::sm_zred(c, a, h->nb, h->N, h->d_rp_i, h->d_rp_j, h->d_permj, h->d_smZ);
     })));

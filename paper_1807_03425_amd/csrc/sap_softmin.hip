@@ -22,10 +22,10 @@
 //             k_sm_fwd     per-block (min, scaled sum) over the tiles
 //             k_sm_fin     one block: merge in FP64, L, loss
 //   backward: k_sm_prep    (short-pair blocks only) a_ij (y_i - y_j) per short pair
-//             k_sm_bwd     per half-tile partial z sums, rows and columns
-//                          (weights and column side on VALU, row-side
-//                          contraction on FP64 MFMA)
-//             k_sm_zred    z_i per point: tile partials + short pairs, FP64
+//             k_sm_bwd     partial z sums of rows (per share: half-tiles of a
+//                          row of tiles) and columns (per tile) -- weights and
+//                          column side on VALU, row-side contraction on FP64 MFMA
+//             k_sm_zred    z_i per point: partials + short pairs, FP64
 //             k_sm_grad    (X - mu)^T Z per row chunk, FP64 MFMA
 //             k_sm_dP      sum of the chunks times dL/dloss
 #include "sap_common.h"
@@ -59,8 +59,12 @@ struct SmArgs {
     SmPart *part;          // npass + nshort partials (forward)
     const double *Lp;      // L of the forward (backward)
     // backward partials
-    float *Zr;             // per half-tile: 32 x K row-side partials, point-major
-    float *Zc;             // per half-tile: 64 x K column-side partials, point-major
+    int nshares, layer;        // shares, blocks of a round over the compute units
+    int64_t share;             // half-tiles per share, rounded down, and the rest
+    int share_rem;
+    int64_t nb, ntiles;        // 64-point blocks, tiles
+    float *Zr;                 // per share and row of tiles it touches: K x 64 row-side partials
+    float *Zc;                 // per tile, then per share: K x 64 column-side partials
     double *zpair;         // per short pair: a (y_i - y_j), K values
 };
 
@@ -165,61 +169,98 @@ __device__ __forceinline__ float comp4(const float4 &v, int r) {
     return r == 0 ? v.x : r == 1 ? v.y : r == 2 ? v.z : v.w;
 }
 
-// Forward pass: one wavefront per half-tile (as the pair pass).  Per lane,
-// the 32 r of a half-tile are reduced to their min m_c and
-// s_c = sum 2^((m_c - r) c2), then folded into the lane's running (m, s).
-// Masked pairs take r = 2e30, beyond the 1e30 start of every min, so their
-// terms underflow to 0.
+// Forward pass: half-tiles dealt to the wavefronts of a resident grid (as the
+// pair pass: y_i rows by scalar loads, the next half-tile's weights and y_j in
+// flight during the current one).  Per lane, the 32 r of a half-tile are
+// reduced to their min m_c and s_c = sum 2^((m_c - r) c2), then folded into
+// the lane's running (m, s).  A masked pair's 1/d^2 is negative: its r is NaN
+// (the sum of squares starts at 1e-36, so that it is not -0 where y_i = y_j),
+// which the minimum passes over and the clamp of its term to [0, 1] (a
+// modifier of the exponential) makes 0.
+// Bound by VALU issue, 2K + 12 slots per pair (sqrt and exp2 as 4): N = 20000,
+// k = 10 172 us against 163 (224 with the y_i rows through LDS, 8192 blocks and
+// two slots more per pair); N = 1531, k = 3 6 us (10).
 template <int K>
-__global__ __launch_bounds__(kPairBlock) void k_sm_fwd(SmArgs a) {
-    __shared__ float4 s_y[kPairBlock / kWave][32 * kMaxK / 4];
+__global__ __launch_bounds__(kPairBlock, 4) void k_sm_fwd(SmArgs a) {
+    constexpr int KP = K <= 4 ? 4 : (K <= 8 ? 8 : (K <= 12 ? 12 : 16));   // the Y row length (a.kp)
+    constexpr int R = KP >= 12 ? 2 : KP == 8 ? 4 : 8;                     // y_i rows per scalar group
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t wid = (int64_t)blockIdx.x * (kPairBlock / kWave) + wv;
     const int64_t nw = (int64_t)a.npass * (kPairBlock / kWave);
-    const int kp = a.kp;
     const float c2 = a.c2;
-    float4 *yl = s_y[wv];
-    const int nf4 = 8 * kp;
     float m = 1e30f;
     double s = 0.0;
-    for (int64_t h = wid; h < a.nhalf; h += nw) {
-        const int64_t t = h >> 1;
-        const int half = (int)(h & 1);
-        const float4 *tp = a.invd2 + t * (kTileElems / 4) + half * 512 + lane;
-        float4 w[8];
-#pragma unroll
-        for (int g = 0; g < 8; ++g) w[g] = tp[g * 64];
-        const int2 b = a.tiles[t];
-        const float4 *ysrc =
-            reinterpret_cast<const float4 *>(a.Y + ((int64_t)b.x * kTile + 32 * half) * kp);
-        __builtin_amdgcn_wave_barrier();
-        for (int f = lane; f < nf4; f += kWave) yl[f] = ysrc[f];
-        __builtin_amdgcn_wave_barrier();
-        float yj[K];
-        load_yj<K>(a.Y, kp, (int64_t)b.y * kTile + lane, yj);
-        const float *yi0 = reinterpret_cast<const float *>(yl);
+    int64_t h = (int64_t)blockIdx.x * (kPairBlock / kWave) + wv;
+    float4 w[8];
+    float yj[K];
+    int2 bt, btn;
+    auto tile_of = [&](int64_t hh) __attribute__((always_inline)) {
+        const int2_bits v = *(UniformI2)(a.tiles + ((hh < a.nhalf ? hh : a.nhalf - 1) >> 1));
+        return make_int2(v.x, v.y);
+    };
+    auto weights = [&](int64_t hh) __attribute__((always_inline)) {
+        return a.invd2 + (hh >> 1) * (kTileElems / 4) + (int)(hh & 1) * 512 + lane;
+    };
+    auto item = [&](auto pf) __attribute__((always_inline)) {
+        constexpr bool PF = decltype(pf)::value;
+        const UniformF yi0 = (UniformF)(a.Y + ((int64_t)bt.x * kTile + 32 * (int)(h & 1)) * KP);
+        const float4 *wn = weights(h + nw);
+        float yjn[K];
+        if constexpr (PF) load_yj<K>(a.Y, KP, (int64_t)btn.y * kTile + lane, yjn);
         float r[32];
         float mc = 1e30f;
+        float yr[2][R][KP];
+        load_rows<KP, R>(yi0, yr[0]);
 #pragma unroll
-        for (int g = 0; g < 8; ++g) {
+        for (int e0 = 0; e0 < 32; e0 += R) {
+            wait_rows<KP, R>(yr[(e0 / R) & 1]);
+            if (e0 + R < 32) load_rows<KP, R>(yi0 + (e0 + R) * KP, yr[(e0 / R + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const float wt = comp4(w[g], rr);
-                const float acc = pair_r2<K>(yi0 + (4 * g + rr) * kp, yj, 1.0f);
-                const float rv = wt > 0.0f ? __builtin_amdgcn_sqrtf(acc * wt) : 2e30f;
-                r[4 * g + rr] = rv;
-                mc = fminf(mc, rv);
+            for (int rr = 0; rr < R; ++rr) {
+                const int e = e0 + rr;
+                float acc = 1e-36f;
+#pragma unroll
+                for (int c = 0; c < K; ++c) {
+                    const float d = yr[(e0 / R) & 1][rr][c] - yj[c];
+                    acc = __builtin_fmaf(d, d, acc);
+                }
+                r[e] = __builtin_amdgcn_sqrtf(acc * comp4(w[e / 4], e % 4));
+                asm volatile("" : "+v"(r[e]));   // computed here: deferred, the rows would outlive the scalar registers
+                mc = fminf(mc, r[e]);
+                if constexpr (PF)
+                    if (e % 4 == 3) w[e / 4] = wn[(e / 4) * 64];
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
         float sc = 0.0f;
         const float mcc = mc * c2;
 #pragma unroll
-        for (int e = 0; e < 32; ++e) sc += __builtin_amdgcn_exp2f(__builtin_fmaf(-r[e], c2, mcc));
+        for (int e = 0; e < 32; ++e)
+            sc += __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(__builtin_fmaf(-r[e], c2, mcc)), 0.0f, 1.0f);
         const float mn = fminf(m, mc);
         s = s * (double)__builtin_amdgcn_exp2f((mn - m) * c2) +
             (double)(sc * __builtin_amdgcn_exp2f((mn - mc) * c2));
         m = mn;
+        if constexpr (PF) {
+#pragma unroll
+            for (int c = 0; c < K; ++c) yj[c] = yjn[c];
+        }
+    };
+    if (h < a.nhalf) {
+        bt = tile_of(h);
+        btn = tile_of(h + nw);
+        const float4 *tp = weights(h);
+#pragma unroll
+        for (int g = 0; g < 8; ++g) w[g] = tp[g * 64];
+        load_yj<K>(a.Y, KP, (int64_t)bt.y * kTile + lane, yj);
+        for (; h + nw < a.nhalf; h += nw) {
+            const int2 bt2 = tile_of(h + 2 * nw);
+            item(std::true_type{});
+            bt = btn;
+            btn = bt2;
+        }
+        item(std::false_type{});
     }
     block_lse((double)m, s, a.tau, a.part + blockIdx.x);
 }
@@ -251,13 +292,28 @@ __global__ __launch_bounds__(kPairBlock) void k_sm_fin(const SmPart *__restrict_
 // consecutive columns) too.
 constexpr int kAStride = 66;
 
-// Backward pass: one wavefront per half-tile (rows i = 64 bi + 32 half +
-// 0..31, columns j = 64 bj + 0..63).
-// Phase 1 (lane = column j): the weights a_ij of the lane's column, one
-// float4 of 1/d^2 per four rows, and the column side
+// First half-tile of share w (of a.nshares equal runs, to one half-tile).
+__device__ __forceinline__ int64_t share_start(const SmArgs &a, int w) {
+    return w * a.share + (unsigned)w * (unsigned)a.share_rem / (unsigned)a.nshares;
+}
+
+// The share that holds half-tile p: the last that starts at or before it.
+__device__ __forceinline__ int share_of(const SmArgs &a, int64_t p) {
+    int w = (int)((double)p * (double)a.nshares / (double)a.nhalf);
+    while (w + 1 < a.nshares && share_start(a, w + 1) <= p) ++w;
+    while (share_start(a, w) > p) --w;
+    return w;
+}
+
+// Backward pass: one wavefront per share, a run of consecutive half-tiles (32
+// rows of a tile), row of tiles by row of tiles.
+// Phase 1 of a half-tile (lane = column j): the weights a_ij of the lane's
+// column, one float4 of 1/d^2 per four rows (y_i rows by scalar loads), and
+// the column side
 //   z_j += sum_i a_ij (y_j - y_i)
 // accumulated in FP32 from the differences y_i - y_j that the weight needed
-// anyway; a_ij goes to the wavefront's LDS block.
+// anyway, over the halves of the tile that the share holds; a_ij goes to the
+// wavefront's LDS block.
 // Phase 2: the row side
 //   z_i += sum_j a_ij (y_i - y_j) = (sum_j a_ij) y_i - (A Y_J)_i
 // on the matrix cores in FP64 (v_mfma_f64_16x16x4f64, K padded to 16
@@ -266,197 +322,231 @@ constexpr int kAStride = 66;
 // coordinates are exact in FP64 and the products and sums FP64, so the
 // difference of the two large terms keeps the accuracy of the direct sum of
 // differences.  For K < 16 the padding column 15 of B is 1, which makes
-// column 15 of the product the row sum; K = 16 sums the rows separately.
-// Partials go to Zr (32 x K) and Zc (64 x K) per half-tile, point-major, in
-// FP32.  LDS per block: 38 KB (K <= 4) to 56 KB (K >= 13): three blocks per
-// compute unit for K <= 12 (at most 168 registers), two for K >= 13.
+// column 15 of the product the row sum; K = 16 sums the rows separately.  The
+// products accumulate over a row of tiles, and the row side is formed at its end.
+//
+// Partials, component-major in FP32: Zr once per row, Zc once per tile, and
+// once more for a tile whose halves fall in two shares.  Per half-tile and
+// point-major they were 377 MB written and read again at N = 20000, k = 10
+// (k_sm_zred 90 us; 25 now).
+// Bound by issue: 4K + 16 VALU slots per pair (rsq and exp2 as 4) and the FP64
+// products, which other wavefronts' VALU work covers in part: N = 20000, k = 10
+// 383 us (407 with a block per half-tile and the rows through LDS), N = 14000,
+// k = 16 250 (296), N = 9000, k = 10 85 (79; runs and their merge together 140
+// and 155).
+// LDS per block: 37 KB (K <= 4) to 49 KB (K >= 13): three blocks per compute
+// unit, two for K >= 13 (at three they would spill).
 template <int K>
 __global__ __launch_bounds__(kPairBlock, K <= 12 ? 3 : 2) void k_sm_bwd(SmArgs a) {
-    constexpr int KP = K <= 4 ? 4 : (K <= 8 ? 8 : (K <= 12 ? 12 : 16));   // the Y row length kp
-    __shared__ float4 s_y[kPairBlock / kWave][32 * KP / 4];
+    constexpr int KP = K <= 4 ? 4 : (K <= 8 ? 8 : (K <= 12 ? 12 : 16));   // the Y row length (a.kp)
     __shared__ float4 s_yc[kPairBlock / kWave][64 * KP / 4];
     __shared__ float s_a[kPairBlock / kWave][32 * kAStride];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t wid = (int64_t)blockIdx.x * (kPairBlock / kWave) + wv;
-    const int64_t nw = (int64_t)a.npass * (kPairBlock / kWave);
-    constexpr int kp = KP;                            // equals a.kp
     const float c2 = a.c2;
     const float Lc = (float)(*a.Lp) * c2;
-    float4 *yl = s_y[wv];
     float4 *ycl = s_yc[wv];
     float *al = s_a[wv];
+    const float *yc0 = reinterpret_cast<const float *>(ycl);
     const int c16 = lane & 15, r4 = lane >> 4;
     const bool qin = c16 < K;
-    const int qc = qin ? c16 : K - 1;                 // clamped component: in-bounds LDS reads
+    const int qc = qin ? c16 : K - 1;                 // clamped component: in-bounds reads
     const double bpad = (K < 16 && c16 == 15) ? 1.0 : 0.0;
-    const float *alr = al + c16 * kAStride + r4;      // row-side reads: + 16 mb kAStride + 4 tt
-    for (int64_t h = wid; h < a.nhalf; h += nw) {
-        const int64_t t = h >> 1;
-        const int half = (int)(h & 1);
-        const float4 *tp = a.invd2 + t * (kTileElems / 4) + half * 512 + lane;
-        float4 wn = tp[0];
-        const int2 b = a.tiles[t];
-        const float4 *ysrc =
-            reinterpret_cast<const float4 *>(a.Y + ((int64_t)b.x * kTile + 32 * half) * kp);
-        const float4 *ycsrc = reinterpret_cast<const float4 *>(a.Y + (int64_t)b.y * kTile * kp);
-        __builtin_amdgcn_wave_barrier();
-        for (int f = lane; f < 8 * kp; f += kWave) yl[f] = ysrc[f];
-        for (int f = lane; f < 16 * kp; f += kWave) ycl[f] = ycsrc[f];
-        __builtin_amdgcn_wave_barrier();
-        const float *yi0 = reinterpret_cast<const float *>(yl);
-        const float *yc0 = reinterpret_cast<const float *>(ycl);
-        float yj[K], zc[K];
+    const float *alr = al + c16 * kAStride + r4;      // row-side reads: + 16 mb kAStride + 4 u
+    // the shares that one SIMD gets (blocks c, c + layer, ..., same wavefront)
+    // are neighbours: their lengths add to the same total, to one half-tile
+    const int w = (((int)blockIdx.x % a.layer) * (kPairBlock / kWave) + wv) * (a.nshares / (a.layer * (kPairBlock / kWave))) +
+                  (int)blockIdx.x / a.layer;
+    int64_t p = share_start(a, w);
+    const int64_t p1 = share_start(a, w + 1);
+    int bi = ((UniformI2)(a.tiles + (p >> 1)))->x;
+    do {                                              // (an empty share: a row side of zeros)
+        const int64_t trow = (int64_t)bi * a.nb - (int64_t)bi * (bi - 1) / 2;   // tile (bi, bi)
+        const int64_t row1 = 2 * (trow + a.nb - bi);
+        const int h0 = (int)(p - 2 * trow), h1 = (int)((p1 < row1 ? p1 : row1) - 2 * trow);
+        const float4 *trow4 = a.invd2 + trow * (kTileElems / 4) + lane;
+        const float *yrow = a.Y + (int64_t)bi * kTile * KP;
+        auto column = [&](int h) __attribute__((always_inline)) {
+            return reinterpret_cast<const float4 *>(a.Y + ((int64_t)(bi + (h >> 1)) * kTile + lane) * KP);
+        };
+        double4_t accr[4];
+        double rs[4];
 #pragma unroll
-        for (int q = 0; q < K; ++q) { yj[q] = yc0[lane * kp + q]; zc[q] = 0.0f; }
-        // phase 1, four rows (one weight float4) per step; the next step's
-        // weights are loaded ahead
+        for (int u = 0; u < 4; ++u) { accr[u] = double4_t{0.0, 0.0, 0.0, 0.0}; rs[u] = 0.0; }
+        // the first tile's column rows and the first weights
+        float4 yv[KP / 4], wq[2];
+#pragma unroll
+        for (int u = 0; u < KP / 4; ++u) yv[u] = column(h0)[u];
+        wq[0] = trow4[(int64_t)h0 * 512];
+        wq[1] = trow4[(int64_t)h0 * 512 + 64];
+        for (int h = h0; h < h1;) {
+            float yj[K], zc[K];
+            __builtin_amdgcn_wave_barrier();   // (the previous tile's columns have been read)
+#pragma unroll
+            for (int u = 0; u < KP / 4; ++u) ycl[lane * (KP / 4) + u] = yv[u];
+#pragma unroll
+            for (int q = 0; q < K; ++q) {
+                yj[q] = comp4(yv[q / 4], q % 4);
+                zc[q] = 0.0f;
+            }
+            const int hn = (h | 1) + 1;        // the next tile's first half
+            {   // its column rows (this tile's again at the end)
+                const float4 *src = column(hn < h1 ? hn : h);
+#pragma unroll
+                for (int u = 0; u < KP / 4; ++u) yv[u] = src[u];
+            }
+            auto half_tile = [&](auto hsel) __attribute__((always_inline)) {
+                constexpr int HS = decltype(hsel)::value;
+                const float4 *tp = trow4 + (int64_t)h * 512;
+                const float4 *tpn = trow4 + (int64_t)(h + 1 < h1 ? h + 1 : h) * 512;
+                const UniformF yi0 = (UniformF)(yrow + 32 * HS * KP);
 #pragma unroll 1
-        for (int g = 0; g < 8; ++g) {
-            const float4 w4 = wn;
-            if (g < 7) wn = tp[(g + 1) * 64];
+                for (int g = 0; g < 8; g += 2) {
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const int i = 4 * g + rr;
-                const float wt = comp4(w4, rr);
-                const float *yi = yi0 + i * kp;
-                float d[K];
-                float acc2 = 0.0f;
+                    for (int g2 = 0; g2 < 2; ++g2) {
+                        const float4 w4 = wq[g2];
+                        wq[g2] = g < 6 ? tp[(g + 2 + g2) * 64] : tpn[g2 * 64];
+                        float yr[4][KP];
+                        load_rows<KP, 4>(yi0 + 4 * (g + g2) * KP, yr);
 #pragma unroll
-                for (int q = 0; q < K; ++q) {
-                    d[q] = yi[q] - yj[q];
-                    acc2 = __builtin_fmaf(d[q], d[q], acc2);
+                        for (int rr = 0; rr < 4; ++rr) {
+                            const float wt = comp4(w4, rr);
+                            float d[K];
+                            float acc2 = 0.0f;
+#pragma unroll
+                            for (int q = 0; q < K; ++q) {
+                                d[q] = yr[rr][q] - yj[q];
+                                acc2 = __builtin_fmaf(d[q], d[q], acc2);
+                            }
+                            // masked pairs (1/d^2 < 0) and r = 0: the reciprocal
+                            // root makes NaN of both, the maximum 0 of that
+                            const float r2 = acc2 * wt;
+                            const float rinv = __builtin_amdgcn_rsqf(r2);
+                            const float rv = r2 * rinv;
+                            const float ex = __builtin_amdgcn_exp2f(__builtin_fmaf(-rv, c2, Lc));
+                            const float av = fmaxf(ex * wt * rinv, 0.0f);
+#pragma unroll
+                            for (int q = 0; q < K; ++q) zc[q] = __builtin_fmaf(-av, d[q], zc[q]);
+                            al[(4 * (g + g2) + rr) * kAStride + lane] = av;
+                        }
+                    }
                 }
-                // r2 > 0 also excludes the masked pairs (1/d^2 < 0)
-                const float r2 = acc2 * wt;
-                const float rinv = __builtin_amdgcn_rsqf(r2);
-                const float rv = r2 * rinv;
-                const float ex = __builtin_amdgcn_exp2f(__builtin_fmaf(-rv, c2, Lc));
-                const float av = r2 > 0.0f ? ex * wt * rinv : 0.0f;
-#pragma unroll
-                for (int q = 0; q < K; ++q) zc[q] = __builtin_fmaf(-av, d[q], zc[q]);
-                al[i * kAStride + lane] = av;
-            }
-        }
-        float *zcol = a.Zc + h * (int64_t)(K * 64) + lane * K;
-#pragma unroll
-        for (int q = 0; q < K; ++q) zcol[q] = zc[q];
-        __builtin_amdgcn_wave_barrier();
-        // phase 2: A[16 mb + c16][4 tt + r4] from LDS, B = Y_J[4 tt + r4][c16]
-        double4_t accr0 = {0.0, 0.0, 0.0, 0.0}, accr1 = {0.0, 0.0, 0.0, 0.0};
-        double rs0 = 0.0, rs1 = 0.0;
+                __builtin_amdgcn_wave_barrier();
+                // phase 2: A[16 mb + c16][4 u + r4] from LDS, B = Y_J[4 u + r4][c16]
 #pragma unroll 4
-        for (int tt = 0; tt < 16; ++tt) {
-            const int jc = 4 * tt + r4;
-            const float yv = yc0[jc * kp + qc];
-            const double bq = qin ? (double)yv : bpad;
-            const double a0 = (double)alr[4 * tt];
-            const double a1 = (double)alr[16 * kAStride + 4 * tt];
-            if constexpr (K == 16) {
-                rs0 += a0;
-                rs1 += a1;
-            }
-            accr0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, bq, accr0, 0, 0, 0);
-            accr1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, bq, accr1, 0, 0, 0);
+                for (int u = 0; u < 16; ++u) {
+                    const int jc = 4 * u + r4;
+                    const float yv2 = yc0[jc * KP + qc];
+                    const double bq = qin ? (double)yv2 : bpad;
+                    const double a0 = (double)alr[4 * u];
+                    const double a1 = (double)alr[16 * kAStride + 4 * u];
+                    if constexpr (K == 16) {
+                        rs[2 * HS] += a0;
+                        rs[2 * HS + 1] += a1;
+                    }
+                    accr[2 * HS] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, bq, accr[2 * HS], 0, 0, 0);
+                    accr[2 * HS + 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, bq, accr[2 * HS + 1], 0, 0, 0);
+                }
+                __builtin_amdgcn_wave_barrier();
+                ++h;
+            };
+            const bool tail = h & 1;           // the tile's first half lies in the share before
+            float *zcol = a.Zc + (tail ? a.ntiles + w : trow + (h >> 1)) * (int64_t)(K * 64) + lane;
+            if (!tail) half_tile(std::integral_constant<int, 0>{});
+            if (h < hn && h < h1) half_tile(std::integral_constant<int, 1>{});
+#pragma unroll
+            for (int q = 0; q < K; ++q) zcol[q * 64] = zc[q];
         }
-        if constexpr (K == 16) {
-            rs0 += __shfl_xor(rs0, 16, kWave);
-            rs0 += __shfl_xor(rs0, 32, kWave);
-            rs1 += __shfl_xor(rs1, 16, kWave);
-            rs1 += __shfl_xor(rs1, 32, kWave);
-        }
-        float *zrow = a.Zr + h * (int64_t)(K * 32);
+        float *zrow = a.Zr + (w + bi) * (int64_t)(K * 64);
         // lane holds (A Y_J)[16 mb + r4 + 4 v][c16]; row (r4 + 4 v)'s sum sits
         // in the lanes with c16 = r4 + 4 v (K = 16), or in column 15 of the
         // product, lane (r4, 15) (K < 16)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int i0 = r4 + 4 * v, i1 = 16 + r4 + 4 * v;
-            double s0, s1;
+        for (int mb = 0; mb < 4; ++mb) {
             if constexpr (K == 16) {
-                const int src = (lane & 48) | (r4 + 4 * v);
-                s0 = __shfl(rs0, src, kWave);
-                s1 = __shfl(rs1, src, kWave);
-            } else {
-                s0 = __shfl(accr0[v], (lane & 48) | 15, kWave);
-                s1 = __shfl(accr1[v], (lane & 48) | 15, kWave);
+                rs[mb] += __shfl_xor(rs[mb], 16, kWave);
+                rs[mb] += __shfl_xor(rs[mb], 32, kWave);
             }
-            const double z0 = s0 * (double)yi0[i0 * kp + qc] - accr0[v];
-            const double z1 = s1 * (double)yi0[i1 * kp + qc] - accr1[v];
-            if (qin) {
-                zrow[i0 * K + c16] = (float)z0;
-                zrow[i1 * K + c16] = (float)z1;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = 16 * mb + r4 + 4 * v;
+                double sm;
+                if constexpr (K == 16) sm = __shfl(rs[mb], (lane & 48) | (r4 + 4 * v), kWave);
+                else sm = __shfl(accr[mb][v], (lane & 48) | 15, kWave);
+                const double z = sm * (double)yrow[(int64_t)i * KP + qc] - accr[mb][v];
+                if (qin) zrow[c16 * 64 + i] = (float)z;
             }
         }
-        __builtin_amdgcn_wave_barrier();
-    }
+        p = row1;
+        ++bi;
+    } while (p < p1);
 }
 
-// z_p for the 64 points of point block b (one block per point block):
-// row-side partials of tiles (b, bj >= b), column-side partials of tiles
-// (bi <= b, b), then the short pairs through their CSR segments (pairs with
-// i = p add, pairs with j = p subtract).  The four wavefronts split the terms;
-// their sums are added in a fixed order.
+// z_p for the 64 points of point block b (one block of eight wavefronts per
+// point block): row-side partials of the items of row b, column-side partials
+// of tiles (bi <= b, b), then the short pairs through their CSR segments
+// (pairs with i = p add, pairs with j = p subtract).  The wavefronts split the
+// terms; their sums are added in a fixed order.
+constexpr int kZredWaves = 8;
 template <int K>
-__global__ __launch_bounds__(kPairBlock) void k_sm_zred(SmArgs a, int64_t nb, int64_t N,
-                                                        const int32_t *__restrict__ rp_i,
-                                                        const int32_t *__restrict__ rp_j,
-                                                        const int32_t *__restrict__ permj,
-                                                        double *__restrict__ Z) {
-    __shared__ double sz[kPairBlock / kWave][64 * K];
+__global__ __launch_bounds__(kZredWaves * kWave) void k_sm_zred(SmArgs a, int64_t nb, int64_t N,
+                                                                const int32_t *__restrict__ rp_i,
+                                                                const int32_t *__restrict__ rp_j,
+                                                                const int32_t *__restrict__ permj,
+                                                                double *__restrict__ Z) {
+    __shared__ double sz[kZredWaves][64 * K];
     const int lane = threadIdx.x & 63;
     const int wv = threadIdx.x >> 6;
     const int64_t b = blockIdx.x;
     double z[K];
 #pragma unroll
     for (int q = 0; q < K; ++q) z[q] = 0.0;
-    const int64_t trow0 = b * nb - b * (b - 1) / 2;   // first tile of row b
-    const int half = lane >> 5, rr = lane & 31;
-    // two tiles per step, all their loads issued before the adds
-    int64_t bj = b + wv;
-    for (; bj + 4 < nb; bj += 8) {
-        const float *z0 = a.Zr + (2 * (trow0 + bj - b) + half) * (int64_t)(K * 32) + rr * K;
-        const float *z1 = z0 + 8 * (int64_t)(K * 32);   // tile bj + 4 of the same row
-        float t0[K], t1[K];
+    // two partials per step, all their loads issued before the adds
+    auto add2 = [&](const float *z0, const float *z1) __attribute__((always_inline)) {
+        float u0[K], u1[K];
 #pragma unroll
-        for (int q = 0; q < K; ++q) { t0[q] = z0[q]; t1[q] = z1[q]; }
+        for (int q = 0; q < K; ++q) { u0[q] = z0[q * 64]; u1[q] = z1[q * 64]; }
 #pragma unroll
-        for (int q = 0; q < K; ++q) z[q] += (double)t0[q] + (double)t1[q];
-    }
-    for (; bj < nb; bj += 4) {
-        const float *zp = a.Zr + (2 * (trow0 + bj - b) + half) * (int64_t)(K * 32) + rr * K;
+        for (int q = 0; q < K; ++q) z[q] += (double)u0[q] + (double)u1[q];
+    };
+    auto add1 = [&](const float *z0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < K; ++q) z[q] += (double)zp[q];
-    }
+        for (int q = 0; q < K; ++q) z[q] += (double)z0[q * 64];
+    };
+    const int64_t len = K * 64;
+    // rows: the shares that touch row b
+    const int64_t trow = b * nb - b * (b - 1) / 2;
+    const int64_t i1 = share_of(a, 2 * (trow + nb - b) - 1) + b;
+    int64_t ix = share_of(a, 2 * trow) + b + wv;
+    for (; ix + kZredWaves <= i1; ix += 2 * kZredWaves)
+        add2(a.Zr + ix * len + lane, a.Zr + (ix + kZredWaves) * len + lane);
+    if (ix <= i1) add1(a.Zr + ix * len + lane);
+    // columns: the tiles (bi, b), then the second halves in shares of their own
+    auto col = [&](int64_t bi) { return a.Zc + (bi * nb - bi * (bi - 1) / 2 + (b - bi)) * len + lane; };
     int64_t bi = wv;
-    for (; bi + 4 <= b; bi += 8) {
-        const int64_t t0 = bi * nb - bi * (bi - 1) / 2 + (b - bi);
-        const int64_t bi1 = bi + 4;
-        const int64_t t1 = bi1 * nb - bi1 * (bi1 - 1) / 2 + (b - bi1);
-        const float *z0 = a.Zc + 2 * t0 * (int64_t)(K * 64) + lane * K;
-        const float *z1 = a.Zc + 2 * t1 * (int64_t)(K * 64) + lane * K;
-        float u0[K], u1[K], v0[K], v1[K];
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            u0[q] = z0[q]; v0[q] = z0[K * 64 + q];
-            u1[q] = z1[q]; v1[q] = z1[K * 64 + q];
-        }
-#pragma unroll
-        for (int q = 0; q < K; ++q) z[q] += ((double)u0[q] + (double)v0[q]) + ((double)u1[q] + (double)v1[q]);
+    for (; bi + kZredWaves <= b; bi += 2 * kZredWaves) add2(col(bi), col(bi + kZredWaves));
+    if (bi <= b) add1(col(bi));
+    for (int64_t b0 = wv; b0 <= b; b0 += kZredWaves * kWave) {   // (a lane per tile)
+        bi = b0 + kZredWaves * lane;
+        const int64_t x = 2 * (bi * nb - bi * (bi - 1) / 2 + (b - bi)) + 1;
+        const int w = bi <= b ? share_of(a, x) : 0;
+        for (uint64_t hit = __ballot(bi <= b && share_start(a, w) == x); hit; hit &= hit - 1)
+            add1(a.Zc + (a.ntiles + __shfl(w, __ffsll((unsigned long long)hit) - 1, kWave)) * len + lane);
     }
-    for (; bi <= b; bi += 4) {
-        const int64_t t = bi * nb - bi * (bi - 1) / 2 + (b - bi);
-        const float *zp = a.Zc + 2 * t * (int64_t)(K * 64) + lane * K;
+    // the tile weights were taken at L c2 rounded to FP32, the same for every
+    // pair: what the rounding took from their exponent is put back here (the
+    // short pairs' weights are FP64)
+    const double Lc = *a.Lp * (double)a.c2;
+    const double corr = exp2(Lc - (double)((float)(*a.Lp) * a.c2));
 #pragma unroll
-        for (int q = 0; q < K; ++q) z[q] += (double)zp[q] + (double)zp[K * 64 + q];
-    }
+    for (int q = 0; q < K; ++q) z[q] *= corr;
     const int64_t p = b * kTile + lane;
     if (a.nclose > 0 && p < N) {
-        for (int32_t e = rp_i[p] + wv; e < rp_i[p + 1]; e += 4) {
+        for (int32_t e = rp_i[p] + wv; e < rp_i[p + 1]; e += kZredWaves) {
 #pragma unroll
             for (int q = 0; q < K; ++q) z[q] += a.zpair[(int64_t)e * K + q];
         }
-        for (int32_t e = rp_j[p] + wv; e < rp_j[p + 1]; e += 4) {
+        for (int32_t e = rp_j[p] + wv; e < rp_j[p + 1]; e += kZredWaves) {
             const int64_t ee = permj[e];
 #pragma unroll
             for (int q = 0; q < K; ++q) z[q] -= a.zpair[ee * K + q];
@@ -465,11 +555,13 @@ __global__ __launch_bounds__(kPairBlock) void k_sm_zred(SmArgs a, int64_t nb, in
 #pragma unroll
     for (int q = 0; q < K; ++q) sz[wv][lane * K + q] = z[q];
     __syncthreads();
-    if (wv == 0 && p < N) {
+    for (int e = threadIdx.x; e < 64 * K; e += kZredWaves * kWave) {
+        if (b * kTile + e / K < N) {
+            double acc = 0.0;
 #pragma unroll
-        for (int q = 0; q < K; ++q)
-            Z[p * K + q] = ((sz[0][lane * K + q] + sz[1][lane * K + q]) + sz[2][lane * K + q]) +
-                           sz[3][lane * K + q];
+            for (int w = 0; w < kZredWaves; ++w) acc += sz[w][e];
+            Z[b * kTile * K + e] = acc;
+        }
     }
 }
 
