@@ -246,8 +246,9 @@ sap_status sap_softmin_fwd(sap_handle h, const float *P, double tau,
  * never stored.  Pairs with r_ij = 0 contribute nothing.  dP is n x k
  * row-major FP32, overwritten.  Deterministic.  P must hold, bit for bit,
  * the projection passed to that forward, and tau must be the forward's:
- * otherwise SAP_ERR_INVALID_ARG (P is compared with the forward's copy, so
- * this call synchronises the stream before enqueuing the backward). */
+ * otherwise SAP_ERR_INVALID_ARG and dP is left as it was (P is compared with
+ * the forward's copy on the device, and the call returns when the stream has
+ * come to the end of that comparison). */
 sap_status sap_softmin_bwd(sap_handle h, const float *P, double tau,
                            const float *grad_loss, float *dP);
 

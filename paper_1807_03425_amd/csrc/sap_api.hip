@@ -82,7 +82,21 @@ struct sap_ctx {
     double *d_mu = nullptr;
     DevState *d_st = nullptr;
     Partial *d_part = nullptr;   // pass-block results, then one per short-pair block
-    DevResult *d_res = nullptr;
+    // Pinned host memory for what the host reads back: the verdicts on P, the
+    // result of a synchronous evaluation, init's counts.  Kernels write the
+    // first three there themselves: a copy to pageable memory took 8 us of a
+    // 44 us step (N = 1037, k = 5), P and its check on the host 34 to 52 us
+    // of a set_P, two copies and the gap behind them 50 us of a soft-min
+    // backward.
+    struct HostBack {
+        DevResult res;
+        double ortho;       // max |P^T P - I|
+        int32_t finite_P;
+        int32_t same_P;     // the backward's P is the forward's
+        DevState st;
+    };
+    HostBack *back = nullptr, *back_dev = nullptr;   // one allocation: host and device address
+    hipEvent_t ev_same = nullptr;
     int pass_grid = 0, short_grid = 0;
     // fused FP64 Y GEMM split over two wavefronts per 16-row tile (k_prep and
     // k_selprep run n_pad / 32 blocks; see gemm_block_deep)
@@ -225,32 +239,30 @@ static sap_status validate(const sap_config *c, int64_t ldx, const void *X, cons
     return SAP_OK;
 }
 
-static sap_status check_P_host(sap_ctx *h, const std::vector<double> &P, int n, int k) {
-    for (double v : P)
-        if (!std::isfinite(v)) return fail(h, SAP_ERR_NONFINITE, "P holds NaN or Inf");
-    double e = 0.0;
-    for (int a = 0; a < k; ++a)
-        for (int b = 0; b < k; ++b) {
-            double acc = 0.0;
-            for (int l = 0; l < n; ++l) acc += P[(size_t)l * k + a] * P[(size_t)l * k + b];
-            e = std::max(e, std::fabs(acc - (a == b ? 1.0 : 0.0)));
-        }
-    if (e > 1e-6) return fail(h, SAP_ERR_NOT_ORTHONORMAL, "max |P^T P - I| = %.3g > 1e-6", e);
+static sap_status back_alloc(sap_ctx *h) {
+    void *p = nullptr, *d = nullptr;
+    SAP_HIP(h, hipHostMalloc(&p, sizeof(sap_ctx::HostBack), hipHostMallocMapped));
+    h->back = static_cast<sap_ctx::HostBack *>(p);
+    SAP_HIP(h, hipHostGetDevicePointer(&d, p, 0));
+    h->back_dev = static_cast<sap_ctx::HostBack *>(d);
     return SAP_OK;
 }
 
-// Load a device P (n x k row-major) into the FP64 master (k x n) after checks.
+static sap_status read_state(sap_ctx *h, DevState *st) {
+    SAP_HIP(h, hipMemcpyAsync(&h->back->st, h->d_st, sizeof *st, hipMemcpyDeviceToHost, h->stream));
+    SAP_HIP(h, hipStreamSynchronize(h->stream));
+    *st = h->back->st;
+    return SAP_OK;
+}
+
+// Load a device P (n x k row-major) into the FP64 master (k x n) if it passes
+// the checks.
 static sap_status load_P(sap_ctx *h, const double *P_dev) {
     const int n = h->n, k = h->k;
-    std::vector<double> P((size_t)n * k), Pt((size_t)n * k);
-    SAP_HIP(h, hipMemcpyAsync(P.data(), P_dev, sizeof(double) * n * k, hipMemcpyDeviceToHost, h->stream));
-    SAP_HIP(h, hipStreamSynchronize(h->stream));
-    SAP_TRY(check_P_host(h, P, n, k));
-    for (int l = 0; l < n; ++l)
-        for (int q = 0; q < k; ++q) Pt[(size_t)q * n + l] = P[(size_t)l * k + q];
-    SAP_HIP(h, hipMemcpyAsync(h->d_P64t, Pt.data(), sizeof(double) * n * k, hipMemcpyHostToDevice,
-                              h->stream));
-    if (h->cfg.form == SAP_PLAIN) {
+    hipLaunchKernelGGL(k_load_P, dim3(1), dim3(kLoadP), 0, h->stream, P_dev, n, k, kOrthoTol, h->d_P64t,
+                       &h->back_dev->ortho, &h->back_dev->finite_P);
+    SAP_LAUNCHED(h, "k_load_P");
+    if (h->cfg.form == SAP_PLAIN) {   // (of the old master if P is refused)
         const int blocks = (int)ceil_div((int64_t)n * k, 256);
         if (h->cfg.dtype == SAP_F64)
             hipLaunchKernelGGL(k_write_Pr<double>, dim3(blocks), dim3(256), 0, h->stream, h->d_P64t, n, k,
@@ -261,6 +273,9 @@ static sap_status load_P(sap_ctx *h, const double *P_dev) {
         SAP_LAUNCHED(h, "k_write_Pr");
     }
     SAP_HIP(h, hipStreamSynchronize(h->stream));
+    if (!h->back->finite_P) return fail(h, SAP_ERR_NONFINITE, "P holds NaN or Inf");
+    if (h->back->ortho > kOrthoTol)
+        return fail(h, SAP_ERR_NOT_ORTHONORMAL, "max |P^T P - I| = %.3g > 1e-6", h->back->ortho);
     return SAP_OK;
 }
 
@@ -290,8 +305,7 @@ static sap_status init_moments(sap_ctx *h) {
     if (h->cfg.dtype == SAP_F64) SAP_TRY(launch_moments<double>(h, part, nblk, rows));
     else SAP_TRY(launch_moments<float>(h, part, nblk, rows));
     DevState st;
-    SAP_HIP(h, hipMemcpyAsync(&st, h->d_st, sizeof st, hipMemcpyDeviceToHost, h->stream));
-    SAP_HIP(h, hipStreamSynchronize(h->stream));
+    SAP_TRY(read_state(h, &st));
     if (st.nonfinite) return fail(h, SAP_ERR_NONFINITE, "X holds NaN or Inf");
     double r;
     std::memcpy(&r, &st.radius_bits, sizeof r);
@@ -319,8 +333,7 @@ static sap_status init_plain(sap_ctx *h) {
                            static_cast<float *>(h->d_S), h->pcols, h->p, kept, drop);
     SAP_LAUNCHED(h, "k_build_secants");
     DevState st;
-    SAP_HIP(h, hipMemcpyAsync(&st, h->d_st, sizeof st, hipMemcpyDeviceToHost, h->stream));
-    SAP_HIP(h, hipStreamSynchronize(h->stream));
+    SAP_TRY(read_state(h, &st));
     h->kept = st.kept;
     h->dropped = st.dropped;
     // |c~ - c| <= (n+3) u sqrt(k) (rounded secants and P, FMA accumulation),
@@ -391,8 +404,7 @@ static sap_status init_fused(sap_ctx *h) {
     }
     SAP_LAUNCHED(h, "k_build_invd2");
     DevState st;
-    SAP_HIP(h, hipMemcpyAsync(&st, h->d_st, sizeof st, hipMemcpyDeviceToHost, h->stream));
-    SAP_HIP(h, hipStreamSynchronize(h->stream));
+    SAP_TRY(read_state(h, &st));
     h->kept = st.kept;
     h->dropped = st.dropped;
     if (h->kept == 0) return SAP_OK;  // caller reports SAP_ERR_NO_PAIRS
@@ -426,8 +438,7 @@ static sap_status init_fused(sap_ctx *h) {
         hipLaunchKernelGGL(k_mark_close, dim3(grid), dim3(256), 0, h->stream, h->d_invd2, h->d_tiles,
                            h->ntiles, thr, h->d_close, want, d_count, &h->d_st->keep_max);
         SAP_LAUNCHED(h, "k_mark_close");
-        SAP_HIP(h, hipMemcpyAsync(&st, h->d_st, sizeof st, hipMemcpyDeviceToHost, h->stream));
-        SAP_HIP(h, hipStreamSynchronize(h->stream));
+        SAP_TRY(read_state(h, &st));
         if (st.n_close != want)
             return fail(h, SAP_ERR_DEVICE, "short-pair count mismatch (%lld vs %lld)",
                         (long long)st.n_close, (long long)want);
@@ -587,7 +598,7 @@ static SweepArgs<TX> sweep_args(sap_ctx *h, double *tr_min, int64_t *tr_ij, int3
     a.N = h->N;
     a.P64t = h->d_P64t;
     a.gmin_out = &h->d_st->gmin;
-    a.res = h->d_res;
+    a.res = nullptr;
     a.tr_min = tr_min;
     a.tr_ij = tr_ij;
     a.tr_cert = tr_cert;
@@ -628,10 +639,11 @@ static sap_status launch_pass(sap_ctx *h) {
 
 template <typename TX>
 static sap_status launch_select(sap_ctx *h, int do_step, double *tr_min, int64_t *tr_ij, int32_t *tr_cert,
-                                int it) {
+                                int it, DevResult *res = nullptr) {
     const int K = h->k;
     const bool fused = h->cfg.form == SAP_FUSED;
-    const SweepArgs<TX> a = sweep_args<TX>(h, tr_min, tr_ij, tr_cert, it);
+    SweepArgs<TX> a = sweep_args<TX>(h, tr_min, tr_ij, tr_cert, it);
+    a.res = res;
     const int nshort = fused ? h->short_grid_it : 0;
     const int pr_kind = fused ? 0 : (h->cfg.dtype == SAP_F64 ? 2 : 1);
     const uint32_t lds = (uint32_t)h->tail_lds;
@@ -670,10 +682,10 @@ static sap_status launch_selprep(sap_ctx *h, double *tr_min, int64_t *tr_ij, int
 // One evaluation (+ update when do_step): GEMM (fused), pass, selection.
 template <typename TX>
 static sap_status launch_iteration(sap_ctx *h, int do_step, double *tr_min, int64_t *tr_ij,
-                                   int32_t *tr_cert, int it) {
+                                   int32_t *tr_cert, int it, DevResult *res = nullptr) {
     if (h->cfg.form == SAP_FUSED) SAP_TRY(launch_prep<TX>(h));
     SAP_TRY(launch_pass<TX>(h));
-    return launch_select<TX>(h, do_step, tr_min, tr_ij, tr_cert, it);
+    return launch_select<TX>(h, do_step, tr_min, tr_ij, tr_cert, it, res);
 }
 
 // iters updates and a final evaluation.  Fused form with a small GEMM grid:
@@ -700,16 +712,16 @@ static sap_status launch_run(sap_ctx *h, int32_t iters, double *tr_min, int64_t 
     return launch_select<TX>(h, 0, tr_min, tr_ij, tr_cert, iters);
 }
 
-static sap_status enqueue_eval(sap_ctx *h, int do_step, double *tr_min, int64_t *tr_ij,
-                               int32_t *tr_cert, int it) {
-    if (h->cfg.dtype == SAP_F64) return launch_iteration<double>(h, do_step, tr_min, tr_ij, tr_cert, it);
-    return launch_iteration<float>(h, do_step, tr_min, tr_ij, tr_cert, it);
+// One evaluation (+ update when do_step), its result to host memory if wanted.
+static sap_status enqueue_eval(sap_ctx *h, int do_step, bool result) {
+    DevResult *res = result ? &h->back_dev->res : nullptr;
+    if (h->cfg.dtype == SAP_F64) return launch_iteration<double>(h, do_step, nullptr, nullptr, nullptr, 0, res);
+    return launch_iteration<float>(h, do_step, nullptr, nullptr, nullptr, 0, res);
 }
 
 static sap_status read_result(sap_ctx *h, sap_min_result *out) {
-    DevResult r;
-    SAP_HIP(h, hipMemcpyAsync(&r, h->d_res, sizeof r, hipMemcpyDeviceToHost, h->stream));
     SAP_HIP(h, hipStreamSynchronize(h->stream));
+    const DevResult r = h->back->res;
     out->min_norm = r.min_norm;
     out->runner_up = r.runner_up;
     out->i = r.i;
@@ -738,6 +750,8 @@ static void destroy_ctx(sap_ctx *h) {
     for (auto &m : h->marks) { (void)hipEventDestroy(m.a); (void)hipEventDestroy(m.b); }
     for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
     for (void *p : h->allocs) (void)hipFree(p);
+    if (h->ev_same) (void)hipEventDestroy(h->ev_same);
+    if (h->back) (void)hipHostFree(h->back);
     delete h;
 }
 
@@ -817,7 +831,7 @@ static sap_status sm_forward(sap_ctx *h, const float *P, double tau, float *loss
     const dim3 blk(kPairBlock);
     const TX *X = static_cast<const TX *>(h->X);
     SAP_TRY(launch(h, 5, "k_sm_loadP", k_sm_loadP, dim3((unsigned)ceil_div((int64_t)h->n * K, 256)),
-                   dim3(256), 0, P, h->n, K, h->d_smP64t));
+                   dim3(256), 0, P, h->n, K, h->d_smP64t, h->d_smP32));
     SAP_DISPATCH_K(K, SAP_TRY(launch_with(h, 5, "k_sm_prep", dim3((unsigned)(gemm_blocks + nshort)), blk, 0,
                                           [&](const LaunchCfg &c) {
         return KLaunch<K, TX>::sm_prep(c, a, X, h->ldx, h->N, h->d_mu, h->d_smY, h->Npad, gemm_blocks, 0);
@@ -851,7 +865,7 @@ static sap_status sm_backward(sap_ctx *h, double tau, const float *grad_loss, fl
                    X, h->ldx, h->N, h->n, K, (const double *)h->d_mu, (const double *)h->d_smZ,
                    h->sm_rows, h->d_smG));
     SAP_TRY(launch(h, 5, "k_sm_dP", k_sm_dP, dim3((unsigned)ceil_div((int64_t)h->n * K, 64)), dim3(256), 0,
-                   (const double *)h->d_smG, h->sm_chunks, h->n, K, grad_loss, dP));
+                   (const double *)h->d_smG, h->sm_chunks, h->n, K, grad_loss, dP, (const DevState *)h->d_st));
     return SAP_OK;
 }
 
@@ -1086,10 +1100,10 @@ sap_status sap_init(const sap_config *cfg, const void *X, int64_t ldx, const dou
     hipError_t e = hipGetDevice(&h->device);
     if (e != hipSuccess) return bail(fail(h, SAP_ERR_DEVICE, "hipGetDevice: %s", hipGetErrorString(e)));
     sap_status s;
+    if ((s = back_alloc(h)) != SAP_OK) return bail(s);
     if ((s = dalloc(h, &h->d_P64t, sizeof(double) * h->n * h->k)) != SAP_OK) return bail(s);
     if ((s = dalloc(h, &h->d_mu, sizeof(double) * h->n)) != SAP_OK) return bail(s);
     if ((s = dalloc(h, &h->d_st, sizeof(DevState))) != SAP_OK) return bail(s);
-    if ((s = dalloc(h, &h->d_res, sizeof(DevResult))) != SAP_OK) return bail(s);
     if ((s = init_moments(h)) != SAP_OK) return bail(s);
     if ((s = (cfg->form == SAP_PLAIN ? init_plain(h) : init_fused(h))) != SAP_OK) return bail(s);
     if (h->kept == 0) return bail(fail(h, SAP_ERR_NO_PAIRS, "every pair is a duplicate or shorter than min_len"));
@@ -1115,13 +1129,13 @@ sap_status sap_init(const sap_config *cfg, const void *X, int64_t ldx, const dou
 sap_status sap_min_secant(sap_handle h, sap_min_result *out) {
     SAP_TRY(usable(h));
     if (!out) return fail(h, SAP_ERR_INVALID_ARG, "null result pointer");
-    SAP_TRY(enqueue_eval(h, 0, nullptr, nullptr, nullptr, 0));
+    SAP_TRY(enqueue_eval(h, 0, true));
     return read_result(h, out);
 }
 
 sap_status sap_step(sap_handle h, sap_min_result *out) {
     SAP_TRY(usable(h));
-    SAP_TRY(enqueue_eval(h, 1, nullptr, nullptr, nullptr, 0));
+    SAP_TRY(enqueue_eval(h, 1, out != nullptr));
     if (out) return read_result(h, out);
     return SAP_OK;
 }
@@ -1188,7 +1202,6 @@ sap_status sap_softmin_fwd(sap_handle h, const float *P, double tau, float *loss
     if (!loss) return fail(h, SAP_ERR_INVALID_ARG, "null loss pointer");
     SAP_TRY(sm_alloc(h));
     h->sm_ready = false;
-    SAP_HIP(h, hipMemcpyAsync(h->d_smP32, P, sizeof(float) * h->n * h->k, hipMemcpyDeviceToDevice, h->stream));
     if (h->cfg.dtype == SAP_F64) SAP_TRY(sm_forward<double>(h, P, tau, loss));
     else SAP_TRY(sm_forward<float>(h, P, tau, loss));
     h->sm_ready = true;
@@ -1203,20 +1216,24 @@ sap_status sap_softmin_bwd(sap_handle h, const float *P, double tau, const float
     if (!grad_loss || !dP) return fail(h, SAP_ERR_INVALID_ARG, "null grad_loss or dP");
     if (!h->sm_ready || tau != h->sm_tau)
         return fail(h, SAP_ERR_INVALID_ARG, "sap_softmin_bwd must follow sap_softmin_fwd with the same tau");
-    {
-        // the gradient is that of the forward's P: P must be that projection
-        // (compared bit for bit with the forward's copy)
-        const size_t nk = (size_t)h->n * h->k;
-        std::vector<float> a(nk), b(nk);
-        SAP_HIP(h, hipMemcpyAsync(a.data(), P, sizeof(float) * nk, hipMemcpyDeviceToHost, h->stream));
-        SAP_HIP(h, hipMemcpyAsync(b.data(), h->d_smP32, sizeof(float) * nk, hipMemcpyDeviceToHost, h->stream));
+    // the gradient is that of the forward's P: P must be that projection
+    // (compared bit for bit with the forward's copy).  The comparison is a
+    // kernel and the backward is enqueued behind it, so that the device works
+    // while the host waits for the verdict; where P differs, k_sm_dP writes
+    // nothing and the call ends with nothing pending.
+    if (!h->ev_same) SAP_HIP(h, hipEventCreateWithFlags(&h->ev_same, hipEventDisableTiming));
+    SAP_TRY(launch(h, 5, "k_sm_same", k_sm_same, dim3(1), dim3(kSameBlock), 0, P, (const float *)h->d_smP32,
+                   h->n * h->k, h->d_st, &h->back_dev->same_P));
+    SAP_HIP(h, hipEventRecord(h->ev_same, h->stream));
+    if (h->cfg.dtype == SAP_F64) SAP_TRY(sm_backward<double>(h, tau, grad_loss, dP));
+    else SAP_TRY(sm_backward<float>(h, tau, grad_loss, dP));
+    SAP_HIP(h, hipEventSynchronize(h->ev_same));
+    if (!h->back->same_P) {
         SAP_HIP(h, hipStreamSynchronize(h->stream));
-        if (std::memcmp(a.data(), b.data(), sizeof(float) * nk) != 0)
-            return fail(h, SAP_ERR_INVALID_ARG,
-                        "sap_softmin_bwd: P differs from the P of the latest sap_softmin_fwd");
+        return fail(h, SAP_ERR_INVALID_ARG,
+                    "sap_softmin_bwd: P differs from the P of the latest sap_softmin_fwd");
     }
-    if (h->cfg.dtype == SAP_F64) return sm_backward<double>(h, tau, grad_loss, dP);
-    return sm_backward<float>(h, tau, grad_loss, dP);
+    return SAP_OK;
 }
 
 sap_status sap_profile_enable(sap_handle h, int32_t on) {

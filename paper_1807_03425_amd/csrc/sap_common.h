@@ -70,7 +70,7 @@ struct DevState {
     // soft-min
     double sm_m, sm_s;   // running (reference, scaled sum)
     double sm_L;         // loss of the last forward
-    int64_t sm_nzero;
+    int32_t sm_same, pad3;   // the backward's P is the forward's
 };
 
 __device__ __forceinline__ int64_t pair_index(int64_t N, int64_t i, int64_t j) {

@@ -1801,19 +1801,20 @@ __device__ int2 select_min(const SweepArgs<TX> &a, int nparts, bool record, Part
             r_lo = (t - a.e_abs) / (1.0 + a.e_rel) * (1.0 - 1e-9);
         }
         const double ru = fmin(f.r2, r_lo);
-        DevResult *res = a.res;
-        res->min_norm = f.r;
-        res->runner_up = ru;
-        res->runner_up_exact = (cert && f.r2 <= r_lo) ? 1 : 0;
-        res->i = found ? f.i : -1;
-        res->j = found ? f.j : -1;
-        res->q = found ? pair_index(a.N, f.i, f.j) : -1;
-        res->coarse_min = coarse;
-        res->window = coarse >= 0.0 ? tr - coarse : 0.0;
-        res->certified = cert;
-        res->n_rescored = f.n_rescored;
-        res->n_tiles = f.n_units;
-        res->t = -1;
+        if (DevResult *res = a.res) {
+            res->min_norm = f.r;
+            res->runner_up = ru;
+            res->runner_up_exact = (cert && f.r2 <= r_lo) ? 1 : 0;
+            res->i = found ? f.i : -1;
+            res->j = found ? f.j : -1;
+            res->q = found ? pair_index(a.N, f.i, f.j) : -1;
+            res->coarse_min = coarse;
+            res->window = coarse >= 0.0 ? tr - coarse : 0.0;
+            res->certified = cert;
+            res->n_rescored = f.n_rescored;
+            res->n_tiles = f.n_units;
+            res->t = -1;
+        }
         if (a.tr_min) a.tr_min[a.it] = f.r;
         if (a.tr_ij) {
             a.tr_ij[2 * a.it] = found ? f.i : -1;

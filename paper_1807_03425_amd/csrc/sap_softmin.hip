@@ -16,12 +16,13 @@
 // vectors, as in the iteration.
 //
 // Launch sequence
-//   forward:  k_sm_loadP   P (FP32, n x k) -> FP64 k x n
+//   forward:  k_sm_loadP   P (FP32, n x k) -> FP64 k x n, and a copy
 //             k_sm_prep    Y = (X - mu) P (FP64 MFMA, rounded to FP32) and the
 //                          FP64 (min, sum) partials of the short pairs
 //             k_sm_fwd     per-block (min, scaled sum) over the tiles
 //             k_sm_fin     one block: merge in FP64, L, loss
-//   backward: k_sm_prep    (short-pair blocks only) a_ij (y_i - y_j) per short pair
+//   backward: k_sm_same    P against the forward's
+//             k_sm_prep    (short-pair blocks only) a_ij (y_i - y_j) per short pair
 //             k_sm_bwd     partial z sums of rows (per share: half-tiles of a
 //                          row of tiles) and columns (per tile) -- weights and
 //                          column side on VALU, row-side contraction on FP64 MFMA
@@ -96,12 +97,31 @@ __device__ void block_lse(double m, double s, double tau, SmPart *out) {
 }
 
 #ifndef SAP_KINST
-// P (n x k row-major FP32) -> k x n FP64.
-__global__ void k_sm_loadP(const float *__restrict__ P, int n, int k, double *__restrict__ P64t) {
+// P (n x k row-major FP32) -> k x n FP64, and the copy that the backward's P
+// is compared with.
+__global__ void k_sm_loadP(const float *__restrict__ P, int n, int k, double *__restrict__ P64t,
+                           float *__restrict__ P32) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n * k) return;
     const int l = e / k, q = e % k;
-    P64t[(int64_t)q * n + l] = (double)P[e];
+    const float v = P[e];
+    P64t[(int64_t)q * n + l] = (double)v;
+    P32[e] = v;
+}
+
+// Whether P is, bit for bit, the forward's P: for k_sm_dP and for the host
+// (pinned memory).
+constexpr int kSameBlock = 1024;
+__global__ __launch_bounds__(kSameBlock) void k_sm_same(const float *__restrict__ P, const float *__restrict__ P32,
+                                                        int nk, DevState *__restrict__ st,
+                                                        int32_t *__restrict__ host) {
+    int diff = 0;
+    for (int e = threadIdx.x; e < nk; e += kSameBlock) diff |= __float_as_int(P[e]) != __float_as_int(P32[e]);
+    diff = __syncthreads_or(diff);
+    if (threadIdx.x == 0) {
+        st->sm_same = !diff;
+        *host = !diff;
+    }
 }
 
 #endif
@@ -328,12 +348,12 @@ __device__ __forceinline__ int share_of(const SmArgs &a, int64_t p) {
 // Partials, component-major in FP32: Zr once per row, Zc once per tile, and
 // once more for a tile whose halves fall in two shares.  Per half-tile and
 // point-major they were 377 MB written and read again at N = 20000, k = 10
-// (k_sm_zred 90 us; 25 now).
+// (k_sm_zred 90 us, 32 now, traced).
 // Bound by issue: 4K + 16 VALU slots per pair (rsq and exp2 as 4) and the FP64
 // products, which other wavefronts' VALU work covers in part: N = 20000, k = 10
 // 383 us (407 with a block per half-tile and the rows through LDS), N = 14000,
-// k = 16 250 (296), N = 9000, k = 10 85 (79; runs and their merge together 140
-// and 155).
+// k = 16 250 (296), N = 9000, k = 10 85 (79: the merge gained what this
+// lost, 6 us).
 // LDS per block: 37 KB (K <= 4) to 49 KB (K >= 13): three blocks per compute
 // unit, two for K >= 13 (at three they would spill).
 template <int K>
@@ -625,7 +645,8 @@ __global__ __launch_bounds__(256) void k_sm_grad(const TX *__restrict__ X, int64
 // eight loads in flight per lane, and their sums are added in a fixed order.
 __global__ __launch_bounds__(256) void k_sm_dP(const double *__restrict__ Gpart, int nchunks, int n,
                                                int K, const float *__restrict__ grad_loss,
-                                               float *__restrict__ dP) {
+                                               float *__restrict__ dP, const DevState *__restrict__ st) {
+    if (!st->sm_same) return;
     __shared__ double sp[4][64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int e = blockIdx.x * 64 + lane;

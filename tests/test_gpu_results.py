@@ -1,0 +1,108 @@
+"""What the library reads back from the device: the result of a synchronous
+evaluation, the checks of a P, and the soft-min backward's refusal of a P that is not the
+forward's, with dP untouched."""
+import numpy as np
+import pytest
+
+import sap_inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import ctypes as C  # noqa: E402
+
+from paper_1807_03425_amd import SapContext, SapError, lib  # noqa: E402
+
+DEV = torch.device("cuda:0")
+
+
+def _handle(form="fused"):
+    w = sap_inputs.make("trig64", N=130, k=5)
+    X = torch.from_numpy(w.X).to(DEV)
+    return SapContext(X, torch.from_numpy(w.P0), form=form), torch.from_numpy(w.P0).to(DEV)
+
+
+@pytest.mark.parametrize("form", ["fused", "plain"])
+def test_results_interleaved(form):
+    """step and min_secant between steps without a result and runs: each
+    result is that of its own evaluation, equal to the run's trace."""
+    a, P0 = _handle(form)
+    b, _ = _handle(form)
+    tr = b.run(6)
+    mins, ij = tr["min"].cpu().numpy(), tr["ij"].cpu().numpy()
+    assert a.min_secant()["min_norm"] == mins[0]
+    r = a.step()
+    assert r["min_norm"] == mins[0] and [r["i"], r["j"]] == list(ij[0]) and r["t"] >= 0
+    a.step(sync=False)
+    a.run(1)
+    r = a.step()
+    assert r["min_norm"] == mins[3] and [r["i"], r["j"]] == list(ij[3])
+    assert a.min_secant()["min_norm"] == mins[4]
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("bit", [0, 31])
+@pytest.mark.parametrize("where", [0, 319, -1])
+def test_softmin_refused_P_leaves_dP(where, bit):
+    """One flipped bit of P (the sign of a zero included) is refused and
+    writes nothing; the backward of the forward's P still works after it."""
+    h, P0 = _handle()
+    P = P0.float().contiguous()
+    P.view(-1)[where] = 0.0
+    h.softmin_fwd(P, 0.05)
+    one = torch.ones(1, device=DEV)
+    want = h.softmin_bwd(P, 0.05, one)
+    Q = P.clone()
+    Q.view(torch.int32).view(-1)[where] ^= (1 << bit) if bit < 31 else -(1 << 31)
+    assert not torch.equal(Q.view(torch.int32), P.view(torch.int32))
+    dP = torch.full_like(P, 7.0)
+    call = lambda p: lib().sap_softmin_bwd(h.handle, C.c_void_p(p.data_ptr()), 0.05, C.c_void_p(one.data_ptr()),
+                                           C.c_void_p(dP.data_ptr()))
+    assert call(Q) != 0
+    assert bool((dP == 7.0).all())
+    torch.cuda.synchronize()
+    assert bool((dP == 7.0).all())
+    assert call(P) == 0
+    torch.cuda.synchronize()
+    assert np.array_equal(dP.cpu().numpy(), want.cpu().numpy())
+    h.close()
+
+
+@pytest.mark.parametrize("form", ["fused", "plain"])
+@pytest.mark.parametrize("n,k", [(3, 1), (255, 7), (256, 16), (257, 5), (600, 16)])
+def test_set_P_checks(n, k, form):
+    """Rows around the chunks of 256: a P is taken bit for bit, up to
+    |P^T P - I| = 1e-6 in any entry, and a refused one changes nothing."""
+    g = np.random.default_rng(n + k)
+    X = torch.from_numpy(g.standard_normal((40, n))).to(DEV)
+    P0 = np.linalg.qr(g.standard_normal((n, k)))[0]
+    h = SapContext(X, torch.from_numpy(P0), form=form)
+    P1 = np.linalg.qr(g.standard_normal((n, k)))[0]
+    P1[:, -1] *= 1.0 + 0.49e-6                 # squared length within 0.98e-6 of 1
+    h.set_P(torch.from_numpy(P1).to(DEV))
+    assert np.array_equal(h.get_P().cpu().numpy(), P1)
+    ref = h.min_secant()["min_norm"]
+    for l in (0, n // 2, n - 1):
+        for bad in (np.nan, np.inf, -np.inf):
+            Q = P1.copy()
+            Q[l, k // 2] = bad
+            with pytest.raises(SapError, match="NONFINITE"):
+                h.set_P(torch.from_numpy(Q).to(DEV))
+    Q = P1.copy()
+    Q[:, 0] *= 1.0 + (0.51e-6 if k > 1 else 1e-7)
+    if k > 1:
+        Q2 = P1.copy()
+        Q2[:, 0] += 1.1e-6 * Q2[:, k - 1]      # one product off the diagonal
+        refused = [Q, Q2, 1e200 * P1]
+    else:
+        refused = [1e200 * P1, 0.0 * P1]
+    for R in refused:
+        with pytest.raises(SapError, match="NOT_ORTHONORMAL"):
+            h.set_P(torch.from_numpy(R).to(DEV))
+    assert np.array_equal(h.get_P().cpu().numpy(), P1)
+    assert h.min_secant()["min_norm"] == ref
+    h.close()
