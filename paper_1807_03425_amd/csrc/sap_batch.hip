@@ -200,27 +200,31 @@ __global__ __launch_bounds__(256, 4) void k_batch_invd2(BatchArgs a, int64_t nti
         __syncthreads();
         double d2[4][4];
         tile_dist2(X, a.ldx, a.n, L, d2);
-        const int i0 = tb.x * kTile + 4 * ty, j0 = tb.y * kTile + 4 * tx;
+        const int i0 = tb.x * kTile + 4 * ty, j0 = tb.y * kTile;
         unsigned mx = 0u, nkept = 0u, ndrop = 0u;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int j = j0 + q;
+            const int j = j0 + tile_col(tx, q);
             float out[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
+                const int i = i0 + r;
+                const double s = d2[r][q];
                 float v = kMaskDropped;
-                if (j < st.M && i0 + r < j) {
-                    if (d2[r][q] == 0.0 || (ml > 0.0 && sqrt(d2[r][q]) < ml)) {
+                if (j < st.M && i < j) {
+                    if (s == 0.0 || (ml > 0.0 && tile_shorter(X + (int64_t)L.row[i - tb.x * kTile] * a.ldx,
+                                                              X + (int64_t)L.row[kTile + j - tb.y * kTile] * a.ldx,
+                                                              a.n, s, ml))) {
                         ++ndrop;
                     } else {
-                        v = (float)(1.0 / d2[r][q]);
+                        v = (float)(1.0 / s);
                         ++nkept;
                         mx = max(mx, __float_as_uint(v));
                     }
                 }
                 out[r] = v;
             }
-            a.w[t * (kTileElems / 4) + ty * 64 + 4 * tx + q] = make_float4(out[0], out[1], out[2], out[3]);
+            a.w[t * (kTileElems / 4) + ty * 64 + tile_col(tx, q)] = make_float4(out[0], out[1], out[2], out[3]);
         }
         atomicAdd(&s_kept, nkept);
         atomicAdd(&s_drop, ndrop);

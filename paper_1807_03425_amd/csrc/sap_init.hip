@@ -158,8 +158,8 @@ template __global__ void k_build_secants<double>(const void *, int, int64_t, int
 // decides membership of the close list, so the counts are exact.
 //
 // One block per tile (grid-stride), distances from tile_dist2; a thread's
-// 4 x 4 pairs are four consecutive float4 of the tile.  Kept and dropped
-// pairs are counted per thread and reduced once per block.
+// 4 x 4 pairs are twice two consecutive float4 of the tile.  Kept and
+// dropped pairs are counted per thread and reduced once per block.
 template <typename TX>
 __global__ __launch_bounds__(256, 4) void k_build_invd2(const TX *__restrict__ X, int64_t ldx, int64_t N, int n,
                                                         const int2 *__restrict__ tiles, int64_t ntiles,
@@ -173,6 +173,7 @@ __global__ __launch_bounds__(256, 4) void k_build_invd2(const TX *__restrict__ X
     if (threadIdx.x < 64) { s_hist[threadIdx.x] = 0; s_ladder[threadIdx.x] = ladder[threadIdx.x]; }
     if (threadIdx.x == 0) { s_kept = 0; s_drop = 0; }
     const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
+    const float lad0 = ladder[0];
     unsigned long long nkept = 0, ndrop = 0;
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int2 b = tiles[t];
@@ -184,35 +185,43 @@ __global__ __launch_bounds__(256, 4) void k_build_invd2(const TX *__restrict__ X
         __syncthreads();
         double d2[4][4];
         tile_dist2(X, ldx, n, L, d2);
-        const int64_t i0 = (int64_t)b.x * kTile + 4 * ty, j0 = (int64_t)b.y * kTile + 4 * tx;
+        // FULL: a tile of kept and dropped pairs only (off the diagonal, no
+        // points past the end), and nothing asked of a length
+        auto finish = [&](auto full) __attribute__((always_inline)) {
+            constexpr bool FULL = decltype(full)::value;
+            const int i0 = b.x * kTile + 4 * ty, j0 = b.y * kTile;
+            int drop = 0, kept = 0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int64_t j = j0 + q;
-            float out[4];
+            for (int q = 0; q < 4; ++q) {
+                const int j = j0 + tile_col(tx, q);
+                float out[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                float v = kMaskDropped;
-                if (j < N && i0 + r < j) {
-                    // (the root only where a length is asked for: d = 0 is d^2 = 0)
-                    if (d2[r][q] == 0.0 || (min_len > 0.0 && sqrt(d2[r][q]) < min_len)) {
-                        ++ndrop;
-                    } else {
-                        v = (float)(1.0 / d2[r][q]);
-                        ++nkept;
-                        if (v > s_ladder[0]) {
-                            int lo = 0;  // largest m with ladder[m] < v
-                            for (int hi = 63; lo < hi;) {
-                                int mid = (lo + hi + 1) >> 1;
-                                if (s_ladder[mid] < v) lo = mid; else hi = mid - 1;
-                            }
-                            atomicAdd(&s_hist[lo], 1ull);
+                for (int r = 0; r < 4; ++r) {
+                    const int i = i0 + r;
+                    const double s = d2[r][q];
+                    const bool pair = FULL || (j < N && i < j);
+                    const bool keep = pair && s != 0.0 &&
+                                      (FULL || !(min_len > 0.0 && tile_shorter(X + i * ldx, X + j * ldx, n, s, min_len)));
+                    const float v = keep ? (float)(1.0 / s) : kMaskDropped;
+                    drop += pair && !keep;
+                    if constexpr (!FULL) kept += keep;
+                    if (v > lad0) {
+                        int lo = 0;  // largest m with ladder[m] < v
+                        for (int hi = 63; lo < hi;) {
+                            int mid = (lo + hi + 1) >> 1;
+                            if (s_ladder[mid] < v) lo = mid; else hi = mid - 1;
                         }
+                        atomicAdd(&s_hist[lo], 1ull);
                     }
+                    out[r] = v;
                 }
-                out[r] = v;
+                invd2[t * (kTileElems / 4) + ty * 64 + tile_col(tx, q)] = make_float4(out[0], out[1], out[2], out[3]);
             }
-            invd2[t * (kTileElems / 4) + ty * 64 + 4 * tx + q] = make_float4(out[0], out[1], out[2], out[3]);
-        }
+            ndrop += drop;
+            nkept += FULL ? 16 - drop : kept;
+        };
+        if (b.x < b.y && ((int64_t)b.y + 1) * kTile <= N && !(min_len > 0.0)) finish(std::true_type{});
+        else finish(std::false_type{});
     }
     atomicAdd(&s_kept, nkept);
     atomicAdd(&s_drop, ndrop);

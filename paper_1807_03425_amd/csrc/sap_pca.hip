@@ -42,19 +42,21 @@ __global__ __launch_bounds__(256, 4) void k_pca_w(const TX *__restrict__ X, int6
         __syncthreads();
         double d2[4][4];
         tile_dist2(X, ldx, n, L, d2);
-        const int64_t i0 = (int64_t)b.x * kTile + 4 * ty, j0 = (int64_t)b.y * kTile + 4 * tx;
+        const int64_t i0 = (int64_t)b.x * kTile + 4 * ty, j0 = (int64_t)b.y * kTile;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             double v[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const double s = d2[r][q];
-                const bool kept = j0 + q < N && i0 + r < j0 + q && s != 0.0 && !(min_len > 0.0 && sqrt(s) < min_len);
+                const int64_t ii = i0 + r, jj = j0 + tile_col(tx, q);
+                const bool kept = jj < N && ii < jj && s != 0.0 &&
+                                  !(min_len > 0.0 && tile_shorter(X + ii * ldx, X + jj * ldx, n, s, min_len));
                 v[q] = kept ? 1.0 / s : 0.0;
             }
-            double2 *o = reinterpret_cast<double2 *>(W + t * kTileElems + (4 * ty + r) * kTile + 4 * tx);
+            double2 *o = reinterpret_cast<double2 *>(W + t * kTileElems + (4 * ty + r) * kTile + 2 * tx);
             o[0] = make_double2(v[0], v[1]);
-            o[1] = make_double2(v[2], v[3]);
+            o[16] = make_double2(v[2], v[3]);
         }
     }
 }
