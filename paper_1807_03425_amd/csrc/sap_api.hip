@@ -927,21 +927,41 @@ static double *pca_filter(sap_ctx *h, const double *Cs, double *V, const double 
         out = t0;
     } else {
         const double e = 0.5 * theta[b - 1], c = e;   // half width and centre of [0, theta_b]
-        double sg = e / (theta[0] - c);
-        const double tau = 2.0 / sg;
-        const int ne = kPcaMaxB * ld;
-        hipLaunchKernelGGL(k_pca_lin, dim3((unsigned)ceil_div(ne, 256)), blk, 0, h->stream, W, (const double *)V,
-                           sg / e, -c * sg / e, ne, t0);
-        double *x = V, *y = t0, *z = t1;   // the last two terms and the next
-        for (int d = 2; d <= deg; ++d) {
+        const double s1 = e / (theta[0] - c), tau = 2.0 / s1;
+        PcaCoef co;
+        double sg = s1;
+        for (int d = 1; d < deg; ++d) {
             const double sn = 1.0 / (tau - sg);
-            hipLaunchKernelGGL(k_pca_mv<BT>, gmv, blk, 0, h->stream, Cs, ld, (const double *)y, (const double *)x,
-                               2.0 * sn / e, -2.0 * c * sn / e, -sg * sn, z);
-            double *const spent = x;
-            x = y;
-            y = z;
-            z = spent;
+            co.a[d] = 2.0 * sn / e;
+            co.b[d] = -2.0 * c * sn / e;
+            co.g[d] = -sg * sn;
             sg = sn;
+        }
+        double *x = V, *y = t0, *z = t1;   // the last two terms and the next
+        if (ld == 64 || (BT == 1 && ld == 128)) {
+            // the whole filter in one block while its step (LD / 4 products of
+            // each of LD / 16 BT wavefronts on four SIMDs) takes less than a
+            // launch: the whole start, 1000 points, n = 64 638 us with
+            // launches and 557 with this at k = 6, 957 and 892 at k = 12 (b =
+            // 24); n = 128, k = 8 772 and 696
+            if (ld == 64)
+                hipLaunchKernelGGL((k_pca_cheb<BT, 64>), dim3(1), dim3(4 * BT * kWave), 0, h->stream, Cs,
+                                   (const double *)V, W, s1 / e, -c * s1 / e, deg, co, t0);
+            else if constexpr (BT == 1)
+                hipLaunchKernelGGL((k_pca_cheb<1, 128>), dim3(1), dim3(8 * kWave), 0, h->stream, Cs,
+                                   (const double *)V, W, s1 / e, -c * s1 / e, deg, co, t0);
+        } else {
+            const int ne = kPcaMaxB * ld;
+            hipLaunchKernelGGL(k_pca_lin, dim3((unsigned)ceil_div(ne, 256)), blk, 0, h->stream, W, (const double *)V,
+                               s1 / e, -c * s1 / e, ne, t0);
+            for (int d = 1; d < deg; ++d) {
+                hipLaunchKernelGGL(k_pca_mv<BT>, gmv, blk, 0, h->stream, Cs, ld, (const double *)y, (const double *)x,
+                                   co.a[d], co.b[d], co.g[d], z);
+                double *const spent = x;
+                x = y;
+                y = z;
+                z = spent;
+            }
         }
         out = y;
     }
@@ -1006,13 +1026,10 @@ static sap_status pca_run(sap_ctx *h, double *P_out, sap_pca_info *info, bool se
     hipLaunchKernelGGL(k_pca_sym, dim3((unsigned)ceil_div((int64_t)ld * ld, 256)), dim3(256), 0, h->stream,
                        (const double *)Cp, R, n, ld, Cs);
     SAP_LAUNCHED(h, "k_pca_sym");
-    // the iteration's four blocks of vectors start as zeros (their padding
+    // the start block in V[0], zeros in the rest of the four (their padding
     // stays so); V[0], V[1] hold the Ritz vectors and C times them
-    for (int q = 1; q < 4; ++q)
-        hipLaunchKernelGGL(k_pca_start, dim3((unsigned)ceil_div(kPcaMaxB * ld, 256)), dim3(256), 0, h->stream, V[q], n,
-                           0, ld);
-    hipLaunchKernelGGL(k_pca_start, dim3((unsigned)ceil_div(kPcaMaxB * ld, 256)), dim3(256), 0, h->stream, V[0], n, b,
-                       ld);
+    const int ne = 4 * kPcaMaxB * ld;
+    hipLaunchKernelGGL(k_pca_start, dim3((unsigned)ceil_div(ne, 256)), dim3(256), 0, h->stream, V[0], n, b, ld, ne);
     const dim3 gmv((unsigned)(ld / 16));
     double hout[kPcaMaxB + 1] = {0};
     int it = 0;

@@ -218,12 +218,19 @@ __global__ __launch_bounds__(256) void k_pca_sym(const double *__restrict__ Cp, 
     if (e >= (int64_t)ld * ld) return;
     const int a = (int)(e / ld), b = (int)(e % ld);
     double s1 = 0.0, s2 = 0.0;
-    if (a < n && b < n)
-        for (int r = 0; r < R; ++r) {
-            const double *C = Cp + (int64_t)r * n * n;
-            s1 += C[(int64_t)a * n + b];
-            s2 += C[(int64_t)b * n + a];
+    if (a < n && b < n) {
+        const double *c1 = Cp + (int64_t)a * n + b, *c2 = Cp + (int64_t)b * n + a;
+        const int64_t nn = (int64_t)n * n;
+        int r = 0;
+        for (; r + 8 <= R; r += 8) {   // (sixteen loads in flight; the sums in order)
+            double u[8], v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) { u[q] = c1[(r + q) * nn]; v[q] = c2[(r + q) * nn]; }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) { s1 += u[q]; s2 += v[q]; }
         }
+        for (; r < R; ++r) { s1 += c1[r * nn]; s2 += c2[r * nn]; }
+    }
     Cs[e] = 0.5 * (s1 + s2);
 }
 
@@ -242,9 +249,9 @@ __device__ __forceinline__ double pca_hash(uint64_t x) {
     return (double)(x >> 11) * (2.0 / 9007199254740992.0) - 1.0;
 }
 
-__global__ void k_pca_start(double *__restrict__ V, int n, int b, int ld) {
+__global__ void k_pca_start(double *__restrict__ V, int n, int b, int ld, int ne) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= kPcaMaxB * ld) return;
+    if (e >= ne) return;
     const int c = e / ld, l = e % ld;
     V[e] = c < b && l < n ? pca_hash((uint64_t)l * b + c) : 0.0;
 }
@@ -307,6 +314,69 @@ __global__ __launch_bounds__(256) void k_pca_lin(const double *__restrict__ A, c
                                                  double alpha, double beta, int ne, double *__restrict__ Out) {
     const int e = blockIdx.x * 256 + threadIdx.x;
     if (e < ne) Out[e] = __builtin_fma(beta, B[e], alpha * A[e]);
+}
+
+// A round's whole Chebyshev filter in one block, for n <= LD: the first term
+// Y = f1 W + f0 V, then deg - 1 times (X, Y) <- (Y, a_d C Y + b_d Y + g_d X).  A
+// wavefront owns a 16 x 16 tile of the terms; its rows of C stay in registers
+// as MFMA operands, its own elements of X and Y too, and Y goes around through
+// two buffers in LDS (rows of LD + 2: the 16 columns of a read cover every
+// bank).  Products and sums in k_pca_mv's order.  Bound by the MFMA issue, LD /
+// 4 of 64 cycles per step: 1.0 us a step at n = 64 and 16 columns, where a
+// launch of k_pca_mv per step took 3.5.
+struct PcaCoef {
+    double a[32], b[32], g[32];   // of term d, d = 2 .. deg <= 32, at d - 1
+};
+template <int BT, int LD>
+__global__ __launch_bounds__(LD / 16 * BT * kWave) void k_pca_cheb(const double *__restrict__ Cs,
+                                                                  const double *__restrict__ V,
+                                                                  const double *__restrict__ W, double f1, double f0,
+                                                                  int deg, PcaCoef co, double *__restrict__ Out) {
+    __shared__ __align__(16) double s_y[2][16 * BT][LD + 2];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int m = lane & 15, kk = lane >> 4;
+    const int row0 = 16 * (w % (LD / 16)), col = 16 * (w / (LD / 16)) + m;
+    double c[LD / 16][4];
+#pragma unroll
+    for (int q = 0; q < LD / 16; ++q) pca_load4(Cs + (int64_t)(row0 + m) * LD + 16 * q + 4 * kk, c[q]);
+    // element u of a lane: row row0 + kk + 4 u, column col
+    double x[4], y[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int e = col * LD + row0 + kk + 4 * u;
+        x[u] = V[e];
+        y[u] = __builtin_fma(f0, x[u], f1 * W[e]);
+        s_y[0][col][row0 + kk + 4 * u] = y[u];
+    }
+    __syncthreads();
+    const int c0 = col - m;
+    for (int d = 1; d < deg; ++d) {
+        const double *v0 = &s_y[(d - 1) & 1][c0 + m][4 * kk];
+        double4_t acc[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] = double4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < LD / 16; ++q) {
+            double v[4];
+            pca_load4(v0 + 16 * q, v);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                acc[q & 3] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[q][u], v[u], acc[q & 3], 0, 0, 0);
+        }
+        const double al = co.a[d], be = co.b[d], ga = co.g[d];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            double o = al * ((acc[0][u] + acc[1][u]) + (acc[2][u] + acc[3][u]));
+            if (be != 0.0) o = __builtin_fma(be, y[u], o);
+            if (ga != 0.0) o = __builtin_fma(ga, x[u], o);
+            x[u] = y[u];
+            y[u] = o;
+            s_y[d & 1][col][row0 + kk + 4 * u] = o;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) Out[col * LD + row0 + kk + 4 * u] = y[u];
 }
 
 constexpr int kPcaBlock = 1024;                  // threads of the one-block kernels
