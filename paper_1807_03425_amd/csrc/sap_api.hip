@@ -388,6 +388,8 @@ static sap_status init_fused(sap_ctx *h) {
     float *d_ladder = nullptr;
     SAP_TRY(dalloc(h, &d_ladder, sizeof(float) * 64));
     SAP_HIP(h, hipMemcpyAsync(d_ladder, ladder.data(), sizeof(float) * 64, hipMemcpyHostToDevice, h->stream));
+    uint32_t *d_tmax = nullptr;   // largest 1/d^2 of each tile's quarters
+    SAP_TRY(dalloc(h, &d_tmax, sizeof(uint32_t) * 4 * (size_t)h->ntiles));
     const unsigned grid = (unsigned)std::min<int64_t>(h->ntiles, 8192);
     {
         auto *hist = reinterpret_cast<unsigned long long *>(h->d_st->hist);
@@ -396,11 +398,11 @@ static sap_status init_fused(sap_ctx *h) {
         if (h->cfg.dtype == SAP_F64)
             hipLaunchKernelGGL(k_build_invd2<double>, dim3(grid), dim3(256), 0, h->stream,
                                static_cast<const double *>(h->X), h->ldx, h->N, h->n, h->d_tiles, h->ntiles,
-                               h->cfg.min_len, h->d_invd2, d_ladder, hist, kept, drop);
+                               h->cfg.min_len, h->d_invd2, d_ladder, hist, kept, drop, d_tmax);
         else
             hipLaunchKernelGGL(k_build_invd2<float>, dim3(grid), dim3(256), 0, h->stream,
                                static_cast<const float *>(h->X), h->ldx, h->N, h->n, h->d_tiles, h->ntiles,
-                               h->cfg.min_len, h->d_invd2, d_ladder, hist, kept, drop);
+                               h->cfg.min_len, h->d_invd2, d_ladder, hist, kept, drop, d_tmax);
     }
     SAP_LAUNCHED(h, "k_build_invd2");
     DevState st;
@@ -435,8 +437,9 @@ static sap_status init_fused(sap_ctx *h) {
     if (want > 0) SAP_TRY(dalloc(h, &h->d_close, sizeof(int2) * want));
     {
         unsigned long long *d_count = reinterpret_cast<unsigned long long *>(&h->d_st->n_close);
-        hipLaunchKernelGGL(k_mark_close, dim3(grid), dim3(256), 0, h->stream, h->d_invd2, h->d_tiles,
-                           h->ntiles, thr, h->d_close, want, d_count, &h->d_st->keep_max);
+        const unsigned gm = (unsigned)std::min<int64_t>(ceil_div(h->ntiles, 16), 512);
+        hipLaunchKernelGGL(k_mark_close, dim3(gm), dim3(256), 0, h->stream, h->d_invd2, h->d_tiles,
+                           h->ntiles, (const uint32_t *)d_tmax, thr, h->d_close, want, d_count, &h->d_st->keep_max);
         SAP_LAUNCHED(h, "k_mark_close");
         SAP_TRY(read_state(h, &st));
         if (st.n_close != want)

@@ -111,6 +111,15 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
     return v;
 }
 
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        uint32_t w = __shfl_xor(v, o, kWave);
+        v = w > v ? w : v;
+    }
+    return v;
+}
+
 // lexicographic (r, i, j) order (no branches; false whenever r or r2 is NaN)
 __device__ __forceinline__ bool lex_less(double r, int32_t i, int32_t j, double r2,
                                          int32_t i2, int32_t j2) {

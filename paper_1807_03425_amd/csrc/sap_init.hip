@@ -165,7 +165,8 @@ __global__ __launch_bounds__(256, 4) void k_build_invd2(const TX *__restrict__ X
                                                         const int2 *__restrict__ tiles, int64_t ntiles,
                                                         double min_len, float4 *__restrict__ invd2,
                                                         const float *__restrict__ ladder, unsigned long long *hist,
-                                                        unsigned long long *kept, unsigned long long *dropped) {
+                                                        unsigned long long *kept, unsigned long long *dropped,
+                                                        uint32_t *__restrict__ tmax) {
     __shared__ __align__(16) DistLds L;
     __shared__ unsigned long long s_hist[64];
     __shared__ unsigned long long s_kept, s_drop;
@@ -191,6 +192,7 @@ __global__ __launch_bounds__(256, 4) void k_build_invd2(const TX *__restrict__ X
             constexpr bool FULL = decltype(full)::value;
             const int i0 = b.x * kTile + 4 * ty, j0 = b.y * kTile;
             int drop = 0, kept = 0;
+            uint32_t mx = 0u;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int j = j0 + tile_col(tx, q);
@@ -203,6 +205,7 @@ __global__ __launch_bounds__(256, 4) void k_build_invd2(const TX *__restrict__ X
                     const bool keep = pair && s != 0.0 &&
                                       (FULL || !(min_len > 0.0 && tile_shorter(X + i * ldx, X + j * ldx, n, s, min_len)));
                     const float v = keep ? (float)(1.0 / s) : kMaskDropped;
+                    mx = max(mx, keep ? __float_as_uint(v) : 0u);
                     drop += pair && !keep;
                     if constexpr (!FULL) kept += keep;
                     if (v > lad0) {
@@ -217,6 +220,9 @@ __global__ __launch_bounds__(256, 4) void k_build_invd2(const TX *__restrict__ X
                 }
                 invd2[t * (kTileElems / 4) + ty * 64 + tile_col(tx, q)] = make_float4(out[0], out[1], out[2], out[3]);
             }
+            // the largest of the wavefront's 16 rows (a dropped pair's is negative)
+            const uint32_t wmax = wave_max_u32(mx);
+            if ((threadIdx.x & (kWave - 1)) == 0) tmax[4 * t + (threadIdx.x >> 6)] = wmax;
             ndrop += drop;
             nkept += FULL ? 16 - drop : kept;
         };
@@ -238,40 +244,74 @@ __global__ __launch_bounds__(256, 4) void k_build_invd2(const TX *__restrict__ X
 // Also folds the largest 1/d^2 left to the coarse pass into *keep_max (as
 // float bits: positive floats order like their bit patterns); the coarse
 // error bound is stated for the shortest pair the coarse pass still sees.
+// One wavefront per four tiles at a time, lanes first over the maxima tmax of
+// their quarters (16 rows each): only those above thr are read, a few where
+// the short pairs are few.  One atomic per four tiles on the count (they are
+// counted first, then read again) and one per block on keep_max: at 12 ns each
+// on one address an atomic per pair is what bounds this where the short pairs
+// are many.  N = 20000, 222 short pairs: 16 us, 175 with a read of all 800 MB;
+// N = 8000, 29940 short pairs: 57 and 444.
 __global__ __launch_bounds__(256) void k_mark_close(float4 *invd2, const int2 *tiles,
-                                                    int64_t ntiles, float thr, int2 *list,
-                                                    int64_t cap, unsigned long long *count,
+                                                    int64_t ntiles, const uint32_t *__restrict__ tmax, float thr,
+                                                    int2 *list, int64_t cap, unsigned long long *count,
                                                     unsigned *keep_max) {
     __shared__ unsigned s_max;
     if (threadIdx.x == 0) s_max = 0u;
     __syncthreads();
-    const int c = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const uint64_t below = (1ull << lane) - 1;
     unsigned mx = 0u;
-    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const int2 b = tiles[t];
-        float4 v4[4];   // the tile's loads together, ahead of the rare stores
+    for (int64_t q0 = 16 * ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)); q0 < 4 * ntiles;
+         q0 += 64 * (int64_t)gridDim.x) {
+        const uint32_t tm = lane < 16 && q0 + lane < 4 * ntiles ? tmax[q0 + lane] : 0u;
+        const bool over = __uint_as_float(tm) > thr;
+        if (!over) mx = max(mx, tm);
+        const uint64_t some = __ballot(over);
+        if (!some) continue;
+        auto quarter = [&](int64_t q, float (&v)[4][4]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int m = 0; m < 4; ++m) v4[m] = invd2[t * (kTileElems / 4) + (w + 4 * m) * 64 + c];
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int g = w + 4 * m;
-            float4 *ptr = invd2 + t * (kTileElems / 4) + g * 64 + c;
-            float vv[4] = {v4[m].x, v4[m].y, v4[m].z, v4[m].w};
-            bool hit = false;
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                if (vv[rr] > thr) {
-                    unsigned long long at = atomicAdd(count, 1ull);
-                    if ((int64_t)at < cap)
-                        list[at] = make_int2(b.x * kTile + 4 * g + rr, b.y * kTile + c);
-                    vv[rr] = kMaskClose;
-                    hit = true;
-                } else if (vv[rr] > 0.0f) {
-                    mx = max(mx, __float_as_uint(vv[rr]));
-                }
+            for (int m = 0; m < 4; ++m) {
+                const float4 f = invd2[q * (kTileElems / 16) + m * 64 + lane];
+                v[m][0] = f.x; v[m][1] = f.y; v[m][2] = f.z; v[m][3] = f.w;
             }
-            if (hit) *ptr = make_float4(vv[0], vv[1], vv[2], vv[3]);
+        };
+        int hits = 0;   // of the lane
+        for (uint64_t todo = some; todo; todo &= todo - 1) {
+            float v[4][4];
+            quarter(q0 + __ffsll((unsigned long long)todo) - 1, v);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) hits += v[e / 4][e % 4] > thr;
+        }
+        for (int o = 1; o < kWave; o <<= 1) hits += __shfl_xor(hits, o, kWave);
+        unsigned long long at = 0;
+        if (lane == 0) at = atomicAdd(count, (unsigned long long)hits);
+        at = __shfl(at, 0, kWave);
+        for (uint64_t todo = some; todo; todo &= todo - 1) {
+            const int64_t q = q0 + __ffsll((unsigned long long)todo) - 1;
+            const int2 b = tiles[q >> 2];
+            const int g0 = 4 * (int)(q & 3);
+            float v[4][4];
+            quarter(q, v);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                bool hit = false;
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) {
+                    const bool one = v[m][rr] > thr;
+                    const uint64_t ones = __ballot(one);
+                    if (one) {
+                        const int64_t to = (int64_t)at + __popcll(ones & below);
+                        if (to < cap) list[to] = make_int2(b.x * kTile + 4 * (g0 + m) + rr, b.y * kTile + lane);
+                        v[m][rr] = kMaskClose;
+                        hit = true;
+                    } else if (v[m][rr] > 0.0f) {
+                        mx = max(mx, __float_as_uint(v[m][rr]));
+                    }
+                    at += __popcll(ones);
+                }
+                if (hit)
+                    invd2[q * (kTileElems / 16) + m * 64 + lane] = make_float4(v[m][0], v[m][1], v[m][2], v[m][3]);
+            }
         }
     }
     atomicMax(&s_max, mx);
