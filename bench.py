@@ -281,7 +281,7 @@ def batch_leg(torch, np, name, X, sets, problems, P0s, iters, set_min_len=None):
                 certified_frac=float(np.mean(cert == 1)),
                 roofline=dict(bound="alu", achieved=valu / run_s / 1e12, peak=VALU_LANE_OPS / 1e12,
                               unit="T lane-instr/s", frac=valu / run_s / VALU_LANE_OPS,
-                              note=f"one workgroup per problem: at most {len(problems)} of 256 compute units"),
+                              note="two launches per iteration for the whole batch, each problem on its own blocks"),
                 final_min_by_problem=[float(v) for v in mins[:, -1]])
 
 

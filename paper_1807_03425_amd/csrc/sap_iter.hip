@@ -3,18 +3,17 @@
 // One iteration of the method (paper Sec. 4, Algorithm 1) is
 //   evaluate  r_ij = ||P^T s_ij|| for every kept pair, min + argmin,
 //   update    argmax basis vector, modified Gram-Schmidt, alpha shift.
-// Here it runs as three launches (two for the plain form):
+// Here it runs as three launches (two for the plain form; two for the fused
+// form inside a run, where k_selprep does the last and the first):
 //   k_prep    (fused form) Y = (X - mu) P in FP64 on the matrix cores, rounded
 //             to FP32;
-//   k_pass    the coarse FP32 score of every pair, reduced to per-unit and
-//             per-block minima (fused: ||y_i - y_j||^2 / d^2 per 16 x 64
-//             sub-tile; plain: ||P^T s||^2 per 256-pair chunk, with the
-//             chunk's argmin and second-smallest score); in the fused form
-//             the same grid scores the short pairs (too short for the coarse
-//             error bound) in FP64 on the matrix cores;
-//   k_select  one block: global coarse minimum, the proven rescoring window,
-//             FP64 rescoring of every in-window pair, the FP64 (min, i, j)
-//             record, then the FP64 update of P by one wavefront.
+//   k_pass    the coarse FP32 score of every pair (fused: ||y_i - y_j||^2 / d^2
+//             per 64 x 64 tile; plain: ||P^T s||^2 per stored secant), the
+//             window of the block's running minimum, and the FP64 rescoring of
+//             the block's window pairs; in the fused form the same grid scores
+//             the short pairs (too short for the coarse error bound) in FP64;
+//   k_select  one block: the FP64 (min, i, j) over the blocks' results, its
+//             record, then the FP64 update of P.
 // No two blocks ever contend on one address: each writes its own result
 // slot, and the kernel boundary is the grid-wide barrier.  (Device-scope
 // atomics on one address serialize across the eight XCDs of the part at tens
