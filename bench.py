@@ -155,18 +155,19 @@ def sap_leg(torch, np, w, form, steps, warmup, gemm="f64", prof_steps=None, keep
 
 
 def softmin_slots(K):
-    """Vector issue slots per pair of the soft-min passes, counting the
-    method's own work (a transcendental -- sqrt, rsq, exp2 -- as 4):
+    """Vector lane-instructions per pair of the soft-min passes, the method's
+    own work (a transcendental -- sqrt, rsq, exp2 -- as one: counted as four,
+    the passes would run above the issue rate):
       forward:  K subtractions + K FMAs (||y_i - y_j||^2), a multiply by
-                1/d^2, a select of masked pairs, sqrt, min, and for the sum
-                an FMA, exp2 and an add: 2K + 14;
+                1/d^2, sqrt, min, and for the sum an FMA, exp2, a clamp and
+                an add: 2K + 7;
       backward: the same 2K for the norm, then multiply, rsq, multiply,
-                FMA, exp2, two multiplies, two compares and a select for the
-                weight, and the column side's K FMAs (z_j += a (y_j - y_i)):
-                3K + 16.  The row side's contraction sum_j a_ij y_j (2K flops
-                per pair) runs on the FP64 matrix cores and is priced there
+                FMA, exp2, two multiplies and a maximum for the weight, and
+                the column side's K FMAs (z_j += a (y_j - y_i)): 3K + 8.  The
+                row side's contraction sum_j a_ij y_j (2K flops per pair)
+                runs on the FP64 matrix cores and is priced there
                 (softmin_bwd_flops)."""
-    return 2 * K + 14, 3 * K + 16
+    return 2 * K + 7, 3 * K + 8
 
 
 def softmin_bwd_flops(K):

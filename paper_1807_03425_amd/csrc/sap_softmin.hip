@@ -197,9 +197,10 @@ __device__ __forceinline__ float comp4(const float4 &v, int r) {
 // (the sum of squares starts at 1e-36, so that it is not -0 where y_i = y_j),
 // which the minimum passes over and the clamp of its term to [0, 1] (a
 // modifier of the exponential) makes 0.
-// Bound by VALU issue, 2K + 12 slots per pair (sqrt and exp2 as 4): N = 20000,
-// k = 10 172 us against 163 (224 with the y_i rows through LDS, 8192 blocks and
-// two slots more per pair); N = 1531, k = 3 6 us (10).
+// Bound by VALU issue, 2K + 7 instructions per pair (137 us at N = 20000, k =
+// 10 if sqrt and exp2 took one slot each): 157 to 172 us from card to card; 224
+// with the y_i rows through LDS, 8192 blocks and two instructions more per
+// pair.  N = 1531, k = 3: 6 us (10).
 template <int K>
 __global__ __launch_bounds__(kPairBlock, 4) void k_sm_fwd(SmArgs a) {
     constexpr int KP = K <= 4 ? 4 : (K <= 8 ? 8 : (K <= 12 ? 12 : 16));   // the Y row length (a.kp)
@@ -349,11 +350,11 @@ __device__ __forceinline__ int share_of(const SmArgs &a, int64_t p) {
 // once more for a tile whose halves fall in two shares.  Per half-tile and
 // point-major they were 377 MB written and read again at N = 20000, k = 10
 // (k_sm_zred 90 us, 32 now, traced).
-// Bound by issue: 4K + 16 VALU slots per pair (rsq and exp2 as 4) and the FP64
-// products, which other wavefronts' VALU work covers in part: N = 20000, k = 10
-// 383 us (407 with a block per half-tile and the rows through LDS), N = 14000,
-// k = 16 250 (296), N = 9000, k = 10 85 (79: the merge gained what this
-// lost, 6 us).
+// Bound by issue: 3K + 8 VALU instructions per pair, a sixth more around the
+// products, and the FP64 products, which other wavefronts' VALU work covers in
+// part: N = 20000, k = 10 383 us (407 with a block per half-tile and the rows
+// through LDS), N = 14000, k = 16 250 (296), N = 9000, k = 10 85 (79: the merge
+// gained what this lost, 6 us).
 // LDS per block: 37 KB (K <= 4) to 49 KB (K >= 13): three blocks per compute
 // unit, two for K >= 13 (at three they would spill).
 template <int K>
