@@ -97,6 +97,7 @@ struct sap_ctx {
     };
     HostBack *back = nullptr, *back_dev = nullptr;   // one allocation: host and device address
     hipEvent_t ev_same = nullptr;
+    double *d_stage = nullptr;   // n x k, a P that no kernel can read (kernel_readable)
     int pass_grid = 0, short_grid = 0;
     // fused FP64 Y GEMM split over two wavefronts per 16-row tile (k_prep and
     // k_selprep run n_pad / 32 blocks; see gemm_block_deep)
@@ -255,10 +256,34 @@ static sap_status read_state(sap_ctx *h, DevState *st) {
     return SAP_OK;
 }
 
+// *out = p in device memory; else the `count` values go through hipMemcpy,
+// which takes pinned host memory and refuses (an error, where a kernel would
+// fault) what is not the device's to read.
+template <typename T>
+static sap_status kernel_readable(sap_ctx *h, const T *p, size_t count, const T **out) {
+    hipPointerAttribute_t at{};
+    *out = p;
+    if (hipPointerGetAttributes(&at, p) == hipSuccess &&
+        (at.type == hipMemoryTypeDevice || at.type == hipMemoryTypeManaged))
+        return SAP_OK;
+    (void)hipGetLastError();
+    std::vector<T> v(count);
+    const hipError_t read = hipMemcpyAsync(v.data(), p, sizeof(T) * count, hipMemcpyDeviceToHost, h->stream);
+    if (read != hipSuccess) (void)hipGetLastError();   // (the next launch would report it)
+    SAP_HIP(h, read);
+    SAP_HIP(h, hipStreamSynchronize(h->stream));
+    if (!h->d_stage) SAP_TRY(dalloc(h, &h->d_stage, sizeof(double) * h->n * h->k));
+    SAP_HIP(h, hipMemcpyAsync(h->d_stage, v.data(), sizeof(T) * count, hipMemcpyHostToDevice, h->stream));
+    SAP_HIP(h, hipStreamSynchronize(h->stream));   // (the host vector ends here)
+    *out = reinterpret_cast<const T *>(h->d_stage);
+    return SAP_OK;
+}
+
 // Load a device P (n x k row-major) into the FP64 master (k x n) if it passes
 // the checks.
 static sap_status load_P(sap_ctx *h, const double *P_dev) {
     const int n = h->n, k = h->k;
+    SAP_TRY(kernel_readable(h, P_dev, (size_t)n * k, &P_dev));
     hipLaunchKernelGGL(k_load_P, dim3(1), dim3(kLoadP), 0, h->stream, P_dev, n, k, kOrthoTol, h->d_P64t,
                        &h->back_dev->ortho, &h->back_dev->finite_P);
     SAP_LAUNCHED(h, "k_load_P");
@@ -1241,6 +1266,7 @@ sap_status sap_softmin_bwd(sap_handle h, const float *P, double tau, const float
     // kernel and the backward is enqueued behind it, so that the device works
     // while the host waits for the verdict; where P differs, k_sm_dP writes
     // nothing and the call ends with nothing pending.
+    SAP_TRY(kernel_readable(h, P, (size_t)h->n * h->k, &P));
     if (!h->ev_same) SAP_HIP(h, hipEventCreateWithFlags(&h->ev_same, hipEventDisableTiming));
     SAP_TRY(launch(h, 5, "k_sm_same", k_sm_same, dim3(1), dim3(kSameBlock), 0, P, (const float *)h->d_smP32,
                    h->n * h->k, h->d_st, &h->back_dev->same_P));

@@ -106,3 +106,29 @@ def test_set_P_checks(n, k, form):
     assert np.array_equal(h.get_P().cpu().numpy(), P1)
     assert h.min_secant()["min_norm"] == ref
     h.close()
+
+
+def test_P_in_host_memory():
+    """set_P and softmin_bwd read a P in pinned host memory; pageable memory is
+    an error."""
+    h, P0 = _handle()
+    ptr = lambda p: C.c_void_p(p.data_ptr())
+    host = torch.empty(P0.shape, dtype=torch.float64, pin_memory=True)
+    host.copy_(P0.flip(1))
+    assert lib().sap_set_P(h.handle, ptr(host)) == 0
+    assert np.array_equal(h.get_P().cpu().numpy(), host.numpy())
+    P = P0.float().contiguous()
+    h.softmin_fwd(P, 0.05)
+    one, dP = torch.ones(1, device=DEV), torch.full_like(P, 7.0)
+    want = h.softmin_bwd(P, 0.05, one).cpu().numpy()
+    same = torch.empty(P.shape, dtype=torch.float32, pin_memory=True)
+    other = torch.empty(P.shape, dtype=torch.float32, pin_memory=True)
+    same.copy_(P)
+    other.copy_(P)
+    other[3, 2] += 0.25
+    call = lambda p: lib().sap_softmin_bwd(h.handle, ptr(p), 0.05, ptr(one), ptr(dP))
+    assert call(other) != 0 and bool((dP == 7.0).all())
+    assert call(same) == 0
+    assert np.array_equal(dP.cpu().numpy(), want)
+    assert lib().sap_set_P(h.handle, ptr(host.clone())) != 0   # (a device error: the handle ends here)
+    h.close()
