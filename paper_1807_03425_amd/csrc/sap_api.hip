@@ -256,15 +256,16 @@ static sap_status read_state(sap_ctx *h, DevState *st) {
     return SAP_OK;
 }
 
-// *out = p in device memory; else the `count` values go through hipMemcpy,
-// which takes pinned host memory and refuses (an error, where a kernel would
-// fault) what is not the device's to read.
+// *out = p where a kernel can read it (device, managed and pinned memory);
+// else the `count` values go through hipMemcpy, which makes an error of what
+// a kernel would fault on.
 template <typename T>
 static sap_status kernel_readable(sap_ctx *h, const T *p, size_t count, const T **out) {
     hipPointerAttribute_t at{};
     *out = p;
     if (hipPointerGetAttributes(&at, p) == hipSuccess &&
-        (at.type == hipMemoryTypeDevice || at.type == hipMemoryTypeManaged))
+        (at.type == hipMemoryTypeDevice || at.type == hipMemoryTypeManaged ||
+         (at.type == hipMemoryTypeHost && at.devicePointer && at.devicePointer == at.hostPointer)))
         return SAP_OK;
     (void)hipGetLastError();
     std::vector<T> v(count);
@@ -1247,6 +1248,7 @@ sap_status sap_softmin_fwd(sap_handle h, const float *P, double tau, float *loss
     if (!loss) return fail(h, SAP_ERR_INVALID_ARG, "null loss pointer");
     SAP_TRY(sm_alloc(h));
     h->sm_ready = false;
+    SAP_TRY(kernel_readable(h, P, (size_t)h->n * h->k, &P));
     if (h->cfg.dtype == SAP_F64) SAP_TRY(sm_forward<double>(h, P, tau, loss));
     else SAP_TRY(sm_forward<float>(h, P, tau, loss));
     h->sm_ready = true;

@@ -109,7 +109,7 @@ def test_set_P_checks(n, k, form):
 
 
 def test_P_in_host_memory():
-    """set_P and softmin_bwd read a P in pinned host memory; pageable memory is
+    """set_P and the soft-min read a P in pinned host memory; pageable memory is
     an error."""
     h, P0 = _handle()
     ptr = lambda p: C.c_void_p(p.data_ptr())
@@ -130,5 +130,12 @@ def test_P_in_host_memory():
     assert call(other) != 0 and bool((dP == 7.0).all())
     assert call(same) == 0
     assert np.array_equal(dP.cpu().numpy(), want)
+    loss = torch.zeros(1, device=DEV)
+    assert lib().sap_softmin_fwd(h.handle, ptr(same), 0.05, ptr(loss)) == 0
+    assert call(P) == 0
+    assert np.array_equal(dP.cpu().numpy(), want)
     assert lib().sap_set_P(h.handle, ptr(host.clone())) != 0   # (a device error: the handle ends here)
+    h.close()
+    h, _ = _handle()
+    assert lib().sap_softmin_fwd(h.handle, ptr(same.clone()), 0.05, ptr(loss)) != 0
     h.close()
