@@ -278,7 +278,10 @@ __global__ __launch_bounds__(256) void k_batch_checkP(BatchArgs a) {
             for (int q = 0; q < 16; ++q) acc += u[q] * v[q];
         }
         for (; l < n; ++l) acc += P[l * k + x] * P[l * k + y];
-        atomicMax(&s_err, (unsigned long long)__double_as_longlong(fabs(acc - (x == y ? 1.0 : 0.0))));
+        const double e = fabs(acc - (x == y ? 1.0 : 0.0));
+        // (a NaN ranks above inf by its bits: inf - inf off the diagonal stays
+        // out, an infinite square of a column is on it)
+        if (e >= 0.0) atomicMax(&s_err, (unsigned long long)__double_as_longlong(e));
     }
     __syncthreads();
     if (threadIdx.x == 0) a.chk[blockIdx.x] = BatchCheck{__longlong_as_double((long long)s_err), s_bad, 0};

@@ -267,3 +267,19 @@ def test_one_large_problem_and_many_small_ones():
     alone = batch_run(Xt, many[:7], problems[:7], starts[:7], 4)
     _equal(out, alone, 7)
     assert np.all(out["certified"].cpu().numpy() == 1)
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_starts_whose_products_overflow_are_refused(noalloc):
+    """Finite entries of P0 whose products overflow: infinite on the diagonal
+    of P0^T P0, and inf - inf off it in the first."""
+    X = torch.from_numpy(np.random.default_rng(3).standard_normal((100, 2))).to(DEV)
+    sets = [np.arange(40), np.arange(100)]
+    good = np.eye(2)
+    for bad in (np.array([[1e200, 1e200], [1e200, -1e200]]), 1e200 * good, np.array([[1.0, 1e200], [0.0, 1e200]])):
+        for b in (0, 1):
+            P0s = [good, good]
+            P0s[b] = bad
+            with pytest.raises(SapError, match="NOT_ORTHONORMAL.*problem %d" % b):
+                batch_run(X, sets, [dict(set=0, k=2), dict(set=1, k=2)], P0s, 2, noalloc=noalloc)
+    assert batch_run(X, sets, [dict(set=0, k=2)], [good], 2, noalloc=noalloc)["min"].isfinite().all()
