@@ -193,11 +193,13 @@ __device__ __forceinline__ float comp4(const float4 &v, int r) {
 // pair pass: y_i rows by scalar loads, the next half-tile's weights and y_j in
 // flight during the current one).  Per lane, the 32 r of a half-tile are
 // reduced to their min m_c and s_c = sum 2^((m_c - r) c2), then folded into
-// the lane's running (m, s).  A masked pair's 1/d^2 is negative: its r is NaN
-// (the sum of squares starts at 1e-36, so that it is not -0 where y_i = y_j),
-// which the minimum passes over and the clamp of its term to [0, 1] (a
-// modifier of the exponential) makes 0.
-// Bound by VALU issue, 2K + 7 instructions per pair (137 us at N = 20000, k =
+// the lane's running (m, s).  A masked pair's 1/d^2 is -1 or -2: its r is NaN
+// (1/d^2 itself is added to its r^2, which alone would be -0 where y_i = y_j;
+// for the others the addend is 0), which the minimum passes over and the
+// clamp of its term to [0, 1] (a modifier of the exponential) makes 0.  A
+// constant start of the sum of squares would do without the addend, but it is
+// a length: next to coordinates of 1e-15 1e-36 is not small any more.
+// Bound by VALU issue, 2K + 8 instructions per pair (142 us at N = 20000, k =
 // 10 if sqrt and exp2 took one slot each): 157 to 172 us from card to card; 224
 // with the y_i rows through LDS, 8192 blocks and two instructions more per
 // pair.  N = 1531, k = 3: 6 us (10).
@@ -240,13 +242,14 @@ __global__ __launch_bounds__(kPairBlock, 4) void k_sm_fwd(SmArgs a) {
 #pragma unroll
             for (int rr = 0; rr < R; ++rr) {
                 const int e = e0 + rr;
-                float acc = 1e-36f;
+                float acc = 0.0f;
 #pragma unroll
                 for (int c = 0; c < K; ++c) {
                     const float d = yr[(e0 / R) & 1][rr][c] - yj[c];
                     acc = __builtin_fmaf(d, d, acc);
                 }
-                r[e] = __builtin_amdgcn_sqrtf(acc * comp4(w[e / 4], e % 4));
+                const float wt = comp4(w[e / 4], e % 4);
+                r[e] = __builtin_amdgcn_sqrtf(__builtin_fmaf(acc, wt, __builtin_amdgcn_fmed3f(wt, -2.0f, 0.0f)));
                 asm volatile("" : "+v"(r[e]));   // computed here: deferred, the rows would outlive the scalar registers
                 mc = fminf(mc, r[e]);
                 if constexpr (PF)

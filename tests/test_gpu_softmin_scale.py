@@ -1,0 +1,60 @@
+"""The soft-min is a function of ratios: points scaled by a power of two give
+the same loss and the same gradient, bit for bit.  Every quantity of the two
+passes then scales exactly (1/d^2 in FP32 by 2^-2e, Y by 2^e, the squares by
+2^2e) as long as it stays a normal number, which the scales here leave room
+for: the smallest squares are r^2 d^2 2^-100, r about 2^-7.  Masked pairs
+(duplicates, the diagonal, the padding) and short pairs are among them."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_1807_03425_amd import SapContext  # noqa: E402
+
+DEV = torch.device("cuda:0")
+
+
+def _loss_grad(X, P, tau):
+    with SapContext(X, P.cpu(), form="fused") as ctx:
+        P32 = P.float().contiguous()
+        loss = ctx.softmin_fwd(P32, tau).cpu().numpy()
+        return loss, ctx.softmin_bwd(P32, tau, torch.ones(1, device=DEV)).cpu().numpy(), ctx.info()["n_close"]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("k", [3, 7, 10, 16])
+def test_loss_and_gradient_do_not_depend_on_the_scale(k, dtype):
+    g = torch.Generator().manual_seed(100 + k)
+    X = torch.randn(300, 20, generator=g, dtype=torch.float64)
+    X[297] = X[5]                             # masked pairs
+    X[70] = X[71]
+    X[10] = X[11] + 1e-6 * X[12]              # a short pair
+    X = X.to(dtype).to(DEV)
+    P = torch.linalg.qr(torch.randn(20, k, generator=g, dtype=torch.float64))[0].to(DEV)
+    loss, dP, nclose = _loss_grad(X, P, 0.01)
+    assert nclose > 0 and np.isfinite(loss[0]) and np.abs(dP).max() > 0.0
+    for e in (-50, -44, -30, 40):
+        l2, d2, n2 = _loss_grad(X * 2.0 ** e, P, 0.01)
+        assert n2 == nclose
+        assert np.array_equal(l2, loss), (e, l2, loss)
+        assert np.array_equal(d2, dP), (e, np.abs(d2 - dP).max())
+
+
+@pytest.mark.parametrize("k", [1, 4, 6, 12])
+def test_kept_pairs_of_equal_projection_count(k):
+    """A kept pair whose projections are equal has r = 0 and its whole weight
+    in the sum (a masked one, whose product with 1/d^2 is -0, has none): with
+    all r equal to 0, L = -tau log(pairs) in FP32 and the gradient is 0."""
+    N, n, tau = 70, 80 + k, 0.25
+    X = torch.zeros(N, n, dtype=torch.float64)
+    X[torch.arange(N), k + torch.arange(N)] = torch.arange(1, N + 1, dtype=torch.float64)   # off the columns of P
+    X[69] = X[68]                                                                            # a duplicate
+    P = torch.eye(n, dtype=torch.float64)[:, :k].contiguous()
+    loss, dP, _ = _loss_grad(X.to(DEV), P.to(DEV), tau)
+    want = -tau * np.log(N * (N - 1) // 2 - 1)
+    assert abs(loss[0] - want) <= 2.0 ** -23 * abs(want), (loss, want)
+    assert not dP.any()
