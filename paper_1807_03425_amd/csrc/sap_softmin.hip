@@ -336,7 +336,9 @@ __device__ __forceinline__ int share_of(const SmArgs &a, int64_t p) {
 // the column side
 //   z_j += sum_i a_ij (y_j - y_i)
 // accumulated in FP32 from the differences y_i - y_j that the weight needed
-// anyway, over the halves of the tile that the share holds; a_ij goes to the
+// anyway, over the halves of the tile that the share holds, eight rows and
+// then the eights: a sum over 64 rows in a row would round twice as often as
+// one over a half-tile, this rounds a quarter as often.  a_ij goes to the
 // wavefront's LDS block.
 // Phase 2: the row side
 //   z_i += sum_j a_ij (y_i - y_j) = (sum_j a_ij) y_i - (A Y_J)_i
@@ -426,6 +428,7 @@ __global__ __launch_bounds__(kPairBlock, K <= 12 ? 3 : 2) void k_sm_bwd(SmArgs a
                 const UniformF yi0 = (UniformF)(yrow + 32 * HS * KP);
 #pragma unroll 1
                 for (int g = 0; g < 8; g += 2) {
+                    float z8[K];   // the column side of these eight rows
 #pragma unroll
                     for (int g2 = 0; g2 < 2; ++g2) {
                         const float4 w4 = wq[g2];
@@ -450,10 +453,13 @@ __global__ __launch_bounds__(kPairBlock, K <= 12 ? 3 : 2) void k_sm_bwd(SmArgs a
                             const float ex = __builtin_amdgcn_exp2f(__builtin_fmaf(-rv, c2, Lc));
                             const float av = fmaxf(ex * wt * rinv, 0.0f);
 #pragma unroll
-                            for (int q = 0; q < K; ++q) zc[q] = __builtin_fmaf(-av, d[q], zc[q]);
+                            for (int q = 0; q < K; ++q)
+                                z8[q] = g2 + rr == 0 ? -av * d[q] : __builtin_fmaf(-av, d[q], z8[q]);
                             al[(4 * (g + g2) + rr) * kAStride + lane] = av;
                         }
                     }
+#pragma unroll
+                    for (int q = 0; q < K; ++q) zc[q] += z8[q];
                 }
                 __builtin_amdgcn_wave_barrier();
                 // phase 2: A[16 mb + c16][4 u + r4] from LDS, B = Y_J[4 u + r4][c16]

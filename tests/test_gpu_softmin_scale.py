@@ -58,3 +58,46 @@ def test_kept_pairs_of_equal_projection_count(k):
     want = -tau * np.log(N * (N - 1) // 2 - 1)
     assert abs(loss[0] - want) <= 2.0 ** -23 * abs(want), (loss, want)
     assert not dP.any()
+
+
+@pytest.mark.parametrize("k", [1, 10, 16])
+def test_column_sums_keep_the_bits_of_two_half_tiles(k):
+    """One point's 64 equal terms of the gradient, once on the column side of a
+    tile (a sum over the tile's rows in FP32) and, with the points in reverse,
+    on the row side (FP64).  The weights are the same bits, so the two
+    gradients differ by the rounding of the column sum.  On average it is no
+    more than that of two sums of 32 rows, taken on the host for random terms,
+    and the roundings of the stored partials and gradients (four of at most u,
+    taken as one).  The other points, on a line along the first column of P (r
+    near 1, weights below e^-40), make the set large enough for wavefronts that
+    hold both halves of a tile."""
+    u = 2.0 ** -24
+    rng = np.random.default_rng(k)
+    f = np.float32
+    ref = []
+    for c in rng.uniform(1.0, 2.0, 2000).astype(f):
+        s = f(0.0)
+        for _ in range(32):
+            s = f(s + c)
+        ref.append(abs(2.0 * float(s) - 64.0 * float(c)) / (64.0 * float(c)))
+    N = 8000
+    P = torch.eye(65 + k, dtype=torch.float64)[:, :k].contiguous().to(DEV)
+    one = torch.ones(1, device=DEV)
+    err = []
+    for case, h in enumerate(rng.uniform(0.05, 0.4, 64)):
+        X = np.zeros((N, 65 + k))
+        X[:, 0] = (3.0 + 0.001 * np.arange(N)) * (-1.0) ** np.arange(N)
+        X[:64, 0] = h
+        X[np.arange(64), k + np.arange(64)] = 1.0    # all at the same distance from the one point
+        j = 64 * (1 + case)
+        X[j] = 0.0
+        X[j, 64 + k] = 1.0                           # a coordinate of its own
+        got = []
+        for A in (X, np.ascontiguousarray(X[::-1])):
+            with SapContext(torch.from_numpy(A).to(DEV), P.cpu(), form="fused", close_d=0.0) as ctx:
+                ctx.softmin_fwd(P.float(), 0.01)
+                got.append(float(ctx.softmin_bwd(P.float(), 0.01, one)[64 + k, 0]))
+        err.append(abs(got[0] - got[1]) / abs(got[1]))
+    print(f"[column] k={k}: mean {np.mean(err) / u:.2f} u, max {np.max(err) / u:.2f} u, "
+          f"two sums of 32: {np.mean(ref) / u:.2f} u")
+    assert np.mean(err) <= np.mean(ref) + u
