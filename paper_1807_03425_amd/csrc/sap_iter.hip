@@ -1277,9 +1277,13 @@ __device__ __forceinline__ int strike_candidates(const SweepArgs<TX> &a, uint32_
             const double sw = sqrt(w), rt = sqrt(s) * sw;
             const double eb = (a.s_d2 * sw + (a.s_eps + 5.9604644775390625e-08) * rt) * (1.0 + 1e-6);
             const double rc = sqrt((double)__uint_as_float(kv));
-            viol = fabs(rt - rc) > (a.e_abs + a.e_rel * fmax(rt, rc) + eb) * 1.0001 ? 1 : 0;
-            lb = rt - eb;
-            u1 = rt + eb;
+            // (a subnormal 1/d^2 has fewer bits than the bound counts on: its
+            // pair is neither struck nor strikes another)
+            if (w >= 0x1p-126) {
+                viol = fabs(rt - rc) > (a.e_abs + a.e_rel * fmax(rt, rc) + eb) * 1.0001 ? 1 : 0;
+                lb = rt - eb;
+                u1 = rt + eb;
+            }
         }
     }
 #pragma unroll 1
