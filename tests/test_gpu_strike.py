@@ -1,5 +1,6 @@
-"""What the bounds from the unrounded Y may strike from a block's window: never
-a pair whose 1/d^2 FP32 holds with fewer than 24 bits."""
+"""What the bounds from the unrounded Y may strike from a block's window: more
+candidates than are looked at together, the smallest pair among those that are
+not, and 1/d^2 that FP32 holds with fewer than 24 bits."""
 import numpy as np
 import pytest
 
@@ -21,6 +22,50 @@ def _values(X, P):
     r = np.linalg.norm(D @ P, axis=1) / np.linalg.norm(D, axis=1)
     o = np.lexsort((j, i, r))
     return r[o], i[o], j[o]
+
+
+def _late_minimum(k, seed):
+    """64 points (one tile, one block; k >= 8: a list per 16 rows) with some 350
+    pairs of distinct r in the window, 70 to 120 in each list, the smallest the
+    last pair of all.  27 points differ little in the plane of P, the others
+    much; two far points make the window wide, one short pair (r = 1) makes the
+    handle keep the FP64 Y."""
+    rng = np.random.default_rng(seed)
+    n = 40
+    P = np.linalg.qr(rng.standard_normal((n, n)))[0]
+    P, Q = P[:, :k], P[:, k:]
+    special = np.zeros(64, bool)
+    for q, m in enumerate((5, 4, 5, 13)):
+        special[16 * q + 16 - m:16 * q + 16] = True
+    A, B = rng.standard_normal((64, k)), rng.standard_normal((64, n - k))
+    A /= np.linalg.norm(A, axis=1, keepdims=True)
+    B /= np.linalg.norm(B, axis=1, keepdims=True)
+    X = np.where(special[:, None], A @ P.T + 3.3 * B @ Q.T, 12.0 * A @ P.T + B @ Q.T)
+    mid, t = 0.5 * (X[62] + X[63]) @ P, (X[62] - X[63]) @ P
+    for p, s in ((62, 0.3), (63, -0.3)):
+        X[p] += (mid + s * t / np.linalg.norm(t) - X[p] @ P) @ P.T
+    f = rng.standard_normal(n)
+    f /= np.linalg.norm(f)
+    X[0], X[1] = 4e6 * f, -4e6 * f
+    X[3] = X[2] + 1e-3 * P[:, 0]
+    return X, np.ascontiguousarray(P)
+
+
+@pytest.mark.parametrize("k,seed", [(8, 1), (12, 0), (16, 0)])
+def test_more_than_256_candidates_with_the_smallest_last(k, seed):
+    X, P = _late_minimum(k, seed)
+    r, i, j = _values(X, P)
+    assert (i[0], j[0]) == (62, 63) and r[1] - r[0] > 1e-3 and r[2] - r[1] > 1e-6
+    with SapContext(torch.from_numpy(X).to(DEV), torch.from_numpy(P), form="fused", close_d=2e-3) as ctx:
+        assert ctx.info()["n_close"] == 1
+        res = ctx.min_secant()
+    tol = 1e-12 * r[0] + 2.0 * np.sqrt(k) * 40 * 2.0 ** -53
+    inside = int(np.sum(r <= res["coarse_min"] + res["window"]))
+    print(f"[strike] k={k}: {inside} pairs in the window, {res['n_rescored']} evaluated")
+    assert res["certified"] == 1 and (res["i"], res["j"]) == (62, 63), res
+    assert abs(res["min_norm"] - r[0]) <= tol
+    assert res["runner_up_exact"] == 1 and abs(res["runner_up"] - r[1]) <= tol, (res, r[:3])
+    assert inside > 256 + 20 and inside - 256 < res["n_rescored"] < inside // 2, (inside, res)
 
 
 @pytest.mark.parametrize("shift", [0, -40])
