@@ -13,6 +13,7 @@
 #include <hip/hip_ext.h>
 
 #include "sap_common.h"
+#include "sap_mem.h"
 
 // The K-independent kernels are compiled into this translation unit; the
 // kernels templated on K are compiled per K in sap_kinst.hip and reached
@@ -256,17 +257,14 @@ static sap_status read_state(sap_ctx *h, DevState *st) {
     return SAP_OK;
 }
 
-// *out = p where a kernel can read it (device, managed and pinned memory);
-// else the `count` values go through hipMemcpy, which makes an error of what
-// a kernel would fault on.
+// *out = p where a kernel of the handle's device can read it; else the `count`
+// values go through hipMemcpy, which reads another device's memory and makes
+// an error of what a kernel would fault on.
 template <typename T>
 static sap_status kernel_readable(sap_ctx *h, const T *p, size_t count, const T **out) {
     hipPointerAttribute_t at{};
     *out = p;
-    if (hipPointerGetAttributes(&at, p) == hipSuccess &&
-        (at.type == hipMemoryTypeDevice || at.type == hipMemoryTypeManaged ||
-         (at.type == hipMemoryTypeHost && at.devicePointer && at.devicePointer == at.hostPointer)))
-        return SAP_OK;
+    if (hipPointerGetAttributes(&at, p) == hipSuccess && kernel_can_read(at, h->device)) return SAP_OK;
     (void)hipGetLastError();
     std::vector<T> v(count);
     const hipError_t read = hipMemcpyAsync(v.data(), p, sizeof(T) * count, hipMemcpyDeviceToHost, h->stream);
