@@ -48,6 +48,7 @@
 
 #include "sap_dist.h"
 #include "sap_iter.hip"
+#include "sap_mem.h"
 
 namespace sap {
 
@@ -826,6 +827,34 @@ sap_status check_P0(const BatchCheck *chk, int n_problems) {
     return SAP_OK;
 }
 
+// Starts that no kernel can read where they lie: copied to the host (an error
+// where they are not memory of a device or pinned), checked there in
+// k_batch_checkP's order of sums, and put into both P buffers.
+sap_status load_starts_by_copy(const BatchPlan &pl, const double *P0, int n, double *Pbuf, double *Pnext,
+                               std::vector<BatchCheck> &chk, hipStream_t stream) {
+    std::vector<double> h((size_t)pl.P0_total), Pt((size_t)pl.P_total, 0.0);
+    B_HIP(hipMemcpyAsync(h.data(), P0, sizeof(double) * h.size(), hipMemcpyDeviceToHost, stream));
+    B_HIP(hipStreamSynchronize(stream));
+    for (size_t b = 0; b < pl.probs.size(); ++b) {
+        const BatchProb &p = pl.probs[b];
+        const double *P = h.data() + p.P0_off;
+        chk[b] = BatchCheck{0.0, 0, 0};
+        for (int e = 0; e < n * p.k; ++e) chk[b].nonfinite |= std::isfinite(P[e]) ? 0 : 1;
+        for (int x = 0; x < p.k; ++x)
+            for (int y = 0; y < p.k; ++y) {
+                double acc = 0.0;
+                for (int l = 0; l < n; ++l) acc += P[(size_t)l * p.k + x] * P[(size_t)l * p.k + y];
+                chk[b].err = std::max(chk[b].err, std::fabs(acc - (x == y ? 1.0 : 0.0)));   // (a NaN stays out)
+            }
+        for (int q = 0; q < p.k; ++q)
+            for (int l = 0; l < n; ++l) Pt[(size_t)p.P_off + (size_t)q * n + l] = P[(size_t)l * p.k + q];
+    }
+    B_HIP(hipMemcpyAsync(Pbuf, Pt.data(), sizeof(double) * Pt.size(), hipMemcpyHostToDevice, stream));
+    B_HIP(hipMemcpyAsync(Pnext, Pt.data(), sizeof(double) * Pt.size(), hipMemcpyHostToDevice, stream));
+    B_HIP(hipStreamSynchronize(stream));   // (the host vector ends here)
+    return SAP_OK;
+}
+
 // Enqueue the whole batch on `stream` with the scratch at `base` (pl.total
 // bytes), and wait for it.
 sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dtype, int64_t ldx, int32_t n,
@@ -893,11 +922,21 @@ sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dty
     if ((st = launched("batch precomputation")) != SAP_OK) return st;
     int kpmax = 0;
     for (const BatchProb &p : pl.probs) kpmax = std::max(kpmax, p.kp);
-    hipLaunchKernelGGL(k_batch_loadP, dim3((unsigned)((kpmax * n + 255) / 256), (unsigned)n_problems), dim3(256), 0,
-                       stream, a);
-    if ((st = launched("k_batch_loadP")) != SAP_OK) return st;
-    hipLaunchKernelGGL(k_batch_checkP, dim3((unsigned)n_problems), dim3(256), 0, stream, a);
-    if ((st = launched("k_batch_checkP")) != SAP_OK) return st;
+    std::vector<BatchCheck> hc(n_problems);
+    int dev = 0;
+    hipPointerAttribute_t at{};
+    B_HIP(hipGetDevice(&dev));
+    const bool in_place = hipPointerGetAttributes(&at, P0) == hipSuccess && kernel_can_read(at, dev);
+    if (in_place) {
+        hipLaunchKernelGGL(k_batch_loadP, dim3((unsigned)((kpmax * n + 255) / 256), (unsigned)n_problems), dim3(256), 0,
+                           stream, a);
+        if ((st = launched("k_batch_loadP")) != SAP_OK) return st;
+        hipLaunchKernelGGL(k_batch_checkP, dim3((unsigned)n_problems), dim3(256), 0, stream, a);
+        if ((st = launched("k_batch_checkP")) != SAP_OK) return st;
+    } else {
+        (void)hipGetLastError();
+        if ((st = load_starts_by_copy(pl, P0, n, a.Pbuf, a.Pnext, hc, stream)) != SAP_OK) return st;
+    }
     // inputs checked before the run: orthonormal starts, finite rows, kept pairs
     {
         // (the sets' statistics and the starts' checks lie one behind the other)
@@ -905,9 +944,8 @@ sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dty
         B_HIP(hipMemcpyAsync(back.data(), base + pl.o_stat, back.size(), hipMemcpyDeviceToHost, stream));
         B_HIP(hipStreamSynchronize(stream));
         std::vector<BatchStat> hs(n_sets);
-        std::vector<BatchCheck> hc(n_problems);
         std::memcpy(hs.data(), back.data(), sizeof(BatchStat) * n_sets);
-        std::memcpy(hc.data(), back.data() + (pl.o_chk - pl.o_stat), sizeof(BatchCheck) * n_problems);
+        if (in_place) std::memcpy(hc.data(), back.data() + (pl.o_chk - pl.o_stat), sizeof(BatchCheck) * n_problems);
         if ((st = check_P0(hc.data(), n_problems)) != SAP_OK) return st;
         int64_t kept = 0;
         for (int s = 0; s < n_sets; ++s) {

@@ -28,7 +28,9 @@ pytestmark = pytest.mark.gpu
 if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
-from paper_1807_03425_amd import SapError, batch_run  # noqa: E402
+import ctypes as C  # noqa: E402
+
+from paper_1807_03425_amd import SapError, batch_run, lib, sap_batch_problem  # noqa: E402
 
 DEV = torch.device("cuda:0")
 NEAR_TIE = 1e-6
@@ -283,3 +285,34 @@ def test_starts_whose_products_overflow_are_refused(noalloc):
             with pytest.raises(SapError, match="NOT_ORTHONORMAL.*problem %d" % b):
                 batch_run(X, sets, [dict(set=0, k=2), dict(set=1, k=2)], P0s, 2, noalloc=noalloc)
     assert batch_run(X, sets, [dict(set=0, k=2)], [good], 2, noalloc=noalloc)["min"].isfinite().all()
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_starts_in_host_memory(noalloc):
+    """P0 in pinned host memory is read; pageable host memory is an error
+    (through the C ABI: batch_run moves the starts to the device)."""
+    rng = np.random.default_rng(5)
+    X = torch.from_numpy(rng.standard_normal((100, 9))).to(DEV)
+    off, pts = np.array([0, 40, 140], dtype=np.int64), np.concatenate([np.arange(40), np.arange(100)]).astype(np.int32)
+    ks = (2, 5)
+    P0 = torch.from_numpy(np.concatenate([sap_inputs.random_orthonormal(rng, 9, k).ravel() for k in ks]))
+    probs = (sap_batch_problem * 2)(*[sap_batch_problem(b, k, 0, 0, 0.01) for b, k in enumerate(ks)])
+    host = torch.empty(P0.shape, dtype=torch.float64, pin_memory=True)
+    host.copy_(P0)
+    ptr = lambda t: C.c_void_p(t.data_ptr())
+    fn = lib().sap_batch_run_noalloc if noalloc else lib().sap_batch_run
+
+    def call(start):
+        P, tr = torch.zeros(P0.shape, dtype=torch.float64, device=DEV), torch.zeros(2, 4, dtype=torch.float64, device=DEV)
+        rc = fn(ptr(X), 0, 100, 9, 9, 2, off.ctypes.data_as(C.c_void_p), pts.ctypes.data_as(C.c_void_p), None, 2, probs,
+                ptr(start), 3, 0, ptr(P), ptr(tr), None, None, C.c_void_p(torch.cuda.current_stream().cuda_stream), None)
+        return rc, P.cpu().numpy(), tr.cpu().numpy()
+
+    want = call(P0.to(DEV))
+    assert want[0] == 0 and np.isfinite(want[2]).all()
+    got = call(host)
+    assert got[0] == 0 and np.array_equal(got[1], want[1]) and np.array_equal(got[2], want[2])
+    rc, P, tr = call(P0.clone())
+    assert rc != 0 and not P.any() and not tr.any()
+    got = call(P0.to(DEV))
+    assert got[0] == 0 and np.array_equal(got[1], want[1]) and np.array_equal(got[2], want[2])
