@@ -855,6 +855,15 @@ sap_status load_starts_by_copy(const BatchPlan &pl, const double *P0, int n, dou
     return SAP_OK;
 }
 
+// The events of a timed call, destroyed on every way out.
+struct BatchEvents {
+    hipEvent_t e[3] = {};
+    ~BatchEvents() {
+        for (hipEvent_t v : e)
+            if (v) (void)hipEventDestroy(v);
+    }
+};
+
 // Enqueue the whole batch on `stream` with the scratch at `base` (pl.total
 // bytes), and wait for it.
 sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dtype, int64_t ldx, int32_t n,
@@ -891,12 +900,10 @@ sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dty
     a.tr_ij = ij_trace;
     a.tr_cert = cert_trace;
     B_HIP(hipMemcpyAsync(base, pl.tables.data(), pl.tables.size(), hipMemcpyHostToDevice, stream));
-    hipEvent_t e0 = nullptr, e1 = nullptr, e2 = nullptr;
+    BatchEvents ev;
     if (timed) {
-        B_HIP(hipEventCreate(&e0));
-        B_HIP(hipEventCreate(&e1));
-        B_HIP(hipEventCreate(&e2));
-        B_HIP(hipEventRecord(e0, stream));
+        for (hipEvent_t &v : ev.e) B_HIP(hipEventCreate(&v));
+        B_HIP(hipEventRecord(ev.e[0], stream));
     }
     auto launched = [&](const char *what) -> sap_status {
         const hipError_t e = hipGetLastError();
@@ -954,7 +961,7 @@ sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dty
         for (const BatchProb &p : pl.probs) kept += (int64_t)hs[p.set].kept;
         if (stats) stats->n_pairs = kept;
     }
-    if (timed) B_HIP(hipEventRecord(e1, stream));
+    if (timed) B_HIP(hipEventRecord(ev.e[1], stream));
     const bool f64 = dtype == SAP_F64, one = pl.one_block;
     const void *fn = one ? (f64 ? reinterpret_cast<const void *>(&k_batch_run<double>)
                                 : reinterpret_cast<const void *>(&k_batch_run<float>))
@@ -987,7 +994,7 @@ sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dty
             if (it < iters) std::swap(a.Pbuf, a.Pnext);
         }
     }
-    if (timed) B_HIP(hipEventRecord(e2, stream));
+    if (timed) B_HIP(hipEventRecord(ev.e[2], stream));
     hipLaunchKernelGGL(k_batch_storeP, dim3((unsigned)((kpmax * n + 255) / 256), (unsigned)n_problems), dim3(256), 0,
                        stream, a);
     if ((st = launched("k_batch_storeP")) != SAP_OK) return st;
@@ -999,13 +1006,10 @@ sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dty
     }
     if (timed) {
         float t1 = 0.0f, t2 = 0.0f;
-        B_HIP(hipEventElapsedTime(&t1, e0, e1));
-        B_HIP(hipEventElapsedTime(&t2, e1, e2));
+        B_HIP(hipEventElapsedTime(&t1, ev.e[0], ev.e[1]));
+        B_HIP(hipEventElapsedTime(&t2, ev.e[1], ev.e[2]));
         stats->init_ms = t1;
         stats->run_ms = t2;
-        (void)hipEventDestroy(e0);
-        (void)hipEventDestroy(e1);
-        (void)hipEventDestroy(e2);
     }
     (void)n;
     return SAP_OK;
