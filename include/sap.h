@@ -285,8 +285,9 @@ sap_status sap_profile_read(sap_handle h, sap_profile_t *out);
  * threshold l of Sec. 7 to see through noise.  sap_batch_run runs B such
  * problems at once, iters updates and iters+1 evaluations each: two launches
  * per iteration for the whole batch, every problem with its own workgroups in
- * both, or, where no set has more than 64 points, one launch with one
- * workgroup per problem.
+ * both, or, where every set is small (up to 64 points, up to 256 where that is
+ * faster), one launch with one workgroup per problem.  The results are the
+ * same bits either way.
  *
  * A problem is Algorithm 1 on a point set S_s (rows of X listed by
  * set_points[set_offsets[s] .. set_offsets[s+1]), in that order; pairs and

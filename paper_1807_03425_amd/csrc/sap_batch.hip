@@ -391,8 +391,11 @@ __device__ __forceinline__ BatchBound batch_bound(const BatchStat &bs, int n, in
 // Pass block lb of a problem: wavefront w takes the quarter tiles 4 lb + w, +
 // 4 npass, ... (every load of an item is independent: tile coordinates are
 // computed, not loaded), then the block's wavefronts share the rescoring of
-// its window pairs.  Every thread of the block calls it and gets the result.
-template <int KP, typename TX>
+// its window pairs.  PF: the next item's loads are issued before the current
+// one's arithmetic, for a block that is alone on its compute unit (with the
+// other blocks of a pass they would only cost registers).  Every thread of
+// the block calls it and gets the result.
+template <int KP, bool PF, typename TX>
 __device__ __forceinline__ Partial batch_pass_block(const BatchArgs &a, const BatchDesc &d, int lb, BatchLds &L,
                                                     Partial *out) {
     constexpr int NY = (16 * KP + kWave - 1) / kWave;   // doubles of an item's y_i rows per lane
@@ -411,31 +414,47 @@ __device__ __forceinline__ Partial batch_pass_block(const BatchArgs &a, const Ba
     CandList cl{L.cij[wv], L.ckey[wv], 0, a.cap, 0, kKeyNone};
     uint32_t kmin = kKeyNone;
     double *yl = L.y[wv];
-    for (int64_t h = (int64_t)lb * (kPairBlock / kWave) + wv; h < nitem; h += (int64_t)d.npass * (kPairBlock / kWave)) {
-        const int64_t t = h >> 2;
-        const int q = (int)(h & 3);
+    struct ItemLoads {
+        float4 w4[4];
+        double yr[NY], yj[KP];
+        int32_t row0, col;
+    };
+    auto fetch = [&](int64_t hh, ItemLoads &o) __attribute__((always_inline)) {
+        const int64_t t = hh >> 2;
+        const int q = (int)(hh & 3);
         const int2 tc = tile_of_index(t, d.nb);
         const float4 *tp = wt + t * (kTileElems / 4) + q * 256 + lane;
-        float4 w4[4];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) w4[g] = tp[g * 64];
-        const int32_t row0 = tc.x * kTile + 16 * q, col = tc.y * kTile + lane;
-        const double *ysrc = Y + (int64_t)row0 * KP;
-        double yr[NY], yj[KP];
+        for (int g = 0; g < 4; ++g) o.w4[g] = tp[g * 64];
+        o.row0 = tc.x * kTile + 16 * q;
+        o.col = tc.y * kTile + lane;
+        const double *ysrc = Y + (int64_t)o.row0 * KP;
 #pragma unroll
         for (int u = 0; u < NY; ++u) {
             const int f = lane + u * kWave;
-            yr[u] = ysrc[f < 16 * KP ? f : 0];
+            o.yr[u] = ysrc[f < 16 * KP ? f : 0];
         }
 #pragma unroll
-        for (int c = 0; c < KP; ++c) yj[c] = Y[(int64_t)col * KP + c];
+        for (int c = 0; c < KP; ++c) o.yj[c] = Y[(int64_t)o.col * KP + c];
+    };
+    ItemLoads cur, nxt;
+    int64_t h = (int64_t)lb * (kPairBlock / kWave) + wv;
+    const int64_t hstep = (int64_t)d.npass * (kPairBlock / kWave);
+    if constexpr (PF) {
+        if (h < nitem) fetch(h, cur);
+        nxt = cur;
+    }
+    for (; h < nitem; h += hstep) {
+        if constexpr (!PF) fetch(h, cur);
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int u = 0; u < NY; ++u) {
             const int f = lane + u * kWave;
-            if (f < 16 * KP) yl[f] = yr[u];
+            if (f < 16 * KP) yl[f] = cur.yr[u];
         }
         __builtin_amdgcn_wave_barrier();
+        if constexpr (PF)
+            if (h + hstep < nitem) fetch(h + hstep, nxt);
         uint32_t key[16];
         uint32_t lmin = kKeyNone;
 #pragma unroll
@@ -444,10 +463,10 @@ __device__ __forceinline__ Partial batch_pass_block(const BatchArgs &a, const Ba
             double acc = 0.0;
 #pragma unroll
             for (int c = 0; c < KP; ++c) {
-                const double t2 = yi[c] - yj[c];
+                const double t2 = yi[c] - cur.yj[c];
                 acc = __builtin_fma(t2, t2, acc);
             }
-            const float4 &wg = w4[e >> 2];
+            const float4 &wg = cur.w4[e >> 2];
             const float wv4 = (e & 3) == 0 ? wg.x : (e & 3) == 1 ? wg.y : (e & 3) == 2 ? wg.z : wg.w;
             key[e] = __float_as_uint((float)(acc * (double)wv4));
             lmin = min(lmin, key[e]);
@@ -455,6 +474,7 @@ __device__ __forceinline__ Partial batch_pass_block(const BatchArgs &a, const Ba
         const uint32_t m = wave_min_u32_fast(lmin);
         kmin = min(kmin, m);
         const uint32_t T2 = item_window(block_run_min(&L.run, m), bd.wa, bd.wb);
+        const int32_t row0 = cur.row0, col = cur.col;
         if (m <= T2)
             emit_cands(cl, key, lmin, T2,
                        [=](int e, int32_t &i, int32_t &j) __attribute__((always_inline)) {
@@ -463,6 +483,7 @@ __device__ __forceinline__ Partial batch_pass_block(const BatchArgs &a, const Ba
                        },
                        wb);
         __builtin_amdgcn_wave_barrier();
+        if constexpr (PF) cur = nxt;
     }
     // the window pairs of the block's minimum in FP64 from X, every fourth of
     // the four lists per wavefront (as finish_pass_block)
@@ -496,11 +517,11 @@ __global__ __launch_bounds__(kPairBlock, 3) void k_batch_pass(BatchArgs a) {
     const BatchDesc d = a.desc[bl.x];
     Partial *out = a.part + d.part_off + bl.y;
     switch (d.kp) {
-        case 2: batch_pass_block<2, TX>(a, d, bl.y, L, out); break;
-        case 4: batch_pass_block<4, TX>(a, d, bl.y, L, out); break;
-        case 8: batch_pass_block<8, TX>(a, d, bl.y, L, out); break;
-        case 12: batch_pass_block<12, TX>(a, d, bl.y, L, out); break;
-        default: batch_pass_block<16, TX>(a, d, bl.y, L, out); break;
+        case 2: batch_pass_block<2, false, TX>(a, d, bl.y, L, out); break;
+        case 4: batch_pass_block<4, false, TX>(a, d, bl.y, L, out); break;
+        case 8: batch_pass_block<8, false, TX>(a, d, bl.y, L, out); break;
+        case 12: batch_pass_block<12, false, TX>(a, d, bl.y, L, out); break;
+        default: batch_pass_block<16, false, TX>(a, d, bl.y, L, out); break;
     }
 }
 
@@ -581,7 +602,7 @@ template <> struct KRange<16> { static constexpr int lo = 13, hi = 16; };
 
 // A whole run of problem b in one block (P stays in LDS and, for the
 // rescoring, in its first buffer).
-template <int KP, typename TX>
+template <int KP, bool PF, typename TX>
 __device__ __forceinline__ void batch_run_block(BatchArgs &a, const BatchDesc &d, int b, double *sm, BatchLds &L) {
     const int32_t *idx = a.pts + d.pt_off;
     double *P = a.Pbuf + d.P_off;
@@ -590,33 +611,34 @@ __device__ __forceinline__ void batch_run_block(BatchArgs &a, const BatchDesc &d
         __syncthreads();   // P' (and, before that, the reads of Y) are done
         batch_Y<TX>(a, d, sm, 0, 4 * d.nb);
         __syncthreads();
-        const Partial f = batch_pass_block<KP, TX>(a, d, 0, L, nullptr);
+        const Partial f = batch_pass_block<KP, PF, TX>(a, d, 0, L, nullptr);
         if (threadIdx.x == 0) batch_record(a, d, b, it, f);
-        // (a set without a kept pair keeps P: the same evaluation each time)
-        if (it < a.iters && f.r < __builtin_huge_val())
+        if (!(f.r < __builtin_huge_val())) {
+            // a set without a kept pair keeps P: the other entries repeat this one
+            if (threadIdx.x == 0)
+                for (int r = it + 1; r <= a.iters; ++r) batch_record(a, d, b, r, f);
+            return;
+        }
+        if (it < a.iters)
             batch_update<TX, KRange<KP>::lo, KRange<KP>::hi>(static_cast<const TX *>(a.X), a.ldx, a.n, d.k, P, d.alpha,
                                                              d.rule, idx[f.i], idx[f.j], sm);
     }
 }
 
-// Batches of sets of at most 64 points (one tile, an item per wavefront): one
-// block per problem runs all its iterations.  There the two launches of an
-// iteration cost more than the block barriers between its phases: a call on 30
-// problems of 40 points, n = 15, 40 iterations, takes 0.84 ms here and 1.18 ms
-// in two launches; from 65 points (three tiles) on the launches are as fast
-// (three problems of 65 points, one block each 0.84 ms, launches 0.82) and
-// with more points much faster.
-template <typename TX>
+// Batches of small sets (one_block_per_problem): one block per problem runs all
+// its iterations.  PF: sets of more than one tile (an item per wavefront: the
+// look ahead would cost it 3%).
+template <typename TX, bool PF>
 __global__ __launch_bounds__(kPairBlock) void k_batch_run(BatchArgs a) {
     extern __shared__ __align__(16) double sm_batch[];
     __shared__ BatchLds L;
     const BatchDesc d = a.desc[blockIdx.x];
     switch (d.kp) {
-        case 2: batch_run_block<2, TX>(a, d, blockIdx.x, sm_batch, L); break;
-        case 4: batch_run_block<4, TX>(a, d, blockIdx.x, sm_batch, L); break;
-        case 8: batch_run_block<8, TX>(a, d, blockIdx.x, sm_batch, L); break;
-        case 12: batch_run_block<12, TX>(a, d, blockIdx.x, sm_batch, L); break;
-        default: batch_run_block<16, TX>(a, d, blockIdx.x, sm_batch, L); break;
+        case 2: batch_run_block<2, PF, TX>(a, d, blockIdx.x, sm_batch, L); break;
+        case 4: batch_run_block<4, PF, TX>(a, d, blockIdx.x, sm_batch, L); break;
+        case 8: batch_run_block<8, PF, TX>(a, d, blockIdx.x, sm_batch, L); break;
+        case 12: batch_run_block<12, PF, TX>(a, d, blockIdx.x, sm_batch, L); break;
+        default: batch_run_block<16, PF, TX>(a, d, blockIdx.x, sm_batch, L); break;
     }
 }
 
@@ -662,7 +684,7 @@ struct BatchPlan {
     std::vector<int32_t> pts;
     std::vector<double> minlen;
     std::vector<BatchDesc> desc;
-    bool one_block = false;  // every set has at most 64 points: k_batch_run
+    bool one_block = false;  // one block per problem and one launch: k_batch_run
     std::vector<int2> pass_blk, sel_blk;
     int64_t ntiles_all = 0, P_total = 0, Y_total = 0, P0_total = 0;
     size_t lds = 0;
@@ -675,31 +697,65 @@ struct BatchPlan {
                              // scratch_bytes reports and the fixed scratch's limit counts
 };
 
+// Whether one block per problem runs all its iterations (k_batch_run) rather
+// than two launches per iteration with more blocks.  The block's iteration
+// costs the same for any number of problems up to one per compute unit, and
+// grows with the tiles and k; the launches cost 12 us at least, little more
+// with the tiles while compute units are idle, and grow with the problems,
+// whose blocks repeat the selection.  us per iteration, block and launches:
+//   one 64-point block, k <= 12: the block (a call on 30 problems of 40 points,
+//     n = 15, 40 iterations 0.84 ms and 1.18 ms; k = 16, n = 64 51.9 and 48.4);
+//   two, k <= 4, n <= 128: the block (n = 15, k = 2: 1 problem 9.8 and 13.1,
+//     200 10.4 and 16.1, 600 30.4 and 34.8; n = 128, k = 4: 1 problem 18.6 and
+//     17.5, 30 18.8 and 18.7; n = 200, k = 5: 30 25.9 and 21.5);
+//   more than half a problem per compute unit, up to one: the block for two
+//     and k <= 12 (200 problems, n = 15, k = 12 28.2 and 31.8; n = 200, k =
+//     16 77 and 74), three and k <= 8 (n = 15, k = 6 25.0 and 27.9; k = 12
+//     41.1 and 40.3) and four and k <= 4 (n = 30, k = 4 28.1 and 32.5; k = 6
+//     37.1 and 36.5).
+bool one_block_per_problem(const BatchPlan &pl, int n, int cus) {
+    int nb = 0, k = 0;
+    for (const BatchProb &p : pl.probs) {
+        nb = std::max(nb, pl.sets[p.set].nb);
+        k = std::max(k, p.k);
+    }
+    const int64_t np = (int64_t)pl.probs.size();
+    if ((nb == 1 && k <= 12) || (nb == 2 && k <= 4 && n <= 128)) return true;
+    if (np > cus || 2 * np <= cus) return false;
+    return (nb == 2 && k <= 12) || (nb == 3 && k <= 8) || (nb == 4 && k <= 4);
+}
+
 // Blocks of the two launches.  Pass: one round of resident blocks (three per
 // compute unit) dealt to the problems by their quarter tiles, at most one per
 // four of them; where every problem gets one block there are as many as
 // problems.  Selection: every block repeats its problem's selection and
 // update, so there are about as many as compute units (its registers allow one
-// block on each), each with whole 64-row groups of Y.
-void plan_blocks(BatchPlan &pl, int cus) {
+// block on each), each with whole 64-row groups of Y: the fewest groups that
+// take one round (200 problems of five groups: five per block, 200 blocks, and
+// not four with 400: 38.5 and 30.7 us per iteration at n = 15, k = 2).
+void plan_blocks(BatchPlan &pl, int n, int cus) {
     const int64_t slots = 3 * (int64_t)cus;
     int64_t items = 0, groups = 0, parts = 0;
     for (const BatchProb &p : pl.probs) {
         items += 4ll * pl.sets[p.set].ntiles;
         groups += pl.sets[p.set].nb;
     }
-    const int32_t gt = (int32_t)std::max<int64_t>(1, (groups + cus - 1) / cus);
-    pl.one_block = true;
+    int32_t gt = (int32_t)std::max<int64_t>(1, (groups + cus - 1) / cus);
+    for (int32_t g = gt; g <= 2 * gt; ++g) {
+        int64_t blocks = 0;
+        for (const BatchProb &p : pl.probs) blocks += (pl.sets[p.set].nb + g - 1) / g;
+        if (blocks <= cus) { gt = g; break; }
+    }
+    pl.one_block = one_block_per_problem(pl, n, cus);
     pl.desc.resize(pl.probs.size());
     for (size_t b = 0; b < pl.probs.size(); ++b) {
         const BatchProb &p = pl.probs[b];
         const BatchSet &st = pl.sets[p.set];
         BatchDesc &g = pl.desc[b];
         g = BatchDesc{st.pt_off, st.tile_off, p.P_off, p.Y_off, 0, p.alpha, p.set, p.k, p.kp, p.rule,
-                      st.M, st.nb, st.ntiles, 0, 0, 0};
-        pl.one_block = pl.one_block && st.nb == 1;
+                      st.M, st.nb, st.ntiles, 1, gt, 0};
+        if (pl.one_block) continue;
         g.npass = (int32_t)std::max<int64_t>(1, std::min<int64_t>(st.ntiles, slots * 4 * st.ntiles / items));
-        g.gt = gt;
         g.part_off = parts;
         parts += g.npass;
         for (int q = 0; q < g.npass; ++q) pl.pass_blk.push_back(make_int2((int)b, q));
@@ -780,7 +836,7 @@ sap_status plan_batch(const void *X, int32_t dtype, int64_t N, int32_t n, int64_
         (void)hipGetLastError();
         cus = 256;
     }
-    plan_blocks(pl, cus);
+    plan_blocks(pl, n, cus);
     size_t off = 0, extra = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off = (size_t)align_up((int64_t)(off + bytes), 256); return o; };
     auto more = [&](size_t bytes) { const size_t o = take(bytes); extra += off - o; return o; };
@@ -963,26 +1019,22 @@ sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dty
     }
     if (timed) B_HIP(hipEventRecord(ev.e[1], stream));
     const bool f64 = dtype == SAP_F64, one = pl.one_block;
-    const void *fn = one ? (f64 ? reinterpret_cast<const void *>(&k_batch_run<double>)
-                                : reinterpret_cast<const void *>(&k_batch_run<float>))
-                         : (f64 ? reinterpret_cast<const void *>(&k_batch_select<double>)
-                                : reinterpret_cast<const void *>(&k_batch_select<float>));
+    int nbmax = 0;
+    for (const BatchProb &p : pl.probs) nbmax = std::max(nbmax, pl.sets[p.set].nb);
+    auto *const run = nbmax > 1 ? (f64 ? &k_batch_run<double, true> : &k_batch_run<float, true>)
+                                : (f64 ? &k_batch_run<double, false> : &k_batch_run<float, false>);
+    auto *const sel = f64 ? &k_batch_select<double> : &k_batch_select<float>;
+    const void *fn = one ? reinterpret_cast<const void *>(run) : reinterpret_cast<const void *>(sel);
     B_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds));
     // Y of the starts, then per iteration the pass and the selection (with the
     // update and the next Y); the last evaluation is only recorded
     const dim3 gp((unsigned)pl.pass_blk.size()), gs((unsigned)pl.sel_blk.size());
-    auto select = [&](int it, int sel, int step) {
-        if (f64)
-            hipLaunchKernelGGL(k_batch_select<double>, gs, dim3(kPairBlock), (uint32_t)pl.lds, stream, a, it, sel, step);
-        else
-            hipLaunchKernelGGL(k_batch_select<float>, gs, dim3(kPairBlock), (uint32_t)pl.lds, stream, a, it, sel, step);
+    auto select = [&](int it, int evaluated, int step) {
+        hipLaunchKernelGGL(sel, gs, dim3(kPairBlock), (uint32_t)pl.lds, stream, a, it, evaluated, step);
         return launched("k_batch_select");
     };
     if (one) {
-        if (f64)
-            hipLaunchKernelGGL(k_batch_run<double>, dim3((unsigned)n_problems), dim3(kPairBlock), (uint32_t)pl.lds, stream, a);
-        else
-            hipLaunchKernelGGL(k_batch_run<float>, dim3((unsigned)n_problems), dim3(kPairBlock), (uint32_t)pl.lds, stream, a);
+        hipLaunchKernelGGL(run, dim3((unsigned)n_problems), dim3(kPairBlock), (uint32_t)pl.lds, stream, a);
         if ((st = launched("k_batch_run")) != SAP_OK) return st;
     } else {
         if ((st = select(0, 0, 0)) != SAP_OK) return st;

@@ -316,3 +316,54 @@ def test_starts_in_host_memory(noalloc):
     assert rc != 0 and not P.any() and not tr.any()
     got = call(P0.to(DEV))
     assert got[0] == 0 and np.array_equal(got[1], want[1]) and np.array_equal(got[2], want[2])
+
+
+@pytest.mark.parametrize("M,n,k,count", [
+    (64, 20, 12, 3), (64, 20, 13, 3),                             # one tile: k up to 12 in one launch
+    (65, 128, 4, 3), (128, 129, 4, 2), (128, 70, 5, 2),           # two 64-point blocks: k <= 4, n <= 128
+    (100, 33, 9, 129), (100, 15, 13, 129), (128, 15, 6, 256), (65, 15, 6, 257),
+    (129, 15, 8, 130), (192, 15, 9, 130), (193, 15, 4, 130), (256, 17, 5, 130),
+    (320, 15, 2, 129), (257, 15, 2, 129)])                        # launches: groups of Y rows per block
+def test_one_block_per_problem_equals_launches(M, n, k, count):
+    """The same problems in a batch of their own and beside a large set, which
+    takes the whole batch to two launches per iteration: traces and P bit for
+    bit, on both sides of every line of the rule."""
+    rng = np.random.default_rng(M + n + k + count)
+    N = 700
+    X = torch.from_numpy(rng.standard_normal((N, n)).astype(np.float32 if M % 2 else np.float64)).to(DEV)
+    sets = [rng.choice(N, M, replace=False) for _ in range(min(count, 4))] + [np.arange(N)]
+    probs = [dict(set=b % (len(sets) - 1), k=k, rule=("literal", "normalized")[b % 2]) for b in range(count)]
+    P0s = [sap_inputs.random_orthonormal(rng, n, k) for _ in range(count)]
+    a = batch_run(X, sets[:-1], probs, P0s, 5)
+    b = batch_run(X, sets, probs + [dict(set=len(sets) - 1, k=1)], P0s + [np.eye(n)[:, :1]], 5)
+    for key in ("min", "ij", "certified"):
+        assert torch.equal(a[key], b[key][:count]), key
+    assert all(torch.equal(p, q) for p, q in zip(a["P"], b["P"]))
+    assert int(a["certified"].min()) == 1
+
+
+def test_batches_of_small_sets_take_one_launch():
+    """200 problems of 100 points take 10 us per iteration in one block each,
+    16 in two launches; beside a set of 300 points they take the launches."""
+    rng = np.random.default_rng(8)
+    X = torch.from_numpy(rng.standard_normal((1000, 15))).to(DEV)
+    sets = [rng.choice(1000, 100, replace=False) for _ in range(200)]
+    probs = [dict(set=b, k=2) for b in range(200)]
+    P0s = [sap_inputs.random_orthonormal(rng, 15, 2) for _ in range(201)]
+    ms = lambda s, p: min(batch_run(X, s, p, P0s[:len(p)], 40)["stats"]["run_ms"] for _ in range(5))
+    one, two = ms(sets, probs), ms(sets + [np.arange(300)], probs + [dict(set=200, k=2)])
+    print(f"[batch] 200 problems of 100 points: {25 * one:.1f} us per iteration, beside a larger set {25 * two:.1f}")
+    assert one < 0.8 * two
+
+
+def test_no_kept_pair_repeats_the_entry():
+    """A set whose pairs are all shorter than its threshold, alone (one launch)
+    and among others: min = inf, (-1, -1), not certified, P unchanged."""
+    rng = np.random.default_rng(4)
+    X = torch.from_numpy(rng.standard_normal((300, 6))).to(DEV)
+    P0 = sap_inputs.random_orthonormal(rng, 6, 3)
+    for extra in (0, 1):
+        out = batch_run(X, [np.arange(50)] + [np.arange(300)] * extra, [dict(set=0, k=3)] + [dict(set=1, k=3)] * extra,
+                        [P0] * (1 + extra), 7, set_min_len=[1e3] + [0.0] * extra)
+        assert bool(torch.isinf(out["min"][0]).all()) and bool((out["ij"][0] == -1).all())
+        assert not out["certified"][0].any() and np.array_equal(out["P"][0].cpu().numpy(), P0)
