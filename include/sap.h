@@ -313,9 +313,9 @@ typedef struct {
     double run_ms;      /* device time of the run (all problems, all iterations) */
     int64_t n_pairs;    /* kept pairs summed over the problems' sets          */
     int64_t scratch_bytes; /* device scratch of the batch's data (what
-                              sap_batch_run_noalloc limits); the run's block
-                              tables, block results and second copy of P come
-                              on top                                         */
+                              sap_batch_run_noalloc limits); in a run of two
+                              launches per iteration block tables, block
+                              results and a second copy of P come on top     */
 } sap_batch_stats;
 
 /* Run the batch.  Host arrays: set_offsets (n_sets + 1, increasing, sets of
@@ -345,12 +345,14 @@ sap_status sap_batch_run(const void *X, int32_t dtype, int64_t N, int32_t n, int
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * call as sap_batch_run -- same arguments, same kernels, same results --
- * except that its device scratch is a fixed array inside the library (each GPU
- * the library runs on holds its 65 MiB until the process ends), and that it
- * creates no events (stats, if given, reports init_ms = run_ms = -1).  It
- * calls no hipMalloc or hipFree.  A batch whose data need more than 32 MiB
- * of scratch (stats->scratch_bytes of sap_batch_run tells) fails with
- * SAP_ERR_CAPACITY.  Every call on a GPU uses that GPU's one array and
+ * except that its device scratch is a fixed array inside the library, 32 MiB
+ * per GPU (each GPU the library runs on holds it until the process ends), and
+ * that it creates no events (stats, if given, reports init_ms = run_ms = -1).
+ * It calls no hipMalloc or hipFree.  A batch whose data need more scratch than
+ * the array holds (stats->scratch_bytes of sap_batch_run tells) fails with
+ * SAP_ERR_CAPACITY; one that fits only without the block tables, block results
+ * and second copy of P runs with one workgroup per problem (the same results).
+ * Every call on a GPU uses that GPU's one array and
  * leaves its contents behind (each call rewrites what it reads, and clears
  * its counters with a kernel): calls that overlap on one GPU (concurrent
  * streams or threads) race, and must be serialised by the caller. */

@@ -29,8 +29,9 @@
 //
 // Scratch (device): per-set index lists, tile tables and 1/d^2 tiles (FP32,
 // the single-problem layout), per-set mean / radius / largest kept 1/d^2 /
-// pair counts, per-problem P twice (kp x n FP64, rows >= k zero; the selection
-// reads one and writes the other) and Y (Mpad x kp FP64), block results.
+// pair counts, per-problem P (kp x n FP64, rows >= k zero) and Y (Mpad x kp
+// FP64); for the two launches P twice (the selection reads one and writes the
+// other), block tables and block results.
 #define SAP_KINST 1
 
 #include <algorithm>
@@ -88,6 +89,12 @@ struct BatchDesc {
     int32_t M, nb, ntiles;
     int32_t npass, gt, pad;
 };
+
+// The record of a problem with one block.
+__host__ __device__ inline BatchDesc batch_desc(const BatchProb &p, const BatchSet &st) {
+    return BatchDesc{st.pt_off, st.tile_off, p.P_off, p.Y_off, 0, p.alpha, p.set, p.k, p.kp, p.rule,
+                     st.M, st.nb, st.ntiles, 1, 1, 0};
+}
 
 // a start's check: max |P^T P - I| and whether an entry is NaN or Inf
 struct BatchCheck {
@@ -241,7 +248,7 @@ __global__ __launch_bounds__(256, 4) void k_batch_invd2(BatchArgs a, int64_t nti
     }
 }
 
-// P0 blocks (n x k row-major) -> per-problem P (kp x n, rows >= k zero), both buffers
+// P0 blocks (n x k row-major) -> per-problem P (kp x n, rows >= k zero), every buffer
 __global__ void k_batch_loadP(BatchArgs a) {
     const BatchProb pr = a.probs[blockIdx.y];
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
@@ -250,7 +257,7 @@ __global__ void k_batch_loadP(BatchArgs a) {
     const int q = e / n, l = e % n;
     const double v = q < pr.k ? a.P0[pr.P0_off + (int64_t)l * pr.k + q] : 0.0;
     a.Pbuf[pr.P_off + e] = v;
-    a.Pnext[pr.P_off + e] = v;   // (its rows >= k stay zero)
+    if (a.Pnext) a.Pnext[pr.P_off + e] = v;   // (its rows >= k stay zero)
 }
 
 // The starts: one block per problem, entry (x, y) of P0^T P0 per thread, the
@@ -259,9 +266,9 @@ __global__ void k_batch_loadP(BatchArgs a) {
 __global__ __launch_bounds__(256) void k_batch_checkP(BatchArgs a) {
     __shared__ unsigned long long s_err;
     __shared__ int s_bad;
-    const BatchDesc d = a.desc[blockIdx.x];
-    const double *P = a.P0 + a.probs[blockIdx.x].P0_off;
-    const int n = a.n, k = d.k;
+    const BatchProb pr = a.probs[blockIdx.x];
+    const double *P = a.P0 + pr.P0_off;
+    const int n = a.n, k = pr.k;
     if (threadIdx.x == 0) { s_err = 0ull; s_bad = 0; }
     __syncthreads();
     int bad = 0;
@@ -632,7 +639,8 @@ template <typename TX, bool PF>
 __global__ __launch_bounds__(kPairBlock) void k_batch_run(BatchArgs a) {
     extern __shared__ __align__(16) double sm_batch[];
     __shared__ BatchLds L;
-    const BatchDesc d = a.desc[blockIdx.x];
+    const BatchProb pr = a.probs[blockIdx.x];
+    const BatchDesc d = batch_desc(pr, a.sets[pr.set]);
     switch (d.kp) {
         case 2: batch_run_block<2, PF, TX>(a, d, blockIdx.x, sm_batch, L); break;
         case 4: batch_run_block<4, PF, TX>(a, d, blockIdx.x, sm_batch, L); break;
@@ -689,12 +697,14 @@ struct BatchPlan {
     int64_t ntiles_all = 0, P_total = 0, Y_total = 0, P0_total = 0;
     size_t lds = 0;
     // scratch offsets (bytes); the tables the host fills come first, one copy
-    size_t o_pts, o_sets, o_probs, o_tiles, o_minlen, o_desc, o_pblk, o_sblk, o_w, o_mu, o_stat, o_chk, o_P, o_Y,
-        o_part, o_P2;
+    // (the starts' checks lie where Y will: they are read back before it is written)
+    size_t o_pts, o_sets, o_probs, o_tiles, o_minlen, o_desc, o_pblk, o_sblk, o_w, o_mu, o_P, o_stat, o_Y, o_part,
+        o_P2;
     std::vector<char> tables;   // the tables' host copy
     size_t total = 0;        // bytes of the scratch
-    size_t counted = 0;      // without the block tables, the block results and the second P: what
-                             // scratch_bytes reports and the fixed scratch's limit counts
+    size_t counted = 0;      // with one block per problem: without the block tables, the block results
+                             // and the second P.  What scratch_bytes reports and the fixed scratch's
+                             // limit counts
 };
 
 // Whether one block per problem runs all its iterations (k_batch_run) rather
@@ -733,7 +743,7 @@ bool one_block_per_problem(const BatchPlan &pl, int n, int cus) {
 // block on each), each with whole 64-row groups of Y: the fewest groups that
 // take one round (200 problems of five groups: five per block, 200 blocks, and
 // not four with 400: 38.5 and 30.7 us per iteration at n = 15, k = 2).
-void plan_blocks(BatchPlan &pl, int n, int cus) {
+void plan_blocks(BatchPlan &pl, int cus) {
     const int64_t slots = 3 * (int64_t)cus;
     int64_t items = 0, groups = 0, parts = 0;
     for (const BatchProb &p : pl.probs) {
@@ -746,21 +756,58 @@ void plan_blocks(BatchPlan &pl, int n, int cus) {
         for (const BatchProb &p : pl.probs) blocks += (pl.sets[p.set].nb + g - 1) / g;
         if (blocks <= cus) { gt = g; break; }
     }
-    pl.one_block = one_block_per_problem(pl, n, cus);
     pl.desc.resize(pl.probs.size());
     for (size_t b = 0; b < pl.probs.size(); ++b) {
         const BatchProb &p = pl.probs[b];
         const BatchSet &st = pl.sets[p.set];
         BatchDesc &g = pl.desc[b];
-        g = BatchDesc{st.pt_off, st.tile_off, p.P_off, p.Y_off, 0, p.alpha, p.set, p.k, p.kp, p.rule,
-                      st.M, st.nb, st.ntiles, 1, gt, 0};
-        if (pl.one_block) continue;
+        g = batch_desc(p, st);
         g.npass = (int32_t)std::max<int64_t>(1, std::min<int64_t>(st.ntiles, slots * 4 * st.ntiles / items));
+        g.gt = gt;
         g.part_off = parts;
         parts += g.npass;
         for (int q = 0; q < g.npass; ++q) pl.pass_blk.push_back(make_int2((int)b, q));
         for (int q = 0; q * gt < st.nb; ++q) pl.sel_blk.push_back(make_int2((int)b, q));
     }
+}
+
+// The places of everything in the scratch, and the tables' copy: for one block
+// per problem (pl.one_block), or with the block tables, the block results and
+// the second P of the two launches.
+void plan_layout(BatchPlan &pl, int n) {
+    const size_t n_sets = pl.sets.size(), n_problems = pl.probs.size();
+    size_t off = 0, extra = 0;
+    auto take = [&](size_t bytes) { const size_t o = off; off = (size_t)align_up((int64_t)(off + bytes), 256); return o; };
+    auto more = [&](size_t bytes) { const size_t o = off; if (!pl.one_block) { take(bytes); extra += off - o; } return o; };
+    pl.o_pts = take(sizeof(int32_t) * pl.pts.size());
+    pl.o_sets = take(sizeof(BatchSet) * n_sets);
+    pl.o_probs = take(sizeof(BatchProb) * n_problems);
+    pl.o_tiles = take(sizeof(int4) * pl.ntiles_all);
+    pl.o_minlen = take(sizeof(double) * n_sets);
+    pl.o_desc = more(sizeof(BatchDesc) * n_problems);
+    pl.o_pblk = more(sizeof(int2) * pl.pass_blk.size());
+    pl.o_sblk = more(sizeof(int2) * pl.sel_blk.size());
+    pl.tables.resize(off);
+    pl.o_w = take(sizeof(float) * (size_t)pl.ntiles_all * kTileElems);
+    pl.o_mu = take(sizeof(double) * n_sets * n);
+    pl.o_P = take(sizeof(double) * (size_t)pl.P_total);
+    pl.o_stat = take(sizeof(BatchStat) * n_sets);
+    pl.o_Y = take(sizeof(double) * (size_t)pl.Y_total);
+    pl.o_part = more(sizeof(Partial) * pl.pass_blk.size());
+    pl.o_P2 = more(sizeof(double) * (size_t)pl.P_total);
+    pl.total = off;
+    pl.counted = off - extra;
+    // (the copy's source: it lives as long as the plan, past the call's last wait)
+    auto put = [&](size_t at, const void *p, size_t bytes) { if (bytes) std::memcpy(pl.tables.data() + at, p, bytes); };
+    put(pl.o_pts, pl.pts.data(), sizeof(int32_t) * pl.pts.size());
+    put(pl.o_sets, pl.sets.data(), sizeof(BatchSet) * n_sets);
+    put(pl.o_probs, pl.probs.data(), sizeof(BatchProb) * n_problems);
+    put(pl.o_tiles, pl.tiles.data(), sizeof(int4) * pl.tiles.size());
+    put(pl.o_minlen, pl.minlen.data(), sizeof(double) * n_sets);
+    if (pl.one_block) return;
+    put(pl.o_desc, pl.desc.data(), sizeof(BatchDesc) * n_problems);
+    put(pl.o_pblk, pl.pass_blk.data(), sizeof(int2) * pl.pass_blk.size());
+    put(pl.o_sblk, pl.sel_blk.data(), sizeof(int2) * pl.sel_blk.size());
 }
 
 sap_status plan_batch(const void *X, int32_t dtype, int64_t N, int32_t n, int64_t ldx, int32_t n_sets,
@@ -836,39 +883,9 @@ sap_status plan_batch(const void *X, int32_t dtype, int64_t N, int32_t n, int64_
         (void)hipGetLastError();
         cus = 256;
     }
-    plan_blocks(pl, n, cus);
-    size_t off = 0, extra = 0;
-    auto take = [&](size_t bytes) { const size_t o = off; off = (size_t)align_up((int64_t)(off + bytes), 256); return o; };
-    auto more = [&](size_t bytes) { const size_t o = take(bytes); extra += off - o; return o; };
-    pl.o_pts = take(sizeof(int32_t) * npts);
-    pl.o_sets = take(sizeof(BatchSet) * n_sets);
-    pl.o_probs = take(sizeof(BatchProb) * n_problems);
-    pl.o_tiles = take(sizeof(int4) * pl.ntiles_all);
-    pl.o_minlen = take(sizeof(double) * n_sets);
-    pl.o_desc = more(sizeof(BatchDesc) * n_problems);
-    pl.o_pblk = more(sizeof(int2) * pl.pass_blk.size());
-    pl.o_sblk = more(sizeof(int2) * pl.sel_blk.size());
-    pl.tables.resize(off);
-    pl.o_w = take(sizeof(float) * (size_t)pl.ntiles_all * kTileElems);
-    pl.o_mu = take(sizeof(double) * (size_t)n_sets * n);
-    pl.o_stat = take(sizeof(BatchStat) * n_sets);
-    pl.o_chk = more(sizeof(BatchCheck) * n_problems);
-    pl.o_P = take(sizeof(double) * (size_t)pl.P_total);
-    pl.o_Y = take(sizeof(double) * (size_t)pl.Y_total);
-    pl.o_part = more(sizeof(Partial) * pl.pass_blk.size());
-    pl.o_P2 = more(sizeof(double) * (size_t)pl.P_total);
-    pl.total = off;
-    pl.counted = off - extra;
-    // (the copy's source: it lives as long as the plan, past the call's last wait)
-    auto put = [&](size_t at, const void *p, size_t bytes) { if (bytes) std::memcpy(pl.tables.data() + at, p, bytes); };
-    put(pl.o_pts, pl.pts.data(), sizeof(int32_t) * pl.pts.size());
-    put(pl.o_sets, pl.sets.data(), sizeof(BatchSet) * pl.sets.size());
-    put(pl.o_probs, pl.probs.data(), sizeof(BatchProb) * pl.probs.size());
-    put(pl.o_tiles, pl.tiles.data(), sizeof(int4) * pl.tiles.size());
-    put(pl.o_minlen, pl.minlen.data(), sizeof(double) * pl.minlen.size());
-    put(pl.o_desc, pl.desc.data(), sizeof(BatchDesc) * pl.desc.size());
-    put(pl.o_pblk, pl.pass_blk.data(), sizeof(int2) * pl.pass_blk.size());
-    put(pl.o_sblk, pl.sel_blk.data(), sizeof(int2) * pl.sel_blk.size());
+    pl.one_block = one_block_per_problem(pl, n, cus);
+    if (!pl.one_block) plan_blocks(pl, cus);
+    plan_layout(pl, n);
     (void)iters;
     return SAP_OK;
 }
@@ -885,7 +902,7 @@ sap_status check_P0(const BatchCheck *chk, int n_problems) {
 
 // Starts that no kernel can read where they lie: copied to the host (an error
 // where they are not memory of a device or pinned), checked there in
-// k_batch_checkP's order of sums, and put into both P buffers.
+// k_batch_checkP's order of sums, and put into every P buffer.
 sap_status load_starts_by_copy(const BatchPlan &pl, const double *P0, int n, double *Pbuf, double *Pnext,
                                std::vector<BatchCheck> &chk, hipStream_t stream) {
     std::vector<double> h((size_t)pl.P0_total), Pt((size_t)pl.P_total, 0.0);
@@ -906,7 +923,7 @@ sap_status load_starts_by_copy(const BatchPlan &pl, const double *P0, int n, dou
             for (int l = 0; l < n; ++l) Pt[(size_t)p.P_off + (size_t)q * n + l] = P[(size_t)l * p.k + q];
     }
     B_HIP(hipMemcpyAsync(Pbuf, Pt.data(), sizeof(double) * Pt.size(), hipMemcpyHostToDevice, stream));
-    B_HIP(hipMemcpyAsync(Pnext, Pt.data(), sizeof(double) * Pt.size(), hipMemcpyHostToDevice, stream));
+    if (Pnext) B_HIP(hipMemcpyAsync(Pnext, Pt.data(), sizeof(double) * Pt.size(), hipMemcpyHostToDevice, stream));
     B_HIP(hipStreamSynchronize(stream));   // (the host vector ends here)
     return SAP_OK;
 }
@@ -941,12 +958,12 @@ sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dty
     a.stat = reinterpret_cast<BatchStat *>(base + pl.o_stat);
     a.set_min_len = reinterpret_cast<const double *>(base + pl.o_minlen);
     a.desc = reinterpret_cast<const BatchDesc *>(base + pl.o_desc);
-    a.chk = reinterpret_cast<BatchCheck *>(base + pl.o_chk);
+    a.chk = reinterpret_cast<BatchCheck *>(base + pl.o_Y);
     a.pass_blk = reinterpret_cast<const int2 *>(base + pl.o_pblk);
     a.sel_blk = reinterpret_cast<const int2 *>(base + pl.o_sblk);
     a.part = reinterpret_cast<Partial *>(base + pl.o_part);
     a.Pbuf = reinterpret_cast<double *>(base + pl.o_P);
-    a.Pnext = reinterpret_cast<double *>(base + pl.o_P2);
+    a.Pnext = pl.one_block ? nullptr : reinterpret_cast<double *>(base + pl.o_P2);
     a.Ybuf = reinterpret_cast<double *>(base + pl.o_Y);
     a.P0 = P0;
     a.P_out = P_out;
@@ -1003,12 +1020,12 @@ sap_status run_batch(const BatchPlan &pl, char *base, const void *X, int32_t dty
     // inputs checked before the run: orthonormal starts, finite rows, kept pairs
     {
         // (the sets' statistics and the starts' checks lie one behind the other)
-        std::vector<char> back(pl.o_chk + sizeof(BatchCheck) * n_problems - pl.o_stat);
+        std::vector<char> back(pl.o_Y + sizeof(BatchCheck) * n_problems - pl.o_stat);
         B_HIP(hipMemcpyAsync(back.data(), base + pl.o_stat, back.size(), hipMemcpyDeviceToHost, stream));
         B_HIP(hipStreamSynchronize(stream));
         std::vector<BatchStat> hs(n_sets);
         std::memcpy(hs.data(), back.data(), sizeof(BatchStat) * n_sets);
-        if (in_place) std::memcpy(hc.data(), back.data() + (pl.o_chk - pl.o_stat), sizeof(BatchCheck) * n_problems);
+        if (in_place) std::memcpy(hc.data(), back.data() + (pl.o_Y - pl.o_stat), sizeof(BatchCheck) * n_problems);
         if ((st = check_P0(hc.data(), n_problems)) != SAP_OK) return st;
         int64_t kept = 0;
         for (int s = 0; s < n_sets; ++s) {
@@ -1100,13 +1117,11 @@ extern "C" sap_status sap_batch_run(const void *X, int32_t dtype, int64_t N, int
 // looked up once per device (hipGetSymbolAddress, with that device current)
 // and that address is what the kernels are given.  Each device holds its own
 // copy until the process ends; every call on one device shares it.
-// The limit counts a batch's data (BatchPlan::counted); the array has room
-// beside it for the second P (no larger than the first, which is counted) and
-// the block tables and results (under 200 bytes per problem, whose counted Y
-// is 1 KB at least, and under 100 per block of one round).
+// The limit counts a batch's data (BatchPlan::counted), which is all that one
+// block per problem needs; where what the two launches need beside it does not
+// fit, the batch runs that way.
 constexpr size_t kStaticScratchBytes = size_t(32) << 20;
-constexpr size_t kStaticArrayBytes = (size_t(65) << 20);
-static __device__ __align__(256) char scratch[kStaticArrayBytes];
+static __device__ __align__(256) char scratch[kStaticScratchBytes];
 
 namespace {
 std::mutex g_scratch_mu;
@@ -1141,9 +1156,13 @@ extern "C" sap_status sap_batch_run_noalloc(const void *X, int32_t dtype, int64_
     sap_status st = plan_batch(X, dtype, N, n, ldx, n_sets, set_offsets, set_points, set_min_len, n_problems, problems,
                                P0, iters, cand_cap, P_out, min_trace, pl);
     if (st != SAP_OK) return st;
-    if (pl.counted > kStaticScratchBytes || pl.total > kStaticArrayBytes)
+    if (pl.counted > kStaticScratchBytes)
         return bfail(SAP_ERR_CAPACITY, "sap_batch_run_noalloc: the batch needs %zu bytes of scratch, above the fixed %zu",
                      pl.counted, kStaticScratchBytes);
+    if (pl.total > kStaticScratchBytes) {
+        pl.one_block = true;
+        plan_layout(pl, n);
+    }
     hipStream_t s = static_cast<hipStream_t>(stream);
     char *base = nullptr;
     if ((st = static_scratch(&base)) != SAP_OK) return st;

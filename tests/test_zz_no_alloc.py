@@ -3,6 +3,10 @@ allocating one (sap_batch_run), through the C ABI: the same kernels on the
 same inputs must give the same traces and projections bit for bit, on two
 calls in a row (the second smaller, so that it runs on the array the first
 one left behind), and a batch above the fixed scratch fails cleanly."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -61,3 +65,47 @@ def test_noalloc_rejects_batches_above_its_scratch():
     # the entry point still works afterwards
     out = batch_run(X, [sets[0][:100]], [dict(set=0, k=2)], [P0], 1, noalloc=True)
     assert out["certified"][0, 0].item() == 1
+
+
+def _starts(rng, n, k, count):
+    return [np.linalg.qr(rng.standard_normal((n, k)))[0] for _ in range(count)]
+
+
+@pytest.mark.parametrize("count,fits", [(20, True), (200, False)])
+def test_noalloc_with_room_for_the_data_alone(count, fits):
+    """P of 96 KB per problem: the data of 200 problems take 22 MB of the fixed
+    scratch, with the second copy of P it would be 41 MB.  Accepted as ever, and
+    the results are those of the allocating call."""
+    rng = np.random.default_rng(6)
+    n, k, M = 1000, 12, 200
+    X = torch.from_numpy(rng.standard_normal((M, n))).to(DEV)
+    probs = [dict(set=0, k=k) for _ in range(count)]
+    P0s = _starts(rng, n, k, count)
+    ref = batch_run(X, [np.arange(M)], probs, P0s, 3)
+    data, second = ref["stats"]["scratch_bytes"], 8 * n * k * count
+    assert data <= 32 << 20 and (data + second <= 32 << 20) == fits
+    for _ in range(2):
+        _same(ref, batch_run(X, [np.arange(M)], probs, P0s, 3, noalloc=True))
+
+
+def test_library_holds_little_device_memory():
+    """What the first batch call of a process takes of the device, kernels and
+    fixed scratch: 32 MiB of it are the scratch."""
+    code = """
+import sys
+sys.path.insert(0, sys.argv[1])
+import numpy as np, torch
+torch.cuda.synchronize()
+X = torch.randn(100, 5, device="cuda", dtype=torch.float64)
+torch.cuda.synchronize()
+free = torch.cuda.mem_get_info()[0]
+import paper_1807_03425_amd as m
+m.batch_run(X, [np.arange(40)], [dict(set=0, k=2)], [np.eye(5)[:, :2]], 1)
+torch.cuda.synchronize()
+print("taken", (free - torch.cuda.mem_get_info()[0]) / 2 ** 20)
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", code, root], capture_output=True, text=True, timeout=100, check=True)
+    taken = float(out.stdout.split("taken")[1])
+    print(f"[memory] {taken} MiB")
+    assert taken < 56.0
