@@ -23,6 +23,8 @@
 // The library is compiled with -ffp-contract=off: every FMA below is
 // written explicitly, so a coarse value recomputed by the epilogue is
 // bit-identical to the one the pass reduced.
+#include <type_traits>
+
 #include "sap_common.h"
 
 namespace sap {
@@ -1406,9 +1408,9 @@ __device__ __forceinline__ void finish_pass_block(const SweepArgs<TX> &a, const 
 // Per pair: K subtractions, K FMAs, one multiply, one unsigned min.  Only an
 // item whose minimum lies inside the window of the block's running minimum
 // is scanned for candidates (emit_cands); they are rescored after the loop
-// (finish_pass_block).
-template <int K, typename TX>
-__device__ void fused_pass_block(const SweepArgs<TX> &a, int pb) {
+// (finish_pass_block), with the arguments that again() gives (k_pass).
+template <int K, typename TX, typename Again>
+__device__ __forceinline__ void fused_pass_block(const SweepArgs<TX> &a, int pb, Again again) {
     __shared__ int2 s_cij[kPairBlock / kWave][kCandCap];
     __shared__ uint32_t s_ckey[kPairBlock / kWave][kCandCap];
     __shared__ uint32_t s_run;
@@ -1514,12 +1516,7 @@ __device__ void fused_pass_block(const SweepArgs<TX> &a, int pb) {
         }
         item(std::false_type{});
     }
-    // (the arguments again from the kernel's argument segment: those that only
-    // the rescoring needs would otherwise hold scalar registers all through the
-    // sweep, which needs them for the y_i rows)
-    const auto *ka = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(ka));
-    const SweepArgs<TX> f = *(const SweepArgs<TX> *)ka;
+    const SweepArgs<TX> f = again();
     finish_pass_block<K, TX, true>(f, cl, kmin, &s_run, wb, s_cij, s_ckey, f.part + pb);
 }
 
@@ -1846,9 +1843,24 @@ __global__ __launch_bounds__(kPairBlock, (FUSED || sizeof(TX) == 4 || K <= 12) ?
         }
     }
     const int pb = (int)blockIdx.x - (FUSED ? nshort : 0);
-    if constexpr (FUSED) fused_pass_block<K, TX>(a, pb);
-    else plain_pass_block<K, TX>(a, pb);
+    if constexpr (FUSED) {
+        // a again, from the start of the kernel's argument segment (it is the
+        // first parameter, unmodified: asserted below): what only the rescoring
+        // needs of it would otherwise hold scalar registers all through the
+        // sweep, which needs them for the y_i rows
+        fused_pass_block<K, TX>(a, pb, []() __attribute__((always_inline)) {
+            const auto *ka = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
+            asm volatile("" : "+s"(ka));
+            return SweepArgs<TX>(*(const SweepArgs<TX> *)ka);
+        });
+    } else {
+        plain_pass_block<K, TX>(a, pb);
+    }
 }
+static_assert(std::is_same_v<decltype(&k_pass<1, float, true>), void (*)(SweepArgs<float>, int)> &&
+                  std::is_same_v<decltype(&k_pass<1, double, true>), void (*)(SweepArgs<double>, int)> &&
+                  std::is_trivially_copyable_v<SweepArgs<float>>,
+              "k_pass reads its first parameter from the start of the argument segment");
 
 // The K x n FP64 P into LDS, eight loads in flight per thread before any
 // is stored.
