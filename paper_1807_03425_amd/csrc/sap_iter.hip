@@ -575,12 +575,16 @@ typedef int int4_bits __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(4))) int4_bits *UniformI4;
 
 // R consecutive rows of Y (KP floats each) from a wavefront-uniform address,
-// whole rows (one or two scalar loads each).
+// whole rows (one or two scalar loads each).  Rows of 12 floats lie 48 bytes
+// apart: their first eight are aligned to 16 bytes, not to the 32 of a vector
+// type (a scalar load asks for 4).
 template <int KP, int R>
 __device__ __forceinline__ void load_rows(UniformF p, float (&y)[R][KP]) {
     constexpr int W = KP == 12 ? 4 : KP;
     typedef float vec __attribute__((ext_vector_type(W)));
-    typedef float vec8 __attribute__((ext_vector_type(8)));
+    typedef float vec8 __attribute__((ext_vector_type(8), aligned(16)));
+    static_assert(KP * sizeof(float) % alignof(vec) == 0 && (KP != 12 || KP * sizeof(float) % alignof(vec8) == 0),
+                  "a row of Y is aligned to its length's power of two");
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         if constexpr (KP == 12) {
