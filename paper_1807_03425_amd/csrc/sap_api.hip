@@ -651,6 +651,25 @@ static sap_status launch_prep(sap_ctx *h) {
     return SAP_OK;
 }
 
+// Whether the fused pass stages its y_i rows in LDS rather than loading them
+// as scalars (fused_pass_block): where a wavefront has few items and few others
+// beside it, it waits for every scalar miss.  us of the pass, staged and
+// scalar, n = 40 (256 compute units, an item per wavefront up to N = 4000 for k
+// <= 7, two for k >= 8):
+//   k <= 7: up to two blocks per compute unit (N = 1037, k = 6 5.3 and 6.4; N =
+//     2500 6.5 and 6.9; N = 3500 8.0 and 7.7), and from there on between one
+//     and three items per wavefront (N = 5000, k = 6 12.6 and 14.0, k = 1 11.5
+//     and 11.8; N = 7000 20.2 and 20.7; N = 8000 25.0 and 24.8);
+//   k = 8..15: up to one block per compute unit (N = 1037, k = 10 7.2 and 8.7;
+//     N = 1500, k = 12 7.9 and 8.3; N = 2000 8.7 and 8.4);
+//   k = 16: never (N = 130 8.1 and 7.0, N = 1037 8.7 and 9.0, N = 2000 9.9 and
+//     9.2).
+static bool pass_staged(const sap_ctx *h) {
+    const int64_t waves = 4 * (int64_t)h->pass_grid, halves = 2 * h->ntiles;
+    if (h->k >= 8) return h->k < 16 && h->pass_grid <= h->cus;
+    return h->pass_grid <= 2 * h->cus || (halves > waves && halves <= 3 * waves);
+}
+
 template <typename TX>
 static sap_status launch_pass(sap_ctx *h) {
     const int K = h->k;
@@ -659,7 +678,7 @@ static sap_status launch_pass(sap_ctx *h) {
     const int nshort = fused ? h->short_grid_it : 0;
     const dim3 g1((unsigned)(h->pass_grid + nshort)), blk(kPairBlock);
     SAP_DISPATCH_K(K, SAP_TRY(launch_with(h, 1, "k_pass", g1, blk, 0, [&](const LaunchCfg &c) {
-        return KLaunch<K, TX>::pass(c, fused, a, nshort);
+        return KLaunch<K, TX>::pass(c, fused, fused && pass_staged(h), a, nshort);
     })));
     return SAP_OK;
 }

@@ -1398,22 +1398,32 @@ __device__ __forceinline__ void finish_pass_block(const SweepArgs<TX> &a, const 
     block_reduce_partial(wb.r, wb.i, wb.j, wb.r2, wb.nwin, wb.nunits, wb.nviol, kmin, cl.limit, out, false, true);
 }
 
+__device__ __forceinline__ float component(const float4 &v, int r) {
+    return r == 0 ? v.x : r == 1 ? v.y : r == 2 ? v.z : v.w;
+}
+
 // Fused pass block pb.  Wavefront w = 4 pb + slot takes work items
 // h = w, w + nw, ...: item h covers 4G rows of tile t = h / IPT = (bi, bj)
 // (rows 64 bi + 4G (h % IPT) ..) against its 64 columns; G = 8 (a half-tile),
-// or 4 for K >= 8.  Its y_i rows come by scalar loads (each is the same for
-// every lane, and a VALU instruction takes one scalar operand for free): as
-// broadcasts from LDS they moved 4 KP x 64 bytes per row, as many LDS cycles
-// as the arithmetic has VALU cycles.  The next item's weights and y_j are
-// loaded during the current item.  The pass at N = 40000, k = 16: 780 us, 950
-// before (VALU floor 712, the 3.2 GB at a streaming kernel's rate 535); N =
-// 20000, k = 10: 159 and 182; N = 8000, k = 4: 29.8 and 35; N = 4000, k = 6:
-// 9.5 and 9.7.
+// or 4 for K >= 8.  Two forms of the sweep (pass_staged says which):
+//   scalar rows: an item's y_i rows come by scalar loads (each is the same for
+//     every lane, and a VALU instruction takes one scalar operand for free): as
+//     broadcasts from LDS they move 4 KP x 64 bytes per row, as many LDS cycles
+//     as the arithmetic has VALU cycles.  The next item's weights and y_j are
+//     loaded during the current item.  The pass at N = 40000, k = 16: 780 us,
+//     950 through LDS (VALU floor 712, the 3.2 GB at a streaming kernel's rate
+//     535); N = 20000, k = 10: 159 and 182; N = 4000, k = 6: 9.5 and 9.7;
+//   STAGED: an item's loads (weights, y_j, the rows) are issued together and the
+//     rows go through the wavefront's own LDS slice, read back as broadcasts
+//     (no other wavefront touches it, so no block barrier).  Scalar loads miss
+//     the scalar cache one line after another, which a wavefront with an item
+//     or two, and no others beside it, waits for: N = 1037, k = 5 6.6 us by
+//     scalar rows and 5.3 staged.
 // Per pair: K subtractions, K FMAs, one multiply, one unsigned min.  Only an
 // item whose minimum lies inside the window of the block's running minimum
 // is scanned for candidates (emit_cands); they are rescored after the loop
 // (finish_pass_block), with the arguments that again() gives (k_pass).
-template <int K, typename TX, typename Again>
+template <int K, bool STAGED, typename TX, typename Again>
 __device__ __forceinline__ void fused_pass_block(const SweepArgs<TX> &a, int pb, Again again) {
     __shared__ int2 s_cij[kPairBlock / kWave][kCandCap];
     __shared__ uint32_t s_ckey[kPairBlock / kWave][kCandCap];
@@ -1426,6 +1436,9 @@ __device__ __forceinline__ void fused_pass_block(const SweepArgs<TX> &a, int pb,
     // (half as many rows left a wait per 140 cycles of arithmetic, 10% of the
     // pass at k = 16; twice as many spill)
     constexpr int R = KP >= 12 ? 2 : KP == 8 ? 4 : 8;
+    // (STAGED: every wavefront's slice of the rows, float4 of them per lane)
+    constexpr int NF4 = (K <= 7 ? 8 : 4) * KP, NV = (NF4 + kWave - 1) / kWave;
+    __shared__ float4 s_y[STAGED ? kPairBlock / kWave : 1][STAGED ? NF4 : 1];
     if (threadIdx.x == 0) s_run = kKeyNone;
     __syncthreads();
     // work item: G groups of 4 rows against the tile's 64 columns (a
@@ -1439,7 +1452,7 @@ __device__ __forceinline__ void fused_pass_block(const SweepArgs<TX> &a, int pb,
     uint32_t kmin = kKeyNone;   // the wavefront's smallest key
     int64_t h = (int64_t)pb * (kPairBlock / kWave) + wv;
     // the current item's weights and y_j, its tile and the next item's
-    float4 w[G];
+    float4 w[G], yv[NV];
     float yj[K];
     int2 bt, btn;
     auto tile_of = [&](int64_t hh) __attribute__((always_inline)) {
@@ -1467,25 +1480,37 @@ __device__ __forceinline__ void fused_pass_block(const SweepArgs<TX> &a, int pb,
         // registers
         uint32_t key[4 * G];
         uint32_t lmin = kKeyNone;
-        float yr[2][R][KP];
-        load_rows<KP, R>(yi0, yr[0]);
+        if constexpr (STAGED) {
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int e0 = 0; e0 < 4 * G; e0 += R) {
-            wait_rows<KP, R>(yr[(e0 / R) & 1]);
-            if (e0 + R < 4 * G) load_rows<KP, R>(yi0 + (e0 + R) * KP, yr[(e0 / R + 1) & 1]);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int u = 0; u < NV; ++u)
+                if (lane + u * kWave < NF4) s_y[wv][lane + u * kWave] = yv[u];
+            __builtin_amdgcn_wave_barrier();
+            const float *yl = reinterpret_cast<const float *>(s_y[wv]);
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int e = e0 + r;
-                const float4 &w4 = w[e / 4];
-                const float wt = e % 4 == 0 ? w4.x : e % 4 == 1 ? w4.y : e % 4 == 2 ? w4.z : w4.w;
-                key[e] = __float_as_uint(pair_r2<K>(yr[(e0 / R) & 1][r], yj, wt));
-                asm volatile("" : "+v"(key[e]));   // computed here: deferred, the rows would outlive the scalar registers
+            for (int e = 0; e < 4 * G; ++e) {
+                key[e] = __float_as_uint(pair_r2<K>(yl + e * KP, yj, component(w[e / 4], e % 4)));
                 lmin = min(lmin, key[e]);
-                if constexpr (PF)
-                    if (e % 4 == 3) w[e / 4] = wn[(e / 4) * 64];
             }
-            __builtin_amdgcn_sched_barrier(0);
+        } else {
+            float yr[2][R][KP];
+            load_rows<KP, R>(yi0, yr[0]);
+#pragma unroll
+            for (int e0 = 0; e0 < 4 * G; e0 += R) {
+                wait_rows<KP, R>(yr[(e0 / R) & 1]);
+                if (e0 + R < 4 * G) load_rows<KP, R>(yi0 + (e0 + R) * KP, yr[(e0 / R + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int e = e0 + r;
+                    key[e] = __float_as_uint(pair_r2<K>(yr[(e0 / R) & 1][r], yj, component(w[e / 4], e % 4)));
+                    asm volatile("" : "+v"(key[e]));   // computed here: deferred, the rows would outlive the scalar registers
+                    lmin = min(lmin, key[e]);
+                    if constexpr (PF)
+                        if (e % 4 == 3) w[e / 4] = wn[(e / 4) * 64];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
         const uint32_t m = wave_min_u32_fast(lmin);
         kmin = min(kmin, m);
@@ -1505,13 +1530,30 @@ __device__ __forceinline__ void fused_pass_block(const SweepArgs<TX> &a, int pb,
             for (int c = 0; c < K; ++c) yj[c] = yjn[c];
         }
     };
-    if (h < nitem) {
-        bt = tile_of(h);
-        btn = tile_of(h + nw);
+    // the loads of item h
+    auto fetch = [&]() __attribute__((always_inline)) {
         const float4 *tp = weights(h);
 #pragma unroll
         for (int g = 0; g < G; ++g) w[g] = tp[g * 64];
+        bt = tile_of(h);
+        if constexpr (STAGED) {
+            const float4 *src =
+                reinterpret_cast<const float4 *>(a.Y + ((int64_t)bt.x * kTile + 4 * G * (int)(h % IPT)) * KP);
+#pragma unroll
+            for (int u = 0; u < NV; ++u) yv[u] = src[lane + u * kWave < NF4 ? lane + u * kWave : 0];
+        }
         load_yj<K>(a.Y, KP, (int64_t)bt.y * kTile + lane, yj);
+    };
+    if constexpr (STAGED) {
+        if (h < nitem) fetch();
+        while (h < nitem) {
+            item(std::false_type{});
+            h += nw;
+            if (h < nitem) fetch();
+        }
+    } else if (h < nitem) {
+        btn = tile_of(h + nw);
+        fetch();
         for (; h + nw < nitem; h += nw) {
             const int2 bt2 = tile_of(h + 2 * nw);
             item(std::true_type{});
@@ -1520,7 +1562,7 @@ __device__ __forceinline__ void fused_pass_block(const SweepArgs<TX> &a, int pb,
         }
         item(std::false_type{});
     }
-    const SweepArgs<TX> f = again();
+    const SweepArgs<TX> &f = again();   // (a value lives as long as the reference)
     finish_pass_block<K, TX, true>(f, cl, kmin, &s_run, wb, s_cij, s_ckey, f.part + pb);
 }
 
@@ -1837,7 +1879,7 @@ __device__ int2 select_min(const SweepArgs<TX> &a, int nparts, bool record, Part
 // barrier before selection.
 // Occupancy: four wavefronts per SIMD (128 registers); three (168) for the
 // plain form over FP64 data with K > 12, which would spill at 128.
-template <int K, typename TX, bool FUSED>
+template <int K, typename TX, bool FUSED, bool STAGED>
 __global__ __launch_bounds__(kPairBlock, (FUSED || sizeof(TX) == 4 || K <= 12) ? 4 : 3) void k_pass(SweepArgs<TX> a, int nshort) {
     if constexpr (FUSED) {
         if ((int)blockIdx.x < nshort) {
@@ -1847,22 +1889,24 @@ __global__ __launch_bounds__(kPairBlock, (FUSED || sizeof(TX) == 4 || K <= 12) ?
         }
     }
     const int pb = (int)blockIdx.x - (FUSED ? nshort : 0);
-    if constexpr (FUSED) {
+    if constexpr (!FUSED) {
+        plain_pass_block<K, TX>(a, pb);
+    } else if constexpr (STAGED) {
+        fused_pass_block<K, true, TX>(a, pb, [&]() __attribute__((always_inline)) -> const SweepArgs<TX> & { return a; });
+    } else {
         // a again, from the start of the kernel's argument segment (it is the
         // first parameter, unmodified: asserted below): what only the rescoring
         // needs of it would otherwise hold scalar registers all through the
         // sweep, which needs them for the y_i rows
-        fused_pass_block<K, TX>(a, pb, []() __attribute__((always_inline)) {
+        fused_pass_block<K, false, TX>(a, pb, []() __attribute__((always_inline)) {
             const auto *ka = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
             asm volatile("" : "+s"(ka));
             return SweepArgs<TX>(*(const SweepArgs<TX> *)ka);
         });
-    } else {
-        plain_pass_block<K, TX>(a, pb);
     }
 }
-static_assert(std::is_same_v<decltype(&k_pass<1, float, true>), void (*)(SweepArgs<float>, int)> &&
-                  std::is_same_v<decltype(&k_pass<1, double, true>), void (*)(SweepArgs<double>, int)> &&
+static_assert(std::is_same_v<decltype(&k_pass<1, float, true, false>), void (*)(SweepArgs<float>, int)> &&
+                  std::is_same_v<decltype(&k_pass<1, double, true, false>), void (*)(SweepArgs<double>, int)> &&
                   std::is_trivially_copyable_v<SweepArgs<float>>,
               "k_pass reads its first parameter from the start of the argument segment");
 

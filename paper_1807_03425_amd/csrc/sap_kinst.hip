@@ -23,11 +23,10 @@ hipError_t KLaunch<K, TX>::prep(const LaunchCfg &c, const SweepArgs<TX> &a, cons
 }
 
 template <int K, typename TX>
-hipError_t KLaunch<K, TX>::pass(const LaunchCfg &c, bool fused, const SweepArgs<TX> &a, int nshort) {
-    if (fused)
-        hipExtLaunchKernelGGL(k_pass<K, TX, true>, c.grid, c.block, c.shmem, c.stream, c.ea, c.eb, 0, a, nshort);
-    else
-        hipExtLaunchKernelGGL(k_pass<K, TX, false>, c.grid, c.block, c.shmem, c.stream, c.ea, c.eb, 0, a, nshort);
+hipError_t KLaunch<K, TX>::pass(const LaunchCfg &c, bool fused, bool staged, const SweepArgs<TX> &a, int nshort) {
+    auto *const kernel = !fused ? &k_pass<K, TX, false, false>
+                                : (staged ? &k_pass<K, TX, true, true> : &k_pass<K, TX, true, false>);
+    hipExtLaunchKernelGGL(kernel, c.grid, c.block, c.shmem, c.stream, c.ea, c.eb, 0, a, nshort);
     return hipGetLastError();
 }
 

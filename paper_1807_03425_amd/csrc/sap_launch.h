@@ -21,7 +21,7 @@ struct KLaunch {
     // the iteration (sap_iter.hip)
     static hipError_t prep(const LaunchCfg &c, const SweepArgs<TX> &a, const double *mu, float *Y,
                            int64_t Npad);
-    static hipError_t pass(const LaunchCfg &c, bool fused, const SweepArgs<TX> &a, int nshort);
+    static hipError_t pass(const LaunchCfg &c, bool fused, bool staged, const SweepArgs<TX> &a, int nshort);
     static hipError_t select(const LaunchCfg &c, bool fused, const SweepArgs<TX> &a, int nshort,
                              double *P64t, void *Pr, int pr_kind, double alpha, int rule, int do_step);
     static hipError_t selprep(const LaunchCfg &c, const SweepArgs<TX> &a, int nshort, double *Pn,
