@@ -321,39 +321,54 @@ __global__ __launch_bounds__(256) void k_mark_close(float4 *invd2, const int2 *t
 
 // P (n x k row-major) -> the FP64 master (k x n), if it is finite and
 // max |P^T P - I| <= tol; both verdicts go to host memory.  One block, P in
-// chunks of rows through LDS; a thread per entry (a <= b) of P^T P, its sum in
-// the order of the rows.  On the host (P copied out, k^2 serial sums, a
-// transposed copy back) a set_P took 36 us at n = 64, k = 6 and 52 at n =
-// 1024, k = 8; 16 and 36 with this.
+// chunks of rows through LDS.  The sums of P^T P are shared by up to 32 threads
+// per entry (a <= b); where one lies so close to tol that their
+// order could decide, they are formed again in the order of the rows, a thread
+// per entry, and that is the verdict (a thread per entry throughout took 96 us
+// at n = 4800, k = 1).  On the host (P copied out, k^2 serial sums,
+// a transposed copy back) a set_P took 39 us at n = 64, k = 6, 54 at n = 1024,
+// k = 8 and 30 at n = 4800, k = 1; 20, 27 and 27 with this.
 constexpr double kOrthoTol = 1e-6;
-constexpr int kLoadP = 1024, kLoadPRows = 256;
+constexpr int kLoadP = 1024, kLoadPElems = 4096;
 __global__ __launch_bounds__(kLoadP) void k_load_P(const double *__restrict__ P, int n, int k, double tol,
                                                    double *__restrict__ P64t, double *__restrict__ ortho,
                                                    int32_t *__restrict__ finite) {
-    __shared__ double s_p[kLoadPRows * 16];
-    __shared__ double s_e[kLoadP / kWave];
-    const int tid = threadIdx.x;
-    const int a = tid / k, b = tid % k;
-    const bool entry = a <= b && a < k;
+    __shared__ double s_p[kLoadPElems];
+    __shared__ double s_part[kLoadP], s_e[kLoadP / kWave];
+    const int tid = threadIdx.x, kk = k * k, chunk = kLoadPElems / k;
+    const int part = tid / kk, a = tid % kk / k, b = tid % k;
     int bad = 0;
-    double acc = 0.0;
-    for (int l0 = 0; l0 < n; l0 += kLoadPRows) {
-        const int rows = n - l0 < kLoadPRows ? n - l0 : kLoadPRows;
-        for (int e = tid; e < rows * k; e += kLoadP) {
-            const double v = P[(int64_t)l0 * k + e];
-            bad |= !isfinite(v);
-            s_p[e] = v;
-        }
-        __syncthreads();
-        if (entry) {
+    // |P^T P - I| of the thread's entry, its rows shared by `parts` threads (0
+    // for the threads beside the first of an entry)
+    auto deviation = [&](int parts) {
+        double acc = 0.0;
+        for (int l0 = 0; l0 < n; l0 += chunk) {
+            const int rows = n - l0 < chunk ? n - l0 : chunk;
+            for (int e = tid; e < rows * k; e += kLoadP) {
+                const double v = P[(int64_t)l0 * k + e];
+                bad |= !isfinite(v);
+                s_p[e] = v;
+            }
+            __syncthreads();
+            if (a <= b && part < parts) {
 #pragma unroll 8
-            for (int l = 0; l < rows; ++l) acc += s_p[l * k + a] * s_p[l * k + b];
+                for (int l = part; l < rows; l += parts) acc += s_p[l * k + a] * s_p[l * k + b];
+            }
+            __syncthreads();
         }
+        s_part[tid] = acc;
         __syncthreads();
-    }
+        if (part > 0 || a > b) return 0.0;
+#pragma unroll 8
+        for (int q = 1; q < parts; ++q) acc += s_part[q * kk + tid];
+        const double d = fabs(acc - (a == b ? 1.0 : 0.0));
+        return d >= 0.0 ? d : 0.0;   // (inf - inf off the diagonal: the diagonal is inf)
+    };
+    double e = deviation(max(1, min(min(kLoadP / kk, 32), n / 8)));
     bad = __syncthreads_or(bad);
-    const double d = fabs(acc - (a == b ? 1.0 : 0.0));
-    double e = entry && d >= 0.0 ? d : 0.0;   // (inf - inf off the diagonal: the diagonal is inf)
+    // two orders of a sum of n products are within 2 n 2^-53 sum |p q| of each
+    // other, and sum |p q| is below 2 unless a diagonal entry is far above tol
+    if (__syncthreads_or(fabs(e - tol) <= (n + 8.0) * 0x1p-50)) e = deviation(1);
     for (int m = 1; m < kWave; m <<= 1) {
         const double o = __shfl_xor(e, m, kWave);
         e = o > e ? o : e;

@@ -139,3 +139,50 @@ def test_P_in_host_memory():
     h, _ = _handle()
     assert lib().sap_softmin_fwd(h.handle, ptr(same.clone()), 0.05, ptr(loss)) != 0
     h.close()
+
+
+@pytest.mark.parametrize("n,k", [(4800, 1), (700, 3), (257, 7), (40, 16)])
+def test_set_P_at_the_tolerance(n, k):
+    """Columns whose |P^T P - I| lies within some 1e-16 of 1e-6, above and
+    below: accepted exactly where the sum of the rounded products in the order
+    of the rows says so."""
+    g = np.random.default_rng(n)
+    X = torch.from_numpy(g.standard_normal((30, n))).to(DEV)
+    P0 = np.linalg.qr(g.standard_normal((n, k)))[0]
+    h = SapContext(X, torch.from_numpy(P0), form="fused")
+    verdicts = []
+    for t in range(-30, 31):
+        P = P0.copy()
+        P[:, k // 2] *= np.sqrt(1.0 + 1e-6 + 4e-17 * t * (n ** 0.5 / 10.0))
+        G = np.array([[np.cumsum(P[:, a] * P[:, b])[-1] for b in range(k)] for a in range(k)])
+        want = bool(np.abs(G - np.eye(k)).max() <= 1e-6)
+        try:
+            h.set_P(torch.from_numpy(P).to(DEV))
+            got = True
+        except SapError as e:
+            assert "NOT_ORTHONORMAL" in str(e)
+            got = False
+        assert got == want, (t, np.abs(G - np.eye(k)).max() - 1e-6)
+        verdicts.append(want)
+    assert 5 < sum(verdicts) < 56, sum(verdicts)
+    h.close()
+
+
+def test_set_P_of_long_columns_takes_no_longer():
+    """The check's sums are shared by threads: a column of 4800 takes about as
+    long as six of 64 (one thread's sum over it took five times as long)."""
+    import time
+    best = []
+    for n, k in ((64, 6), (4800, 1)):
+        X = torch.from_numpy(np.random.default_rng(n).standard_normal((30, n))).to(DEV)
+        P = torch.from_numpy(np.linalg.qr(np.random.default_rng(k).standard_normal((n, k)))[0])
+        with SapContext(X, P, form="fused") as h:
+            Pd, t = P.to(DEV), []
+            for _ in range(60):
+                torch.cuda.synchronize()
+                t0 = time.perf_counter()
+                h.set_P(Pd)
+                t.append(time.perf_counter() - t0)
+        best.append(min(t))
+    print(f"[set_P] {1e6 * best[0]:.0f} us at 64 x 6, {1e6 * best[1]:.0f} at 4800 x 1")
+    assert best[1] < 3.0 * best[0]
