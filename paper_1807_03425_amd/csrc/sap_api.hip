@@ -320,6 +320,23 @@ static sap_status launch_moments(sap_ctx *h, double *part, int64_t nblk, int64_t
     return SAP_OK;
 }
 
+// What the column kernels found: X finite, and the radius.
+static sap_status take_moments(sap_ctx *h, const DevState &st) {
+    if (st.nonfinite) return fail(h, SAP_ERR_NONFINITE, "X holds NaN or Inf");
+    std::memcpy(&h->radius, &st.radius_bits, sizeof h->radius);
+    return SAP_OK;
+}
+
+// Bytes of a plain handle's secant array.
+static size_t secant_bytes(const sap_ctx *h) {
+    return (h->cfg.dtype == SAP_F64 ? 8 : 4) * (size_t)h->n * (size_t)(ceil_div(h->p, kChunk) * kChunk);
+}
+
+// Whether the secants are built before it is known that X is finite: one wait
+// less (9 us, what the pinned read-back block costs), where building them for
+// nothing costs little.
+static bool one_wait(const sap_ctx *h) { return h->cfg.form == SAP_PLAIN && secant_bytes(h) <= (1 << 20); }
+
 static sap_status init_moments(sap_ctx *h) {
     const int64_t rows = 256;
     const int64_t nblk = ceil_div(h->N, rows);
@@ -328,13 +345,10 @@ static sap_status init_moments(sap_ctx *h) {
     SAP_HIP(h, hipMemsetAsync(h->d_st, 0, sizeof(DevState), h->stream));
     if (h->cfg.dtype == SAP_F64) SAP_TRY(launch_moments<double>(h, part, nblk, rows));
     else SAP_TRY(launch_moments<float>(h, part, nblk, rows));
+    if (one_wait(h)) return SAP_OK;
     DevState st;
     SAP_TRY(read_state(h, &st));
-    if (st.nonfinite) return fail(h, SAP_ERR_NONFINITE, "X holds NaN or Inf");
-    double r;
-    std::memcpy(&r, &st.radius_bits, sizeof r);
-    h->radius = r;
-    return SAP_OK;
+    return take_moments(h, st);
 }
 
 static sap_status init_plain(sap_ctx *h) {
@@ -342,7 +356,7 @@ static sap_status init_plain(sap_ctx *h) {
     const size_t es = f64 ? 8 : 4;
     h->pcols = ceil_div(h->p, kChunk) * kChunk;
     h->nchunks = h->pcols / kChunk;
-    SAP_TRY(dalloc(h, &h->d_S, es * (size_t)h->n * (size_t)h->pcols));
+    SAP_TRY(dalloc(h, &h->d_S, secant_bytes(h)));
     SAP_TRY(dalloc(h, &h->d_Pr, es * (size_t)h->n * h->k));
     const unsigned grid = (unsigned)std::min<int64_t>(ceil_div(h->pcols, 256), 65536);
     auto *kept = reinterpret_cast<unsigned long long *>(&h->d_st->kept);
@@ -358,6 +372,7 @@ static sap_status init_plain(sap_ctx *h) {
     SAP_LAUNCHED(h, "k_build_secants");
     DevState st;
     SAP_TRY(read_state(h, &st));
+    SAP_TRY(take_moments(h, st));
     h->kept = st.kept;
     h->dropped = st.dropped;
     // |c~ - c| <= (n+3) u sqrt(k) (rounded secants and P, FMA accumulation),

@@ -24,7 +24,7 @@ pytestmark = pytest.mark.gpu
 if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
-from paper_1807_03425_amd import SapContext  # noqa: E402
+from paper_1807_03425_amd import SapContext, SapError  # noqa: E402
 
 DEV = torch.device("cuda:0")
 
@@ -55,3 +55,28 @@ def test_tiles_at_chunk_and_tile_edges(dtype, N, n, pad, min_len):
     want = oracle.softmin(X, P0.astype(np.float32).astype(np.float64), tau, min_len=min_len)["L"]
     tol = info["e_abs"] + info["e_rel"] + tau * 2.0 ** -18 + abs(want) * 2.0 ** -23
     assert abs(L - want) <= tol, (L, want, tol)
+
+
+@pytest.mark.parametrize("form", ["plain", "fused"])
+@pytest.mark.parametrize("N,n", [(2, 3), (20, 7), (600, 9)])   # plain: a secant array below and above 1 MB
+def test_refused_points(N, n, form):
+    """NaN and Inf in X, every pair a duplicate, and both: the same refusals
+    whether or not the secants are built before X is known to be finite."""
+    g = np.random.default_rng(N)
+    good = g.standard_normal((N, n))
+    P = torch.from_numpy(np.linalg.qr(g.standard_normal((n, 2)))[0])
+
+    def refused(X):
+        try:
+            SapContext(torch.from_numpy(X).to(DEV), P, form=form).close()
+        except SapError as e:
+            return str(e).split(":")[0]
+    for bad in (np.nan, np.inf, -np.inf):
+        X = good.copy()
+        X[N - 1, n - 1] = bad
+        assert refused(X) == "SAP_ERR_NONFINITE"
+    same = np.repeat(good[:1], N, axis=0)
+    assert refused(same) == "SAP_ERR_NO_PAIRS"
+    same[0, 0] = np.nan
+    assert refused(same) == "SAP_ERR_NONFINITE"
+    assert refused(good) is None
