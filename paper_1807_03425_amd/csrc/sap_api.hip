@@ -868,9 +868,11 @@ static SmArgs sm_args(sap_ctx *h, double tau) {
     a.vp = h->vec_p;
     a.gemm = h->cfg.gemm;
     a.tau = tau;
-    a.c2 = (float)(1.4426950408889634 / tau);   // log2(e) / tau
+    a.c2d = 1.4426950408889634 / tau;   // log2(e) / tau
+    a.c2 = (float)a.c2d;
     a.part = h->d_smpart;
     a.Lp = &h->d_st->sm_L;
+    a.mp = &h->d_st->sm_m;
     a.nshares = h->sm_nshares;
     a.layer = h->sm_layer;
     a.share = a.nhalf / a.nshares;

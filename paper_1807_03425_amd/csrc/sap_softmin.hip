@@ -57,8 +57,9 @@ struct SmArgs {
     int gemm;              // arithmetic of the Y GEMM (SAP_GEMM_*)
     double tau;
     float c2;              // log2(e) / tau
+    double c2d;            // the same in FP64
     SmPart *part;          // npass + nshort partials (forward)
-    const double *Lp;      // L of the forward (backward)
+    const double *Lp, *mp; // the forward's L and the reference of its sum (backward)
     // backward partials
     int nshares, layer;        // shares, blocks of a round over the compute units
     int64_t share;             // half-tiles per share, rounded down, and the rest
@@ -563,11 +564,15 @@ __global__ __launch_bounds__(kZredWaves * kWave) void k_sm_zred(SmArgs a, int64_
         for (uint64_t hit = __ballot(bi <= b && share_start(a, w) == x); hit; hit &= hit - 1)
             add1(a.Zc + (a.ntiles + __shfl(w, __ffsll((unsigned long long)hit) - 1, kWave)) * len + lane);
     }
-    // the tile weights were taken at L c2 rounded to FP32, the same for every
-    // pair: what the rounding took from their exponent is put back here (the
-    // short pairs' weights are FP64)
-    const double Lc = *a.Lp * (double)a.c2;
-    const double corr = exp2(Lc - (double)((float)(*a.Lp) * a.c2));
+    // the tile weights were taken at L c2 rounded to FP32, and c2 itself is
+    // rounded: what that took from their exponent, the same for every pair, is
+    // put back here (the short pairs' weights are FP64).  The weights sum to 1
+    // when L - m (m the reference of the forward's sum, the r that count are
+    // near it) takes the exact c2 and m, as r, the rounded one: with L c2 the
+    // gradient was off by (m - L) / tau times c2's rounding, 2e-7 to 5e-7 of it
+    // where tau is 0.3.
+    const double L = *a.Lp, m = *a.mp;
+    const double corr = exp2(m * (double)a.c2 + (L - m) * a.c2d - (double)((float)L * a.c2));
 #pragma unroll
     for (int q = 0; q < K; ++q) z[q] *= corr;
     const int64_t p = b * kTile + lane;

@@ -101,3 +101,36 @@ def test_column_sums_keep_the_bits_of_two_half_tiles(k):
     print(f"[column] k={k}: mean {np.mean(err) / u:.2f} u, max {np.max(err) / u:.2f} u, "
           f"two sums of 32: {np.mean(ref) / u:.2f} u")
     assert np.mean(err) <= np.mean(ref) + u
+
+
+@pytest.mark.parametrize("tau0", [0.25, 0.8, 1.6])
+@pytest.mark.parametrize("k", [2, 8, 16])
+def test_gradient_weights_sum_to_one(k, tau0):
+    """The weights' exponents use log2(e)/tau rounded to FP32, by 2^-25 to 2^-24
+    of it at the tau taken here.  That leaves their sum, and with it the length
+    of the gradient, off by at most its part of (max r - min r)/tau; the
+    roundings of single pairs (2 million of them) scatter, and are allowed u.
+    Times log(pairs) it would be 14 units of the first."""
+    u = 2.0 ** -24
+    taus = tau0 * (1.0 + np.arange(200) * 1e-3)
+    c2 = 1.4426950408889634 / taus
+    delta = np.abs(c2.astype(np.float32).astype(np.float64) / c2 - 1.0)
+    tau, delta = float(taus[delta.argmax()]), float(delta.max())
+    assert delta > 2.0 ** -25
+    g = torch.Generator(device=DEV).manual_seed(k)
+    X = torch.randn(2000, 40, generator=g, device=DEV, dtype=torch.float64)
+    P = torch.linalg.qr(torch.randn(40, k, generator=g, device=DEV, dtype=torch.float64))[0].float()
+    with SapContext(X, P.double().cpu(), form="fused") as ctx:
+        ctx.softmin_fwd(P, tau)
+        got = ctx.softmin_bwd(P, tau, torch.ones(1, device=DEV)).double()
+    Y = (X - X.mean(0)) @ P.double()
+    d = torch.cdist(X, X, compute_mode="donot_use_mm_for_euclid_dist")
+    r = torch.cdist(Y, Y, compute_mode="donot_use_mm_for_euclid_dist") / d
+    r.fill_diagonal_(float("inf"))
+    rmin, rmax = float(r.min()), float(r[torch.isfinite(r)].max())
+    w = torch.exp(-(r - rmin) / tau)
+    a = torch.where(torch.isfinite(r), w / (0.5 * w.sum()) / (d * d * r), torch.zeros_like(d))
+    want = (X - X.mean(0)).T @ (a.sum(1, keepdim=True) * Y - a @ Y)
+    scale = float((got * want).sum() / (want * want).sum() - 1.0)
+    print(f"[scale] k={k} tau={tau:.3f}: {scale / u:+.2f} u, rounding of log2(e)/tau {delta / u:.2f} u")
+    assert abs(scale) <= delta * (rmax - rmin) / tau + u
