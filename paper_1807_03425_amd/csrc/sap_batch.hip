@@ -22,7 +22,9 @@
 // One workgroup per problem for the whole run -- no launches between the
 // phases, but 4 wavefronts on one compute unit -- took 52 us per iteration at
 // 30 problems of 256 points (n = 15) and 184 us at 60 of 512 points (n =
-// 200), against 21 and 43 us.
+// 200), against 21 and 43 us.  Batches whose sets are all small enough run that
+// way (k_batch_run; one_block_per_problem draws the line), and batches whose
+// two-launch buffers do not fit the fixed scratch.
 //
 // Y stays FP64, so the coarse error is that of the FP64 product (no pair is
 // too short for it and there is no short-pair list); keys round to FP32.

@@ -202,7 +202,7 @@ __device__ __forceinline__ float comp4(const float4 &v, int r) {
 // a length: next to coordinates of 1e-15 1e-36 is not small any more.
 // Bound by VALU issue, 2K + 8 instructions per pair (142 us at N = 20000, k =
 // 10 if sqrt and exp2 took one slot each): 157 to 172 us from card to card; 224
-// with the y_i rows through LDS, 8192 blocks and two instructions more per
+// with the y_i rows through LDS, 8192 blocks and an instruction more per
 // pair.  N = 1531, k = 3: 6 us (10).
 template <int K>
 __global__ __launch_bounds__(kPairBlock, 4) void k_sm_fwd(SmArgs a) {
@@ -356,8 +356,8 @@ __device__ __forceinline__ int share_of(const SmArgs &a, int64_t p) {
 // once more for a tile whose halves fall in two shares.  Per half-tile and
 // point-major they were 377 MB written and read again at N = 20000, k = 10
 // (k_sm_zred 90 us, 32 now, traced).
-// Bound by issue: 3K + 8 VALU instructions per pair, a sixth more around the
-// products, and the FP64 products, which other wavefronts' VALU work covers in
+// Bound by issue: 3K + 8 VALU instructions per pair, K/8 for the sums by eights,
+// a sixth more around the products, and the FP64 products, which other wavefronts' VALU work covers in
 // part: N = 20000, k = 10 383 us (407 with a block per half-tile and the rows
 // through LDS), N = 14000, k = 16 250 (296), N = 9000, k = 10 85 (79: the merge
 // gained what this lost, 6 us).
