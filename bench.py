@@ -138,7 +138,7 @@ def sap_leg(torch, np, w, form, steps, warmup, gemm="f64", prof_steps=None, keep
         gbs = bytes_launch / (pass_us * 1e-6) / 1e9
         out["roofline"] = dict(bound="hbm", achieved=gbs, peak=HBM_PEAK_GBS, unit="GB/s",
                                frac=gbs / HBM_PEAK_GBS, kernel=f"sap::k_pass<{w.k}, "
-                               # the last argument: no workload here is small enough for staged rows
+                               # the last argument: rows staged in LDS, which is for smaller sets
                                f"{'float' if es == 4 else 'double'}, {'true' if form == 'fused' else 'false'}, false>",
                                bytes_per_launch=bytes_launch, avg_launch_us=pass_us)
         if form == "fused":
